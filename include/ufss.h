@@ -478,10 +478,14 @@ int ufss_autotune(ufss_plan_t plan, const char* cache_path, int32_t flags,
 
 /* Tiling of the GEMM path (what ufss_autotune chooses by timing).  In
  * ufss_plan_set_tiling a field of 0 keeps the plan's current value.
- *   fwd_split   parts of the forward GEMM's d_y range, 1..64
- *   adj_split   parts of the adjoint GEMM's d_y range, 1..64
+ *   fwd_split   parts of the forward GEMM's d_y range, 1..64 (FP32 B-scans: of
+ *               its |d_x| range)
+ *   adj_split   parts of the adjoint GEMM's d_y range, 1..64 (FP32: of its
+ *               (bin chunk, |d_y|) steps; FP32 B-scans: of its |d_x| range)
  *   fwd_waves   FP32 forward: 16-bin sub-tiles (waves) per workgroup, 1..8
- *   fwd_zsplit  forward: parts of the depth range, 1..64 (FP32 and BF16)
+ *   fwd_zsplit  forward: parts of the depth range, 1..64 (FP32 and BF16; an
+ *               FP32 C-scan deals its (depth chunk, |d_y|) steps to fwd_split x
+ *               fwd_zsplit equal parts)
  *   fwd_tile, adj_tile    FP32: 16-position sub-tiles per wave, 2 or 4;
  *               BF16 (adj_tile only): 16-depth sub-tiles per adjoint wave, 2
  *               or 4 (2: half-height depth tiles, twice the workgroups)

@@ -610,10 +610,12 @@ int autotune(Plan& P, const char* cache_path, int flags, hipStream_t s, int32_t*
         if (cache[key].size() >= 14) P.adj_nw = (int)cache[key][13];
         plan_set_splits(P, (int)cache[key][0], (int)cache[key][1], (int)cache[key][5]);
     } else {
+        // parts: up to the rows of a C-scan's window; up to the a_x values of an
+        // FP32 B-scan (the BF16 kernels split rows only)
         const int tpy = P.g.ny == 1 ? 1 : 4;
-        const int ndy = std::min(2 * P.d.wy + 1, P.g.ny + tpy - 1);
+        const int ndy = P.g.ny == 1 && P.dtype == UFSS_F32 ? P.d.wx + 1 : std::min(2 * P.d.wy + 1, P.g.ny + tpy - 1);
         std::vector<int> cand;
-        for (int c : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32})
+        for (int c : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64})
             if (c <= ndy) cand.push_back(c);
         // inputs: the plan's own workspace vectors hold finite values
         UFSS_HIP(hipMemsetAsync(P.d_gamma, 0, P.nvox * sizeof(cf32), s));

@@ -5,14 +5,27 @@
 // dense complex product between the phase matrix P_d[k, z] and the depth
 // profiles of the voxels at p - d.  Instead of the paper's FFT-based
 // correlation (Alg. 2) the window is summed directly, one small GEMM per
-// offset, which puts the work on the matrix cores:
+// offset, which puts the work on the matrix cores.  P_d depends on (|d_x|,
+// |d_y|) only, so the (up to four) voxels at mirrored offsets are added first
+// and share one product:
 //
-//   forward  Y[p, k] = sum_{d in W} sum_z  P_d[k, z] x[p - d, z]
-//   adjoint  G[v, z] = sum_{d in W} sum_k  conj(P_d[k, z]) R[v + d, k]
+//   forward  Y[p, k] = sum_{a in [0, W]} sum_z P_a[k, z] sum_{d = (+-a_x, +-a_y)} x[p - d, z]
+//   adjoint  G[v, z] = sum_{a in [0, W]} sum_k conj(P_a[k, z]) sum_{d = (+-a_x, +-a_y)} R[v + d, k]
 //
-// with P_d[k, z] = exp(-j 2 pi (k * u(|d|, z) mod 2^32) / 2^32), u the
-// integer-turn delay table built by the plan.  H_k scaling, gathers for
-// per-position subsets and residuals live in the small pre/post kernels.
+// with P_a[k, z] = exp(-j 2 pi (k * u(a, z) mod 2^32) / 2^32), u the
+// integer-turn delay table built by the plan (a zero component has one sign,
+// voxels outside the grid are zero).  H_k scaling, gathers for per-position
+// subsets and residuals live in the small pre/post kernels.
+//
+// What bounds it: the FP32 MFMAs and the VALU work share issue cycles on this
+// chip, so the cost is products + phasors + mirror additions.  One product per
+// mirrored offset group is about a quarter of the products and phasors of one
+// per offset when the window is narrow against the grid (0.28 on the 64 x 64
+// C-scan with W = 16) and about half on a full aperture (0.58 at 32 x 32).
+// Core kernels before and after: 64 x 64 x 512 (128 bins, W = 16) forward 12.4 ->
+// 4.0 ms, adjoint 13.3 -> 4.0 ms; 32 x 32 x 256 (66 bins, full) 1.20 -> 0.73 and
+// 1.23 -> 0.75 ms; 32-position B-scan (128 depths, 32 bins) 0.26 -> 0.013 and
+// 0.067 -> 0.014 ms (there from the parts, below).
 //
 // MFMA: v_mfma_f32_16x16x4_f32.  Lane l holds A[i = l%16][k = l/16],
 // B[k = l/16][j = l%16] and D[i = 4(l/16) + r][j = l%16] for r = 0..3.
@@ -20,13 +33,20 @@
 // (Gauss's form: one product of sums, two products with combined phasors).
 //
 // Tiling (both kernels): a workgroup of 4 waves owns one lateral tile of
-// NP sub-tiles of 16 positions (sw x 16/sw each, sw = 4 for C-scans, 16 for
+// NP sub-tiles of 16 positions (SW x 16/SW each, SW = 4 for C-scans, 16 for
 // B-scans).  Forward: each wave owns 16 bins, the 4 waves cover 64 bins.
-// Adjoint: each wave owns NZ x 16 depths.  The shifted input rows for one d_y
-// and one chunk of the reduction axis are staged in LDS (zero outside the
-// grid); phasors are generated per lane in registers.  Accumulation is two
-// level (per d_y in MFMA registers, then into an outer FP32 sum) to keep the
-// FP32 error of ~1e5-term sums near 1e-6.
+// Adjoint: each wave owns 16 depths.  For one a_y and one chunk of the
+// reduction axis the rows at +-a_y are added while they are staged in LDS
+// (zero outside the grid); the columns at +-a_x are two LDS reads and an
+// addition per operand.  Phasors are generated per lane in registers.
+// Accumulation is two level (per a_y in MFMA registers, then into an outer
+// FP32 sum) to keep the FP32 error of ~1e5-term sums near 1e-6.
+//
+// Parts: split-K partials go to separate output slots that the epilogues sum
+// in fixed order.  On a C-scan the (chunk of the reduction axis, a_y) steps of
+// a tile are dealt to its parts in equal contiguous ranges; a B-scan has one
+// a_y, so its parts divide the a_x range instead (a 32-position B-scan is one
+// lateral tile: without that it runs on 1 or 2 of the 256 CUs).
 #include <type_traits>
 
 #include "internal.h"
@@ -44,50 +64,155 @@ __device__ __forceinline__ void phasor(uint32_t ku, float& c, float& s) {
     s = __builtin_amdgcn_sinf(ph);              // sin(2 pi ph)
 }
 
-// Stages rows x hc cells of `chunk` consecutive complex values into LDS
-// (cell stride cs, row pitch `pitch` cells), zero outside the grid or past
-// `ilim` along the inner axis.  Grid row gy = ybase + r lands in row slot
-// gy & slot_mask, so a window of slot_mask + 1 consecutive rows that moves by
-// one row only needs the entering row staged:
-//   halo[((gy & slot_mask) * pitch + c) * cs + e] = src[(gy * nx + xbase + c) * ld + i0 + e].
-// `chunk` is a power of two dividing blockDim.x, so each thread keeps one inner
-// index and walks the cells with a fixed step; UNR independent loads are in
-// flight per thread before their LDS stores.
-template <int UNR>
-__device__ __forceinline__ void stage_halo(cf32* __restrict__ halo, int cs, int rows, int hc, int pitch, int slot_mask, int chunk,
-                                           const cf32* __restrict__ src, int ny, int nx, int64_t ld,
-                                           int ybase, int xbase, int i0, int ilim) {
-    const int e = threadIdx.x & (chunk - 1);
-    const int step = blockDim.x / chunk;
-    const int total = rows * hc;
-    int cell = threadIdx.x / chunk;
-    int r = cell / hc, c = cell - r * hc;
+// ---- LDS layout of the staged rows -----------------------------------------
+// tpy rows of hc = tpx + 2 wx cells (the columns a tile reaches; those outside
+// the grid stay zero), CH complex values per cell at a stride of cell_stride
+// values, then a run of zero cells that stands in for the mirrored columns at
+// a_x = 0.  Strides: 16-byte aligned cells for the 16-byte reads below, and
+// rows 64 bytes apart modulo the 256-byte bank period, so the 4 x 4 cells that
+// 16 lanes read together (cells 144 or 80 bytes apart) touch every bank once.
+__host__ __device__ constexpr int cell_stride(int ch) { return ch == 4 ? 5 : ch + 2; }
+__host__ __device__ static inline int row_pitch(int hc, int ch) {
+    const int raw = hc * cell_stride(ch);
+    return raw + ((8 - raw) & 31);
+}
+__host__ __device__ static inline int zero_run(int np, int sw, int ch) {
+    return (((np - 1) * sw + 1) * cell_stride(ch) + 1) & ~1;
+}
+
+// Stages rows r < TPY, grid columns [x_lo, x_hi], CH values of the reduction
+// axis from i0 on: halo[r pitch + (x - xb) cs + e] = src[y0 + r - ay][x][i0 + e]
+// (+ src[y0 + r + ay][x][i0 + e] for ay > 0), rows outside the grid counting as
+// zero, nothing at or past `ilim`.  Each thread keeps one e and walks the
+// columns with a fixed step, U columns of each of the TPY rows (8 loads) in
+// flight; whether a row is inside the grid is uniform.
+template <int CH, int TPY>
+__device__ __forceinline__ void stage_mirrored(cf32* __restrict__ halo, int pitch, const cf32* __restrict__ src,
+                                               int ny, int nx, int64_t ld, int y0, int ay, int xb, int x_lo,
+                                               int x_hi, int i0, int ilim) {
+    constexpr int cs = cell_stride(CH);
+    constexpr int U = 4 / TPY;
+    const int e = threadIdx.x & (CH - 1);
+    const int step = blockDim.x / CH;
     const bool eok = i0 + e < ilim;
-    for (; cell < total; cell += UNR * step) {
-        cf32 v[UNR];
-        int dst[UNR];
-        int rr = r, cc = c;
+    for (int x = x_lo + (int)(threadIdx.x / CH); x <= x_hi; x += U * step) {
+        cf32 v[TPY * U], w[TPY * U];
+        const cf32* col = src + (int64_t)x * ld + i0 + e;
 #pragma unroll
-        for (int u = 0; u < UNR; ++u) {
-            v[u] = cf32{0.f, 0.f};
-            const int gy = ybase + rr, gx = xbase + cc;
-            dst[u] = ((gy & slot_mask) * pitch + cc) * cs + e;
-            if (cell + u * step < total && eok && gy >= 0 && gy < ny && gx >= 0 && gx < nx)
-                v[u] = src[((int64_t)gy * nx + gx) * ld + i0 + e];
-            cc += step;
-            while (cc >= hc) { cc -= hc; ++rr; }
+        for (int r = 0; r < TPY; ++r) {
+            const int ya = y0 + r - ay, yb = y0 + r + ay;
+            const bool oka = ya >= 0 && ya < ny, okb = ay > 0 && yb < ny;
+#pragma unroll
+            for (int t = 0; t < U; ++t) {
+                v[r * U + t] = w[r * U + t] = cf32{0.f, 0.f};
+                const bool in = eok && x + t * step <= x_hi;
+                const cf32* q = col + (int64_t)t * step * ld;
+                if (oka && in) v[r * U + t] = q[(int64_t)ya * nx * ld];
+                if (okb && in) w[r * U + t] = q[(int64_t)yb * nx * ld];
+            }
         }
+        cf32* dst = halo + (x - xb) * cs + e;
 #pragma unroll
-        for (int u = 0; u < UNR; ++u)
-            if (cell + u * step < total) halo[dst[u]] = v[u];
-        r = rr;
-        c = cc;
+        for (int r = 0; r < TPY; ++r)
+#pragma unroll
+            for (int t = 0; t < U; ++t)
+                if (x + t * step <= x_hi)
+                    dst[r * pitch + t * step * cs] = cf32{v[r * U + t].re + w[r * U + t].re, v[r * U + t].im + w[r * U + t].im};
     }
+}
+
+// The CH / 4 values of one lane group (kq = lane / 16): cell entries
+// kq CH / 4 .. + CH / 4 - 1, consecutive so that they are 16-byte LDS reads.
+template <int CH>
+__device__ __forceinline__ void lane_values(const cf32* __restrict__ p, cf32 (&v)[CH / 4]) {
+    if constexpr (CH >= 8) {
+#pragma unroll
+        for (int h = 0; h < CH / 8; ++h) {
+            const f4 q = *reinterpret_cast<const f4*>(p + 2 * h);
+            v[2 * h] = cf32{q.x, q.y};
+            v[2 * h + 1] = cf32{q.z, q.w};
+        }
+    } else {
+        v[0] = p[0];
+    }
+}
+
+// Last a_x at which a sub-tile of SW columns from c0 on sees the grid (-1:
+// the sub-tile itself lies outside).
+__host__ __device__ static inline int last_ax(int c0, int sw, int nx) {
+    return c0 >= nx ? -1 : max(min(c0 + sw, nx) - 1, nx - 1 - c0);
+}
+
+// a_y values at which the rows y0 .. y0 + tpy - 1 see the grid.
+__host__ __device__ static inline int tile_nay(int y0, int tpy, int ny, int wy) {
+    return min(wy, last_ax(y0, tpy, ny)) + 1;
+}
+
+// Sub-tile offsets a_x of a tile's row of np sub-tiles from x0 on.
+__host__ __device__ static inline int tile_nax(int x0, int np, int sw, int nx, int wx) {
+    int n = 0;
+    for (int s = 0; s < np; ++s) n += min(wx, last_ax(x0 + s * sw, sw, nx)) + 1;
+    return n;
+}
+
+// What a tile and its part of the reduction run over.
+struct TileRange {
+    int t0, t1;          // steps (chunk of the reduction axis, a_y), a_y fastest
+    int nay;             // a_y values of the tile
+    int ax_lo, ax_hi;    // a_x range
+};
+
+// Tile of np sub-tiles (sw x tpy) at (x0, y0); part `sp` of `split` and `spz`
+// of `zsplit`; nch chunks of the reduction axis, a step of the last one costing
+// `last` where a step of the others costs `full`.  On a C-scan a tile whose work
+// is w of the heaviest tile's `top` uses ceil(parts w / top) of the parts, spread
+// evenly, and leaves the others empty, so every workgroup with work has about
+// the same (on a full aperture a corner tile has 2.5 times a central one's
+// offsets).
+__device__ __forceinline__ TileRange tile_range(int x0, int y0, int np, int sw, int tpy, int nx, int ny, int wx, int wy,
+                                                int nch, int full, int last, int sp, int split, int spz, int zsplit,
+                                                int top) {
+    TileRange R;
+    R.nay = tile_nay(y0, tpy, ny, wy);
+    const int nax = min(wx, last_ax(x0, np * sw, nx)) + 1;
+    R.ax_lo = 0;
+    R.ax_hi = nax - 1;
+    if (ny == 1) {
+        R.t0 = spz * nch / zsplit;
+        R.t1 = (spz + 1) * nch / zsplit;
+        R.ax_lo = sp * nax / split;
+        R.ax_hi = (sp + 1) * nax / split - 1;
+    } else {
+        const int part = sp + split * spz;
+        const int64_t w = (int64_t)R.nay * tile_nax(x0, np, sw, nx, wx);
+        const int slots = split * zsplit;
+        const int parts = (int)((slots * w + top - 1) / top);
+        const int64_t head = (int64_t)(nch - 1) * R.nay * full, cost = head + (int64_t)R.nay * last;
+        auto step_at = [&](int64_t c) {                            // first step not before cost c
+            return (int)(c <= head ? (c + full - 1) / full : head / full + (c - head + last - 1) / last);
+        };
+        const int q = (int)((int64_t)part * parts / slots);        // the slot's part, if it has one
+        const bool has = (int)((int64_t)(part + 1) * parts / slots) > q;
+        R.t0 = has ? step_at(q * cost / parts) : 0;
+        R.t1 = has ? step_at((q + 1) * cost / parts) : 0;
+    }
+    return R;
+}
+
+// Block b of `groups` x `parts` -> (group, part).  Blocks are dealt round-robin
+// to the 8 XCDs; where that comes out even, XCD k takes the k-th eighth of the
+// parts of every group: neighbouring parts and neighbouring tiles read the same
+// rows, which then stay in that XCD's L2.
+__device__ __forceinline__ void deal(int b, int groups, int parts, int& group, int& part) {
+    const int per_xcd = groups * parts / 8;
+    if (per_xcd * 8 == groups * parts) b = (b & 7) * per_xcd + (b >> 3);
+    part = b / groups;
+    group = b - part * groups;
 }
 
 struct FwdArgs {
     const cf32* x;
-    cf32* yraw;            // [split][npos][mu]
+    cf32* yraw;            // [split * zsplit][npos][mu]
     const uint32_t* u;     // [wy+1][wx+1][nz]
     const float* amp;      // beam amplitude, same layout (DIR kernels only)
     const int* kb;         // [mu]
@@ -98,72 +223,69 @@ struct FwdArgs {
     int nw;                // waves with a bin sub-tile (<= blockDim / 64)
     int ft;                // bins past the last full tile (1..4) folded into it, else 0
     int zc;                // depth chunk (multiple of 4)
-    int split;             // split of the d_y range
-    int zsplit;            // split of the depth range (partials = split * zsplit)
+    int split;             // parts, see tile_range
+    int zsplit;
+    int top;               // the heaviest tile's work
     int64_t npos;
     int nblk;              // blocks of this plan's grid
 };
 
 // ZC: the depth chunk a.zc as a compile-time constant (16, 8 or 4).
-// DIR: scale each phasor by the beam amplitude g(|d_x|, |d_y|, z) (staged in
-// LDS beside the delay table).
+// DIR: scale each phasor by the beam amplitude g(a, z) (staged in LDS beside
+// the delay table).
 // FOLD: the plan folds a.ft tail bins into its last bin tile (below).
-template <int NP, int ZC, bool DIR = false, bool FOLD = false>
-__device__ __forceinline__ void fwd_f32_body(const FwdArgs& a, int b, const int nblk, unsigned char* smem) {
-    constexpr int zc = ZC;
+template <int NP, int ZC, int SW, bool DIR = false, bool FOLD = false>
+__device__ __forceinline__ void fwd_f32_body(const FwdArgs& a, const int b, unsigned char* smem) {
+    constexpr int NJ = ZC / 4, cs = cell_stride(ZC);
+    constexpr int tpx = SW * NP, tpy = 16 / SW;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int sw = a.sw, sh = 16 / sw;
-    const int tpx = sw * NP, tpy = sh;
     const int hc = tpx + 2 * a.wx;            // halo columns
-    const int cs = zc + 1;                  // padded cell stride (complex)
+    const int pitch = row_pitch(hc, ZC);
+    const int zrun = zero_run(NP, SW, ZC);
     cf32* halo = reinterpret_cast<cf32*>(smem);
-    uint32_t* ulds = reinterpret_cast<uint32_t*>(halo + (size_t)tpy * hc * cs);
-    float* glds = reinterpret_cast<float*>(ulds + (size_t)(a.wx + 1) * zc);
+    uint32_t* ulds = reinterpret_cast<uint32_t*>(halo + (size_t)tpy * pitch + zrun);
+    float* glds = reinterpret_cast<float*>(ulds + (size_t)(a.wx + 1) * ZC);
 
-    // block -> (split, bin tile, lateral tile); consecutive tiles of one split
-    // and bin tile stay on one XCD (blocks are dealt round-robin to 8 XCDs).
-    int per_xcd = nblk / 8;
-    if (per_xcd * 8 == nblk) b = (b % 8) * per_xcd + b / 8;
+    // block -> (part, bin tile, lateral tile)
     const int ntile = a.ntx * a.nty;
-    const int tile = b % ntile;
-    const int bt = (b / ntile) % a.nbt;
-    const int sp_all = b / (ntile * a.nbt);          // partial index: (d_y part, depth part)
-    const int sp = sp_all % a.split, spz = sp_all / a.split;
+    int tile, sp_all;                                // sp_all: partial slot
+    deal(b, ntile * a.nbt, a.split * a.zsplit, tile, sp_all);
+    const int bt = tile / ntile;
+    tile -= bt * ntile;
     const int px0 = (tile % a.ntx) * tpx, py0 = (tile / a.ntx) * tpy;
-    const int zper = ((a.nz + zc * a.zsplit - 1) / (zc * a.zsplit)) * zc;
-    const int z_lo = spz * zper, z_hi = min(a.nz, z_lo + zper);
+    const TileRange R = tile_range(px0, py0, NP, SW, tpy, a.nx, a.ny, a.wx, a.wy, (a.nz + ZC - 1) / ZC, 1, 1,
+                                   sp_all % a.split, a.split, sp_all / a.split, a.zsplit, a.top);
+    const int x_lo = max(0, px0 - a.wx), x_hi = min(a.nx - 1, px0 + tpx - 1 + a.wx);
+    int axl[NP];
+#pragma unroll
+    for (int s = 0; s < NP; ++s) axl[s] = last_ax(px0 + s * SW, SW, a.nx);
 
-    // d_y range of this split (rows that hit the grid for some tile row)
-    int dy_lo = max(-a.wy, py0 - (a.ny - 1));
-    int dy_hi = min(a.wy, py0 + tpy - 1);
-    const int ndy = dy_hi - dy_lo + 1;
-    const int chunk = (ndy + a.split - 1) / a.split;
-    dy_lo += sp * chunk;
-    dy_hi = min(dy_hi, dy_lo + chunk - 1);
-    const int dx_lo = max(-a.wx, px0 - (a.nx - 1));
-    const int dx_hi = min(a.wx, px0 + tpx - 1);
+    for (int t = threadIdx.x; t < tpy * pitch + zrun; t += blockDim.x) halo[t] = cf32{0.f, 0.f};
 
     const int bin0 = bt * 16 * a.nw + wave * 16;               // this wave's first bin
     const bool wave_active = wave < a.nw && bin0 < a.mu;
-    const int i = lane & 15, ix = i % sw, iy = i / sw;
-    const int kq = lane >> 4;
+    const int i = lane & 15, ix = i % SW, iy = i / SW;
+    const int kq = lane >> 4;                                  // depths NJ kq .. NJ kq + NJ - 1 of a chunk
     // A wave left with at most 4 bins (the short last one of a union such as
     // 66 = 4 x 16 + 2) runs v_mfma_f32_4x4x1_16b_f32 instead: 16 blocks of a
     // 4 x 4 product with one depth each, the same rate per flop, a quarter of
     // the 16 x 16 x 4 cycles.  Its A operand is the same (lane l: position
-    // l % 16, depth l / 16), its B operand takes bin l % 4 (block l / 4 =
-    // (position group, depth)), and the four depth blocks of a position group
-    // are summed across lanes at the end.
+    // l % 16, depth group l / 16), its B operand takes bin l % 4 (block l / 4 =
+    // (position group, depth group)), and the four depth blocks of a position
+    // group are summed across lanes at the end.
     const bool tail = wave_active && a.mu - bin0 <= 4;
     // Folded tail (four waves, a.ft bins past the last full bin tile, e.g. the
     // 2 of 66 = 64 + 2): the last tile's waves share those bins' products on the
-    // same 4 x 4 x 1 form, wave w at the offsets d_x = w (mod 4), reusing the
+    // same 4 x 4 x 1 form, wave w at the offsets a_x = w (mod 4), reusing the
     // A operands of their own products; the four partial sums meet in LDS at
     // the end.  Every wave keeps the same work per offset range, where a fifth
     // wave for the tail shares a SIMD with another wave.
     const bool fold = FOLD && bt == a.nbt - 1;
     const int tb = FOLD ? a.nbt * 16 * a.nw + (lane & 3) : 0;   // this lane's folded bin
+    // this lane's cells at a_x = 0 and the zero cells that stand in there
+    const cf32* cell0 = halo + iy * pitch + (ix + a.wx) * cs + NJ * kq;
+    const cf32* zcell = halo + tpy * pitch;
     auto run = [&](auto tailc) {
         constexpr bool TAIL = decltype(tailc)::value;
         const int mb = bin0 + (TAIL ? (lane & 3) : (lane & 15));   // this lane's bin column
@@ -181,102 +303,98 @@ __device__ __forceinline__ void fwd_f32_body(const FwdArgs& a, int b, const int 
 #pragma unroll
         for (int s = 0; s < (FOLD ? NP : 1); ++s) t_re[s] = t_im[s] = f4{0.f, 0.f, 0.f, 0.f};
 
-        for (int z0 = z_lo; z0 < z_hi; z0 += zc) {
-            for (int dy = dy_lo; dy <= dy_hi; ++dy) {
-                __syncthreads();
-                // stage x rows (py0 + r - dy), columns (px0 - wx + c), depths z0..z0+zc
-                // rows live in slot (grid row mod tpy): after the first d_y only the row
-                // entering the window is loaded
-                stage_halo<8>(halo, cs, dy == dy_lo ? tpy : 1, hc, hc, tpy - 1, zc, a.x, a.ny, a.nx, a.nz,
-                              py0 - dy, px0 - a.wx, z0, a.nz);
-                const int ady = dy < 0 ? -dy : dy;
-                for (int t = threadIdx.x; t < (a.wx + 1) * zc; t += blockDim.x) {
-                    int adx = t / zc, zz = t - adx * zc;
-                    int z = z0 + zz;
-                    const int64_t o = ((int64_t)ady * (a.wx + 1) + adx) * a.nz + z;
-                    ulds[t] = z < a.nz ? a.u[o] : 0u;
-                    if (DIR) glds[t] = z < a.nz ? a.amp[o] : 0.f;
+        for (int t = R.t0; t < R.t1; ++t) {
+            const int zi = t / R.nay, ay = t - zi * R.nay, z0 = zi * ZC;
+            __syncthreads();
+            stage_mirrored<ZC, tpy>(halo, pitch, a.x, a.ny, a.nx, a.nz, py0, ay, px0 - a.wx, x_lo, x_hi, z0, a.nz);
+            for (int q = threadIdx.x; q < (a.wx + 1) * ZC; q += blockDim.x) {
+                const int ax = q / ZC, z = z0 + (q & (ZC - 1));
+                const int64_t o = ((int64_t)ay * (a.wx + 1) + ax) * a.nz + z;
+                ulds[q] = z < a.nz ? a.u[o] : 0u;
+                if (DIR) glds[q] = z < a.nz ? a.amp[o] : 0.f;
+            }
+            __syncthreads();
+            if (!wave_active) continue;
+            // Gauss's three-product form of (xr + j xi)(c - j s):
+            //   m1 = c (xr + xi), m2 = xr (-s - c), m3 = xi (c - s);
+            //   Re = m1 - m3 = xr c + xi s,  Im = m1 + m2 = xi c - xr s
+            f4 m1[NP], m2[NP], m3[NP];
+#pragma unroll
+            for (int s = 0; s < NP; ++s) m1[s] = m2[s] = m3[s] = f4{0.f, 0.f, 0.f, 0.f};
+            for (int ax = R.ax_lo; ax <= R.ax_hi; ++ax) {
+                const uint32_t* urow = ulds + ax * ZC;
+                const cf32* lrow = cell0 - ax * cs;
+                const cf32* rrow = ax > 0 ? cell0 + ax * cs : zcell;
+                float cz[NJ], bmz[NJ], bpz[NJ];
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) {
+                    float c, sn;
+                    phasor(kbin * urow[NJ * kq + j], c, sn);
+                    if (DIR) {
+                        const float gv = glds[ax * ZC + NJ * kq + j];
+                        c *= gv;
+                        sn *= gv;
+                    }
+                    cz[j] = c;
+                    bmz[j] = -sn - c;
+                    bpz[j] = c - sn;
                 }
-                __syncthreads();
-                if (!wave_active) continue;
-                // Gauss's three-product form of (xr + j xi)(c - j s):
-                //   m1 = c (xr + xi), m2 = xr (-s - c), m3 = xi (c - s);
-                //   Re = m1 - m3 = xr c + xi s,  Im = m1 + m2 = xi c - xr s
-                f4 m1[NP], m2[NP], m3[NP];
-#pragma unroll
-                for (int s = 0; s < NP; ++s) m1[s] = m2[s] = m3[s] = f4{0.f, 0.f, 0.f, 0.f};
-                for (int dx = dx_lo; dx <= dx_hi; ++dx) {
-                    const int adx = dx < 0 ? -dx : dx;
-                    const uint32_t* urow = ulds + adx * zc;
-                    const cf32* hrow = halo + ((((py0 + iy - dy) & (tpy - 1)) * hc) + ix + a.wx - dx) * cs;
-                    // sub-tiles whose shifted columns all fall outside the grid add
-                    // exact zeros: skip their MFMAs (wave-uniform test)
-                    bool act[NP];
-#pragma unroll
-                    for (int s = 0; s < NP; ++s) {
-                        const int c0 = px0 + s * sw - dx;
-                        act[s] = c0 + sw - 1 >= 0 && c0 <= a.nx - 1;
-                    }
-                    float cz[zc / 4], bmz[zc / 4], bpz[zc / 4];
-#pragma unroll
-                    for (int j = 0; j < zc / 4; ++j) {
-                        float c, sn;
-                        phasor(kbin * urow[4 * j + kq], c, sn);
-                        if (DIR) {
-                            const float gv = glds[adx * zc + 4 * j + kq];
-                            c *= gv;
-                            sn *= gv;
-                        }
-                        cz[j] = c;
-                        bmz[j] = -sn - c;
-                        bpz[j] = c - sn;
+// this wave's offsets for the folded bins, and their phasors: the
+                // wave's 4 bins x ZC depths are one phasor per lane (bin l % 4,
+                // depth l / 4), handed to the lanes that take them
+                const bool folds = FOLD && !TAIL && fold && (ax & 3) == wave;
+                float cj[NJ], sj[NJ];
+                if (folds) {
+                    const int dz = min(lane >> 2, ZC - 1);
+                    float c0, s0;
+                    phasor(kbt * urow[dz], c0, s0);
+                    if (DIR) {
+                        const float gv = glds[ax * ZC + dz];
+                        c0 *= gv;
+                        s0 *= gv;
                     }
 #pragma unroll
-                    for (int s = 0; s < NP; ++s) {
-                        if (!act[s]) continue;
-#pragma unroll
-                        for (int j = 0; j < zc / 4; ++j) {
-                            cf32 xv = hrow[s * sw * cs + 4 * j + kq];
-                            m1[s] = mfma(xv.re + xv.im, cz[j], m1[s]);
-                            m2[s] = mfma(xv.re, bmz[j], m2[s]);
-                            m3[s] = mfma(xv.im, bpz[j], m3[s]);
-                        }
-                    }
-                    if constexpr (FOLD && !TAIL) {
-                        if (fold && (dx & 3) == wave) {
-                            // (xr + j xi)(c - j s) for the folded bins, four real products;
-                            // the wave's 4 bins x zc depths are one phasor per lane (bin
-                            // l % 4, depth l / 4), handed to the lanes that take them
-                            const int dz = min(lane >> 2, zc - 1);
-                            float c0, s0;
-                            phasor(kbt * urow[dz], c0, s0);
-                            if (DIR) {
-                                const float gv = glds[adx * zc + dz];
-                                c0 *= gv;
-                                s0 *= gv;
-                            }
-#pragma unroll
-                            for (int j = 0; j < zc / 4; ++j) {
-                                const int src = 4 * (4 * j + kq) + (lane & 3);
-                                const float c = __shfl(c0, src, 64), sn = __shfl(s0, src, 64);
-#pragma unroll
-                                for (int s = 0; s < NP; ++s) {
-                                    if (!act[s]) continue;
-                                    const cf32 xv = hrow[s * sw * cs + 4 * j + kq];
-                                    t_re[s] = __builtin_amdgcn_mfma_f32_4x4x1f32(xv.re, c, t_re[s], 0, 0, 0);
-                                    t_re[s] = __builtin_amdgcn_mfma_f32_4x4x1f32(xv.im, sn, t_re[s], 0, 0, 0);
-                                    t_im[s] = __builtin_amdgcn_mfma_f32_4x4x1f32(xv.im, c, t_im[s], 0, 0, 0);
-                                    t_im[s] = __builtin_amdgcn_mfma_f32_4x4x1f32(xv.re, -sn, t_im[s], 0, 0, 0);
-                                }
-                            }
-                        }
+                    for (int j = 0; j < NJ; ++j) {
+                        const int src = 4 * (NJ * kq + j) + (lane & 3);
+                        cj[j] = __shfl(c0, src, 64);
+                        sj[j] = __shfl(s0, src, 64);
                     }
                 }
 #pragma unroll
                 for (int s = 0; s < NP; ++s) {
-                    out_re[s] += m1[s] - m3[s];
-                    out_im[s] += m1[s] + m2[s];
+                    // past the last a_x at which a sub-tile sees the grid its
+                    // operands are zero: no products (wave-uniform test)
+                    if (ax > axl[s]) continue;
+                    cf32 l[NJ], r[NJ];
+                    lane_values<ZC>(lrow + s * SW * cs, l);
+                    lane_values<ZC>(rrow + s * SW * cs, r);
+                    float xr[NJ], xi[NJ];
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j) {
+                        xr[j] = l[j].re + r[j].re;
+                        xi[j] = l[j].im + r[j].im;
+                        m1[s] = mfma(xr[j] + xi[j], cz[j], m1[s]);
+                        m2[s] = mfma(xr[j], bmz[j], m2[s]);
+                        m3[s] = mfma(xi[j], bpz[j], m3[s]);
+                    }
+                    if constexpr (FOLD && !TAIL) {
+                        if (folds) {
+                            // (xr + j xi)(c - j s) for the folded bins, four real products
+#pragma unroll
+                            for (int j = 0; j < NJ; ++j) {
+                                t_re[s] = __builtin_amdgcn_mfma_f32_4x4x1f32(xr[j], cj[j], t_re[s], 0, 0, 0);
+                                t_im[s] = __builtin_amdgcn_mfma_f32_4x4x1f32(xi[j], cj[j], t_im[s], 0, 0, 0);
+                                t_re[s] = __builtin_amdgcn_mfma_f32_4x4x1f32(xi[j], sj[j], t_re[s], 0, 0, 0);
+                                t_im[s] = __builtin_amdgcn_mfma_f32_4x4x1f32(xr[j], -sj[j], t_im[s], 0, 0, 0);
+                            }
+                        }
+                    }
                 }
+            }
+#pragma unroll
+            for (int s = 0; s < NP; ++s) {
+                out_re[s] += m1[s] - m3[s];
+                out_im[s] += m1[s] + m2[s];
             }
         }
         if constexpr (FOLD && !TAIL) {
@@ -312,7 +430,7 @@ __device__ __forceinline__ void fwd_f32_body(const FwdArgs& a, int b, const int 
                             vr += __shfl_xor(vr, 32, 64);
                             vi += __shfl_xor(vi, 32, 64);
                             const int irow = 4 * (lane >> 2) + r;
-                            const int px = px0 + s * sw + irow % sw, py = py0 + irow / sw;
+                            const int px = px0 + s * SW + irow % SW, py = py0 + irow / SW;
                             if (lane < 16 && tb < a.mu && px < a.nx && py < a.ny)
                                 yo[((int64_t)py * a.nx + px) * a.mu + tb] = cf32{vr, vi};
                         }
@@ -323,8 +441,8 @@ __device__ __forceinline__ void fwd_f32_body(const FwdArgs& a, int b, const int 
         cf32* yo = a.yraw + (int64_t)sp_all * a.npos * a.mu;
         if constexpr (TAIL) {
             // lane l holds rows r = 0..3 (positions 4 (l / 4 % 4) + r) of column
-            // l % 4 of block l / 4; the blocks of depths 0..3 (lanes l, l ^ 16,
-            // l ^ 32, l ^ 48) are summed in a fixed order
+            // l % 4 of block l / 4; the blocks of the four depth groups (lanes l,
+            // l ^ 16, l ^ 32, l ^ 48) are summed in a fixed order
 #pragma unroll
             for (int s = 0; s < NP; ++s)
 #pragma unroll
@@ -340,7 +458,7 @@ __device__ __forceinline__ void fwd_f32_body(const FwdArgs& a, int b, const int 
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int irow = 4 * (lane >> 2) + r;
-                    const int px = px0 + s * sw + irow % sw, py = py0 + irow / sw;
+                    const int px = px0 + s * SW + irow % SW, py = py0 + irow / SW;
                     if (px < a.nx && py < a.ny)
                         yo[((int64_t)py * a.nx + px) * a.mu + mb] = cf32{out_re[s][r], out_im[s][r]};
                 }
@@ -352,7 +470,7 @@ __device__ __forceinline__ void fwd_f32_body(const FwdArgs& a, int b, const int 
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     int irow = 4 * kq + r;
-                    int px = px0 + s * sw + irow % sw, py = py0 + irow / sw;
+                    int px = px0 + s * SW + irow % SW, py = py0 + irow / SW;
                     if (px < a.nx && py < a.ny)
                         yo[((int64_t)py * a.nx + px) * a.mu + mb] = cf32{out_re[s][r], out_im[s][r]};
                 }
@@ -363,10 +481,14 @@ __device__ __forceinline__ void fwd_f32_body(const FwdArgs& a, int b, const int 
     else run(std::false_type{});
 }
 
-template <int NP, int ZC, bool DIR = false, bool FOLD = false>
-__global__ __launch_bounds__(512) void fwd_gemm_f32_kernel(FwdArgs a) {
+// Registers for at least 3 (4 sub-tiles per wave) or 4 waves per SIMD: two
+// workgroups of a CU already keep its issue slots full, the third covers their
+// staging rounds.
+template <int NP, int ZC, int SW, bool DIR = false, bool FOLD = false>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NP == 4 ? 3 : 4)))
+void fwd_gemm_f32_kernel(FwdArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
-    fwd_f32_body<NP, ZC, DIR, FOLD>(a, blockIdx.x, gridDim.x, smem);
+    fwd_f32_body<NP, ZC, SW, DIR, FOLD>(a, blockIdx.x, smem);
 }
 
 // Grouped launch: block -> (plan index, block index inside that plan's grid).
@@ -376,10 +498,23 @@ __global__ __launch_bounds__(512) void fwd_gemm_f32_kernel_grouped(const FwdArgs
     extern __shared__ __align__(16) unsigned char smem[];
     const int2 sb = blk[blockIdx.x];
     const FwdArgs a = descs[sb.x];
-    // scans of one batch may differ in depth chunk
-    if (a.zc == 16) fwd_f32_body<NP, 16>(a, sb.y, a.nblk, smem);
-    else if (a.zc == 8) fwd_f32_body<NP, 8>(a, sb.y, a.nblk, smem);
-    else fwd_f32_body<NP, 4>(a, sb.y, a.nblk, smem);
+    // scans of one batch may differ in depth chunk and in sub-tile shape
+    if (a.sw == 4) {
+        if (a.zc == 16) fwd_f32_body<NP, 16, 4>(a, sb.y, smem);
+        else if (a.zc == 8) fwd_f32_body<NP, 8, 4>(a, sb.y, smem);
+        else fwd_f32_body<NP, 4, 4>(a, sb.y, smem);
+    } else {
+        if (a.zc == 16) fwd_f32_body<NP, 16, 16>(a, sb.y, smem);
+        else if (a.zc == 8) fwd_f32_body<NP, 8, 16>(a, sb.y, smem);
+        else fwd_f32_body<NP, 4, 16>(a, sb.y, smem);
+    }
+}
+
+// Product steps per offset of the last bin chunk (of kc bins; a last chunk of at
+// most 2 bins takes two offsets per product, half a step each).
+__device__ __forceinline__ int last_chunk_cost(int mu, int kc) {
+    const int left = mu - (mu - 1) / kc * kc;
+    return (left + 3) / 4;
 }
 
 struct AdjArgs {
@@ -389,10 +524,10 @@ struct AdjArgs {
     const float* amp;      // beam amplitude, same layout as u (DIR kernels only)
     const int* kb;
     int nx, ny, nz, wx, wy, mu;
-    int sw, ntx, nty, nzt; // lateral tiles, depth tiles (of 64 * NZ)
+    int sw, ntx, nty, nzt; // lateral tiles, depth tiles (of 16 * waves)
     int kc;                // bin chunk (multiple of 4)
-    int kcons;             // 1: the union's bins are consecutive integers (phasor rotation)
-    int split;             // split of the d_y range; split > 1 writes partials
+    int split;             // parts, see tile_range; split > 1 writes partials
+    int top;               // the heaviest tile's work
     cf32* part;            // [split][ny][nx][nz] when split > 1
     int64_t nvox;
     int nblk;              // blocks of this plan's grid
@@ -400,219 +535,191 @@ struct AdjArgs {
 
 // KC: the bin chunk a.kc as a compile-time constant (16, 8 or 4).
 // DIR: scale each phasor by the beam amplitude (staged in LDS after the bins).
-// NW: waves per workgroup, each on its own 16 x NZ depths; the staged halo
+// NW: waves per workgroup, each on its own 16 depths; the staged halo
 // (positions x bins) is the same for every depth, so 8 waves share one halo
 // over 128 depths where 4 waves cover 64.
-template <int NP, int NZ, int KC, bool DIR = false, int NW = 4>
-__device__ __forceinline__ void adj_f32_body(const AdjArgs& a, int b, const int nblk, unsigned char* smem) {
-    constexpr int kc = KC;
+template <int NP, int KC, int SW, bool DIR = false, int NW = 4>
+__device__ __forceinline__ void adj_f32_body(const AdjArgs& a, const int b, unsigned char* smem) {
+    constexpr int NJ = KC / 4, cs = cell_stride(KC);
+    constexpr int tpx = SW * NP, tpy = 16 / SW;
+    constexpr int zspan = 16 * NW;                   // depths per workgroup
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int sw = a.sw, sh = 16 / sw;
-    const int tpx = sw * NP, tpy = sh;
     const int hc = tpx + 2 * a.wx;
-    const int cs = kc + 1;
-    const int zspan = 16 * NW * NZ;                  // depths per workgroup
+    const int pitch = row_pitch(hc, KC);
+    const int zrun = zero_run(NP, SW, KC);
     cf32* halo = reinterpret_cast<cf32*>(smem);
-    uint32_t* ulds = reinterpret_cast<uint32_t*>(halo + (size_t)tpy * hc * cs);
+    uint32_t* ulds = reinterpret_cast<uint32_t*>(halo + (size_t)tpy * pitch + zrun);
     int* klds = reinterpret_cast<int*>(ulds + (size_t)(a.wx + 1) * zspan);
-    float* glds = reinterpret_cast<float*>(klds + kc);
+    float* glds = reinterpret_cast<float*>(klds + KC);
 
-    int per_xcd = nblk / 8;
-    if (per_xcd * 8 == nblk) b = (b % 8) * per_xcd + b / 8;
     const int ntile = a.ntx * a.nty;
-    const int tile = b % ntile;
-    const int zt = (b / ntile) % a.nzt;
-    const int sp = b / (ntile * a.nzt);
+    int tile, sp;
+    deal(b, ntile * a.nzt, a.split, tile, sp);
+    const int zt = tile / ntile;
+    tile -= zt * ntile;
     const int vx0 = (tile % a.ntx) * tpx, vy0 = (tile / a.ntx) * tpy;
     const int zw0 = zt * zspan;                      // first depth of the workgroup
+    const TileRange R = tile_range(vx0, vy0, NP, SW, tpy, a.nx, a.ny, a.wx, a.wy, (a.mu + KC - 1) / KC, NJ,
+                                   last_chunk_cost(a.mu, KC), sp, a.split, 0, 1, a.top);
+    const int x_lo = max(0, vx0 - a.wx), x_hi = min(a.nx - 1, vx0 + tpx - 1 + a.wx);
+    int axl[NP];
+#pragma unroll
+    for (int s = 0; s < NP; ++s) axl[s] = last_ax(vx0 + s * SW, SW, a.nx);
 
-    // d with v + d inside the grid for some voxel of the tile, split in chunks
-    int dy_lo = max(-a.wy, -(vy0 + tpy - 1));
-    int dy_hi = min(a.wy, a.ny - 1 - vy0);
-    const int chunk = (dy_hi - dy_lo + 1 + a.split - 1) / a.split;
-    dy_lo += sp * chunk;
-    dy_hi = min(dy_hi, dy_lo + chunk - 1);
-    const int dx_lo = max(-a.wx, -(vx0 + tpx - 1)), dx_hi = min(a.wx, a.nx - 1 - vx0);
+    for (int t = threadIdx.x; t < tpy * pitch + zrun; t += 64 * NW) halo[t] = cf32{0.f, 0.f};
 
-    const int i = lane & 15, ix = i % sw, iy = i / sw;
+    const int i = lane & 15, ix = i % SW, iy = i / SW;
     const int kq = lane >> 4;
-    const bool wave_active = zw0 + wave * NZ * 16 < a.nz;
+    const bool wave_active = zw0 + wave * 16 < a.nz;
+    const cf32* cell0 = halo + iy * pitch + (ix + a.wx) * cs;
+    const cf32* zcell = halo + tpy * pitch;
+    const uint32_t* ucol = ulds + wave * 16 + i;
+    const float* gcol = glds + wave * 16 + i;
 
-    f4 out_re[NP][NZ], out_im[NP][NZ];
+    f4 out_re[NP], out_im[NP];
 #pragma unroll
-    for (int s = 0; s < NP; ++s)
-#pragma unroll
-        for (int q = 0; q < NZ; ++q) out_re[s][q] = out_im[s][q] = f4{0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < NP; ++s) out_re[s] = out_im[s] = f4{0.f, 0.f, 0.f, 0.f};
 
-    for (int k0 = 0; k0 < a.mu; k0 += kc) {
-        const int kcur = min(kc, (a.mu - k0 + 3) & ~3);   // last chunk: valid bins, rounded to 4
-        const bool pair = a.mu - k0 <= 2;                 // at most 2 bins left: two offsets per product
-        for (int dy = dy_lo; dy <= dy_hi; ++dy) {
-            __syncthreads();
-            stage_halo<8>(halo, cs, dy == dy_lo ? tpy : 1, hc, hc, tpy - 1, kc, a.r, a.ny, a.nx, a.mu,
-                          dy == dy_lo ? vy0 + dy : vy0 + dy + tpy - 1, vx0 - a.wx, k0, a.mu);
-            const int ady = dy < 0 ? -dy : dy;
-            for (int t = threadIdx.x; t < (a.wx + 1) * zspan; t += 64 * NW) {
-                int adx = t / zspan, zz = t - adx * zspan;
-                int z = zw0 + zz;
-                const int64_t o = ((int64_t)ady * (a.wx + 1) + adx) * a.nz + z;
-                ulds[t] = z < a.nz ? a.u[o] : 0u;
-                if (DIR) glds[t] = z < a.nz ? a.amp[o] : 0.f;
-            }
-            for (int t = threadIdx.x; t < kc; t += 64 * NW)
-                klds[t] = (k0 + t < a.mu) ? a.kb[k0 + t] : 0;
-            __syncthreads();
-            if (!wave_active) continue;
-            // Gauss's three-product form of (rr + j ri)(c + j s):
-            //   m1 = c (rr + ri), m2 = rr (s - c), m3 = ri (c + s);
-            //   Re = m1 - m3 = rr c - ri s,  Im = m1 + m2 = rr s + ri c
-            f4 m1[NP][NZ], m2[NP][NZ], m3[NP][NZ];
+    for (int t = R.t0; t < R.t1; ++t) {
+        const int ki = t / R.nay, ay = t - ki * R.nay, k0 = ki * KC;
+        const int left = a.mu - k0;                       // bins of this chunk, if fewer than KC
+        __syncthreads();
+        stage_mirrored<KC, tpy>(halo, pitch, a.r, a.ny, a.nx, a.mu, vy0, ay, vx0 - a.wx, x_lo, x_hi, k0, a.mu);
+        for (int q = threadIdx.x; q < (a.wx + 1) * zspan; q += 64 * NW) {
+            const int ax = q / zspan, z = zw0 + (q & (zspan - 1));
+            const int64_t o = ((int64_t)ay * (a.wx + 1) + ax) * a.nz + z;
+            ulds[q] = z < a.nz ? a.u[o] : 0u;
+            if (DIR) glds[q] = z < a.nz ? a.amp[o] : 0.f;
+        }
+        for (int q = threadIdx.x; q < KC; q += 64 * NW) klds[q] = q < left ? a.kb[k0 + q] : 0;
+        __syncthreads();
+        if (!wave_active) continue;
+        // Gauss's three-product form of (rr + j ri)(c + j s):
+        //   m1 = c (rr + ri), m2 = rr (s - c), m3 = ri (c + s);
+        //   Re = m1 - m3 = rr c - ri s,  Im = m1 + m2 = rr s + ri c
+        f4 m1[NP], m2[NP], m3[NP];
 #pragma unroll
-            for (int s = 0; s < NP; ++s)
-#pragma unroll
-                for (int q = 0; q < NZ; ++q) m1[s][q] = m2[s][q] = m3[s][q] = f4{0.f, 0.f, 0.f, 0.f};
-            // the offsets of [d0, d1] with the sub-tiles of MASK active: with two
-            // sub-tiles the range splits into (second only, both, first only),
-            // and a sub-tile whose shifted columns all leave the grid runs no
-            // MFMAs (compile-time masks keep the products branch-free); FULL: a
-            // whole chunk of kc bins, so the offset step is one basic block whose
-            // LDS reads and products the compiler can interleave (8-wave
-            // workgroups only: with 4 waves the second copy of the offset loops
-            // costs registers and measured 3% slower on the 64 x 64 C-scan and
-            // in grouped launches)
-            auto dxloop = [&](auto maskc, auto fullc, auto consc, const int d0, const int d1) {
-                constexpr int MASK = decltype(maskc)::value;
-                constexpr bool FULL = decltype(fullc)::value;
+        for (int s = 0; s < NP; ++s) m1[s] = m2[s] = m3[s] = f4{0.f, 0.f, 0.f, 0.f};
+        auto products = [&](const int s, const float rr, const float ri, const float c, const float bm, const float bp) {
+            m1[s] = __builtin_amdgcn_mfma_f32_16x16x4f32(rr + ri, c, m1[s], 0, 0, 0);
+            m2[s] = __builtin_amdgcn_mfma_f32_16x16x4f32(rr, bm, m2[s], 0, 0, 0);
+            m3[s] = __builtin_amdgcn_mfma_f32_16x16x4f32(ri, bp, m3[s], 0, 0, 0);
+        };
+        if (left >= KC) {
+            // a whole chunk: lane group kq takes bins NJ kq .. NJ kq + NJ - 1 of it.
+            // CONS: where those are consecutive integers (for every lane), its
+            // phasor steps by exp(-j 2 pi u) from one to the next: one rotation
+            // (4 FMAs) instead of a cos/sin pair, whose issue does not hide under
+            // the products; the chain restarts from cos/sin at every offset
+            auto offsets = [&](auto consc) {
                 constexpr bool CONS = decltype(consc)::value;
-            for (int dx = d0; dx <= d1; ++dx) {
-                const int adx = dx < 0 ? -dx : dx;
-                uint32_t uz[NZ];
-                float gz[NZ];
+                uint32_t kl[NJ];
 #pragma unroll
-                for (int q = 0; q < NZ; ++q) {
-                    uz[q] = ulds[adx * zspan + wave * NZ * 16 + q * 16 + i];
-                    gz[q] = DIR ? glds[adx * zspan + wave * NZ * 16 + q * 16 + i] : 1.f;
-                }
-                const cf32* hrow = halo + ((((vy0 + iy + dy) & (tpy - 1)) * hc) + ix + a.wx + dx) * cs;
-                // CONS (consecutive bins, whole chunk): lane group kq takes bins
-                // k0 + kq + 4 j, so its phasor steps by exp(-j 2 pi 4 u) from one
-                // bin step to the next: one rotation (4 FMAs) instead of a cos/sin
-                // pair, whose issue does not hide under the products; the chain
-                // restarts from cos/sin at every offset (3 rotations at most)
-                float pc[NZ], ps[NZ], rc[NZ], rsn[NZ];
-                if constexpr (CONS) {
-                    const uint32_t k0l = (uint32_t)klds[kq];
-#pragma unroll
-                    for (int q = 0; q < NZ; ++q) {
-                        phasor(k0l * uz[q], pc[q], ps[q]);
-                        phasor(uz[q] << 2, rc[q], rsn[q]);
+                for (int j = 0; j < NJ; ++j) kl[j] = (uint32_t)klds[NJ * kq + j];
+                for (int ax = R.ax_lo; ax <= R.ax_hi; ++ax) {
+                    const uint32_t uz = ucol[ax * zspan];
+                    const float gz = DIR ? gcol[ax * zspan] : 1.f;
+                    const cf32* lrow = cell0 - ax * cs + NJ * kq;
+                    const cf32* rrow = ax > 0 ? cell0 + ax * cs + NJ * kq : zcell;
+                    float pc, ps, rc, rsn;
+                    if constexpr (CONS) {
+                        phasor(kl[0] * uz, pc, ps);
+                        phasor(uz, rc, rsn);
                     }
-                }
+                    float cj[NJ], bm[NJ], bp[NJ];
 #pragma unroll
-                for (int kk = 0; kk < kc; kk += 4) {
-                    if (!FULL && kk >= kcur) break;
-                    const uint32_t k = (uint32_t)klds[kk + kq];
-                    cf32 rv[NP];
-                    float rs[NP];
-#pragma unroll
-                    for (int s = 0; s < NP; ++s) {
-                        rv[s] = hrow[s * sw * cs + kk + kq];
-                        rs[s] = rv[s].re + rv[s].im;
-                    }
-#pragma unroll
-                    for (int q = 0; q < NZ; ++q) {
+                    for (int j = 0; j < NJ; ++j) {
                         float c, sn;
                         if constexpr (CONS) {
-                            c = pc[q];
-                            sn = ps[q];
-                            if (kk + 4 < kc) {
-                                pc[q] = c * rc[q] - sn * rsn[q];
-                                ps[q] = sn * rc[q] + c * rsn[q];
+                            c = pc;
+                            sn = ps;
+                            if (j + 1 < NJ) {
+                                pc = c * rc - sn * rsn;
+                                ps = sn * rc + c * rsn;
                             }
                         } else {
-                            phasor(k * uz[q], c, sn);
+                            phasor(kl[j] * uz, c, sn);
                         }
                         if (DIR) {
-                            c *= gz[q];
-                            sn *= gz[q];
+                            c *= gz;
+                            sn *= gz;
                         }
-                        const float bm = sn - c, bp = c + sn;
-#pragma unroll
-                        for (int s = 0; s < NP; ++s) {
-                            if (!((MASK >> s) & 1)) continue;
-                            m1[s][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(rs[s], c, m1[s][q], 0, 0, 0);
-                            m2[s][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(rv[s].re, bm, m2[s][q], 0, 0, 0);
-                            m3[s][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(rv[s].im, bp, m3[s][q], 0, 0, 0);
-                        }
+                        cj[j] = c;
+                        bm[j] = sn - c;
+                        bp[j] = c + sn;
                     }
-                }
-            }
-            };
-            if (pair) {
-                // a last chunk of at most 2 bins: the K = 4 of one product takes
-                // those bins at two offsets, lane groups kq = 0, 1 at d_x and
-                // kq = 2, 3 at d_x + 1 (zero past dx_hi), so the chunk runs half
-                // the offset steps and no product lane carries a padding bin
-                // (every sub-tile, out-of-grid cells are staged as zeros)
-                const uint32_t k = (uint32_t)klds[kq & 1];
-                for (int dx = dx_lo; dx <= dx_hi; dx += 2) {
-                    const bool ok = dx + (kq >> 1) <= dx_hi;
-                    const int dl = ok ? dx + (kq >> 1) : dx;
-                    const int adl = dl < 0 ? -dl : dl;
-                    const cf32* hrow = halo + ((((vy0 + iy + dy) & (tpy - 1)) * hc) + ix + a.wx + dl) * cs + (kq & 1);
-                    cf32 rv[NP];
-                    float rs[NP];
 #pragma unroll
                     for (int s = 0; s < NP; ++s) {
-                        rv[s] = ok ? hrow[s * sw * cs] : cf32{0.f, 0.f};
-                        rs[s] = rv[s].re + rv[s].im;
-                    }
+                        if (ax > axl[s]) continue;        // operands zero (wave-uniform)
+                        cf32 l[NJ], r[NJ];
+                        lane_values<KC>(lrow + s * SW * cs, l);
+                        lane_values<KC>(rrow + s * SW * cs, r);
 #pragma unroll
-                    for (int q = 0; q < NZ; ++q) {
-                        float c, sn;
-                        phasor(k * ulds[adl * zspan + wave * NZ * 16 + q * 16 + i], c, sn);
-                        if (DIR) {
-                            const float gv = glds[adl * zspan + wave * NZ * 16 + q * 16 + i];
-                            c *= gv;
-                            sn *= gv;
-                        }
-                        const float bm = sn - c, bp = c + sn;
-#pragma unroll
-                        for (int s = 0; s < NP; ++s) {
-                            m1[s][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(rs[s], c, m1[s][q], 0, 0, 0);
-                            m2[s][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(rv[s].re, bm, m2[s][q], 0, 0, 0);
-                            m3[s][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(rv[s].im, bp, m3[s][q], 0, 0, 0);
-                        }
+                        for (int j = 0; j < NJ; ++j)
+                            products(s, l[j].re + r[j].re, l[j].im + r[j].im, cj[j], bm[j], bp[j]);
                     }
                 }
-            } else if constexpr (NP == 2) {
-                // column ranges of the two sub-tiles' shifted voxels inside the grid
-                const int a0 = -(vx0 + sw - 1), b1 = a.nx - 1 - vx0 - sw;
-                auto segs = [&](auto fullc, auto consc) {
-                    dxloop(std::integral_constant<int, 2>{}, fullc, consc, dx_lo, min(min(a0 - 1, b1), dx_hi));
-                    dxloop(std::integral_constant<int, 3>{}, fullc, consc, max(dx_lo, a0), min(b1, dx_hi));
-                    dxloop(std::integral_constant<int, 1>{}, fullc, consc, max(max(a0, b1 + 1), dx_lo), dx_hi);
-                };
-                if constexpr (NW == 8) {
-                    if (kcur == kc) {                         // every chunk but a short last one
-                        if (a.kcons) segs(std::true_type{}, std::true_type{});
-                        else segs(std::true_type{}, std::false_type{});
-                    } else {
-                        segs(std::false_type{}, std::false_type{});
-                    }
-                } else {
-                    segs(std::false_type{}, std::false_type{});
+            };
+            const bool cons = NJ > 1 && __all(klds[NJ * kq + NJ - 1] - klds[NJ * kq] == NJ - 1);
+            if (cons) offsets(std::true_type{});
+            else offsets(std::false_type{});
+        } else if (left <= 2) {
+            // a last chunk of at most 2 bins: the K = 4 of one product takes
+            // those bins at two offsets, lane groups kq = 0, 1 at a_x and
+            // kq = 2, 3 at a_x + 1 (zero past the last), so the chunk runs half
+            // the offset steps and no product lane carries a padding bin
+            const uint32_t k = (uint32_t)klds[kq & 1];
+            for (int ax = R.ax_lo; ax <= R.ax_hi; ax += 2) {
+                const int al = ax + (kq >> 1);
+                const bool ok = al <= R.ax_hi;
+                const int ad = ok ? al : ax;
+                const cf32* lrow = cell0 - ad * cs + (kq & 1);
+                const cf32* rrow = cell0 + ad * cs + (kq & 1);
+                float c, sn;
+                phasor(k * ucol[ad * zspan], c, sn);
+                if (DIR) {
+                    const float gv = gcol[ad * zspan];
+                    c *= gv;
+                    sn *= gv;
                 }
-            } else {
-                dxloop(std::integral_constant<int, (1 << NP) - 1>{}, std::false_type{}, std::false_type{}, dx_lo, dx_hi);
+                const float bm = sn - c, bp = c + sn;
+#pragma unroll
+                for (int s = 0; s < NP; ++s) {
+                    cf32 l = lrow[s * SW * cs], r = rrow[s * SW * cs];
+                    if (!ok) l = cf32{0.f, 0.f};
+                    if (!ok || ad == 0) r = cf32{0.f, 0.f};
+                    products(s, l.re + r.re, l.im + r.im, c, bm, bp);
+                }
             }
+        } else {
+            // a short last chunk: bins 4 j + kq, as many steps as it has fours
+            const int nj = (left + 3) >> 2;
+            for (int ax = R.ax_lo; ax <= R.ax_hi; ++ax) {
+                const uint32_t uz = ucol[ax * zspan];
+                const float gz = DIR ? gcol[ax * zspan] : 1.f;
+                const cf32* lrow = cell0 - ax * cs + kq;
+                const cf32* rrow = ax > 0 ? cell0 + ax * cs + kq : zcell;
+                for (int j = 0; j < nj; ++j) {
+                    float c, sn;
+                    phasor((uint32_t)klds[4 * j + kq] * uz, c, sn);
+                    if (DIR) {
+                        c *= gz;
+                        sn *= gz;
+                    }
+                    const float bm = sn - c, bp = c + sn;
 #pragma unroll
-            for (int s = 0; s < NP; ++s)
-#pragma unroll
-                for (int q = 0; q < NZ; ++q) {
-                    out_re[s][q] += m1[s][q] - m3[s][q];
-                    out_im[s][q] += m1[s][q] + m2[s][q];
+                    for (int s = 0; s < NP; ++s) {
+                        if (ax > axl[s]) continue;
+                        const cf32 l = lrow[s * SW * cs + 4 * j], r = rrow[s * SW * cs + (ax > 0 ? 4 * j : 0)];
+                        products(s, l.re + r.re, l.im + r.im, c, bm, bp);
+                    }
                 }
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < NP; ++s) {
+            out_re[s] += m1[s] - m3[s];
+            out_im[s] += m1[s] + m2[s];
         }
     }
     if (!wave_active) return;
@@ -620,45 +727,38 @@ __device__ __forceinline__ void adj_f32_body(const AdjArgs& a, int b, const int 
 #pragma unroll
     for (int s = 0; s < NP; ++s)
 #pragma unroll
-        for (int q = 0; q < NZ; ++q)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                int irow = 4 * kq + r;
-                int vx = vx0 + s * sw + irow % sw, vy = vy0 + irow / sw;
-                int z = zw0 + wave * NZ * 16 + q * 16 + i;
-                if (vx < a.nx && vy < a.ny && z < a.nz)
-                    dst[((int64_t)vy * a.nx + vx) * a.nz + z] = cf32{out_re[s][q][r], out_im[s][q][r]};
-            }
+        for (int r = 0; r < 4; ++r) {
+            int irow = 4 * kq + r;
+            int vx = vx0 + s * SW + irow % SW, vy = vy0 + irow / SW;
+            int z = zw0 + wave * 16 + i;
+            if (vx < a.nx && vy < a.ny && z < a.nz)
+                dst[((int64_t)vy * a.nx + vx) * a.nz + z] = cf32{out_re[s][r], out_im[s][r]};
+        }
 }
 
-template <int NP, int NZ, int KC, bool DIR = false>
-__global__ __launch_bounds__(256) void adj_gemm_f32_kernel(AdjArgs a) {
+template <int NP, int KC, int SW, bool DIR = false, int NW = 4>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NP == 4 ? 3 : 4)))
+void adj_gemm_f32_kernel(AdjArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
-    adj_f32_body<NP, NZ, KC, DIR>(a, blockIdx.x, gridDim.x, smem);
-}
-
-// Two sub-tiles per wave: registers capped for 6 waves per SIMD, which pays
-// when a small LDS chunk admits that many workgroups per CU (measured on the
-// 32 x 32 and 64 x 64 C-scans).  NW = 8: one halo for 128 depths, so the
-// LDS of 8 waves is the halo plus twice the delay rows instead of twice both
-// (on the 32 x 32 C-scan 3 workgroups per CU: 6 waves per SIMD, not 3).
-template <int NZ, int KC, bool DIR = false, int NW = 4>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(6, 8)))
-void adj_gemm_f32_kernel_np2(AdjArgs a) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    adj_f32_body<2, NZ, KC, DIR, NW>(a, blockIdx.x, gridDim.x, smem);
+    adj_f32_body<NP, KC, SW, DIR, NW>(a, blockIdx.x, smem);
 }
 
 // Grouped launch: block -> (plan index, block index inside that plan's grid).
-template <int NP, int NZ>
+template <int NP>
 __global__ __launch_bounds__(256) void adj_gemm_f32_kernel_grouped(const AdjArgs* __restrict__ descs,
                                                  const int2* __restrict__ blk) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int2 sb = blk[blockIdx.x];
     const AdjArgs a = descs[sb.x];
-    if (a.kc == 16) adj_f32_body<NP, NZ, 16>(a, sb.y, a.nblk, smem);
-    else if (a.kc == 8) adj_f32_body<NP, NZ, 8>(a, sb.y, a.nblk, smem);
-    else adj_f32_body<NP, NZ, 4>(a, sb.y, a.nblk, smem);
+    if (a.sw == 4) {
+        if (a.kc == 16) adj_f32_body<NP, 16, 4>(a, sb.y, smem);
+        else if (a.kc == 8) adj_f32_body<NP, 8, 4>(a, sb.y, smem);
+        else adj_f32_body<NP, 4, 4>(a, sb.y, smem);
+    } else {
+        if (a.kc == 16) adj_f32_body<NP, 16, 16>(a, sb.y, smem);
+        else if (a.kc == 8) adj_f32_body<NP, 8, 16>(a, sb.y, smem);
+        else adj_f32_body<NP, 4, 16>(a, sb.y, smem);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -686,37 +786,69 @@ int adj_chunk(const Plan& P) {
     adj_args(P, nullptr, a, lds, adj_tile_np(P), adj_waves(P));
     return a.kc;
 }
-static constexpr int kAdjNZ = 1;
 static constexpr size_t kLdsMax = 64 * 1024;
 
 static int sub_width(const Plan& P) { return P.g.ny == 1 ? 16 : 4; }
 
-int gemm_split(const Plan& P) {
-    const int sw = sub_width(P), tpx = sw * fwd_tile_np(P), tpy = 16 / sw;
-    const int ntx = (P.g.nx + tpx - 1) / tpx, nty = (P.g.ny + tpy - 1) / tpy;
-    const int mu = (int)P.ubins_h.size();
-    const int nbt = (mu + 63) / 64;
-    const int nw = std::max(1, std::min(P.fwd_nw, (mu + 15) / 16));
-    const int active_waves = ntx * nty * ((mu + 16 * nw - 1) / (16 * nw)) * nw;
-    const int ndy_max = std::min(2 * P.d.wy + 1, P.g.ny + tpy - 1);
-    int split = (2048 + active_waves - 1) / active_waves;
-    split = std::max(1, std::min(split, std::min(ndy_max, 16)));
-    const int chunk = (ndy_max + split - 1) / split;
-    (void)nbt;
-    return (ndy_max + chunk - 1) / chunk;      // no split left without rows
+// The heaviest tile's work (see tile_range).
+static int top_work(const Plan& P, int np) {
+    const int sw = sub_width(P), tpx = sw * np, tpy = 16 / sw;
+    int mx = 1, my = 1;
+    for (int x0 = 0; x0 < P.g.nx; x0 += tpx) mx = std::max(mx, tile_nax(x0, np, sw, P.g.nx, P.d.wx));
+    for (int y0 = 0; y0 < P.g.ny; y0 += tpy) my = std::max(my, tile_nay(y0, tpy, P.g.ny, P.d.wy));
+    return mx * my;
 }
 
-// Split of the adjoint's d_y range: enough workgroups to fill 256 CUs twice.
+// Default number of parts for `groups` workgroups per part and lateral tile: as
+// many as make about 3072 workgroups with work (12 per CU: the dispatcher evens
+// out their differences; fewer, larger ones measured up to 25% slower on the
+// 32 x 32 C-scan), within 64 parts, the steps of a tile and 512 MiB of partials.
+static int default_split(const Plan& P, int np, int groups, int steps, int64_t part_bytes) {
+    const int sw = sub_width(P), tpx = sw * np, tpy = 16 / sw;
+    int64_t sx = 0, sy = 0;
+    for (int x0 = 0; x0 < P.g.nx; x0 += tpx) sx += tile_nax(x0, np, sw, P.g.nx, P.d.wx);
+    for (int y0 = 0; y0 < P.g.ny; y0 += tpy) sy += tile_nay(y0, tpy, P.g.ny, P.d.wy);
+    const double full = std::max(1.0, (double)sx * sy / top_work(P, np) * groups);   // workgroups with work per part
+    const int64_t most = std::max<int64_t>(1, (int64_t(512) << 20) / std::max<int64_t>(1, part_bytes));
+    const int64_t split = std::max<int64_t>(1, std::min<int64_t>({(int64_t)(3072.0 / full + 0.5), 64, steps, most}));
+    return (int)(split >= 8 ? split & ~(int64_t)7 : split);      // whole eighths for the XCDs
+}
+
+int gemm_split(const Plan& P) {
+    const int mu = (int)P.ubins_h.size();
+    const int nw = std::max(1, std::min(P.fwd_nw, (mu + 15) / 16));
+    const int steps = P.g.ny == 1 ? std::min(P.d.wx + 1, 4) : (P.d.wy + 1) * ((P.g.nz + 15) / 16);
+    return default_split(P, fwd_tile_np(P), (mu + 16 * nw - 1) / (16 * nw), steps, (int64_t)P.npos * mu * 8);
+}
+
+// A B-scan's forward: its parts are depth chunks first (a workgroup walks its
+// chunks one after the other, each with a staging round of its own), then a_x.
+int gemm_zsplit(const Plan& P) { return P.g.ny == 1 ? std::min((P.g.nz + 15) / 16, 8) : 1; }
+
 int adj_split(const Plan& P) {
-    const int sw = sub_width(P), tpx = sw * adj_tile_np(P), tpy = 16 / sw;
-    const int ntx = (P.g.nx + tpx - 1) / tpx, nty = (P.g.ny + tpy - 1) / tpy;
-    const int nzt = (P.g.nz + 64 * kAdjNZ - 1) / (64 * kAdjNZ);
-    const int wgs = ntx * nty * nzt;
-    const int ndy_max = std::min(2 * P.d.wy + 1, P.g.ny + tpy - 1);
-    int split = (512 + wgs - 1) / wgs;
-    split = std::max(1, std::min(split, std::min(ndy_max, 8)));
-    const int chunk = (ndy_max + split - 1) / split;
-    return (ndy_max + chunk - 1) / chunk;
+    const int mu = (int)P.ubins_h.size();
+    const int steps = P.g.ny == 1 ? std::min(P.d.wx + 1, 16) : (P.d.wy + 1) * ((mu + 15) / 16);
+    return default_split(P, adj_tile_np(P), (P.g.nz + 63) / 64, steps, P.nvox * 8);
+}
+
+// LDS bytes of one workgroup: the staged rows, the zero cells and the delay
+// (and beam) rows of `tcols` entries per a_x, plus `extra`.
+static size_t gemm_lds(int tpy, int hc, int np, int sw, int ch, int wx, int tcols, bool beam, size_t extra) {
+    return ((size_t)tpy * row_pitch(hc, ch) + zero_run(np, sw, ch)) * sizeof(cf32) +
+           (size_t)(wx + 1) * tcols * (beam ? 8 : 4) + extra;
+}
+
+// Staged chunk: the preferred one, halved until the LDS fits kLdsMax (powers of
+// two: the staging needs the chunk to divide the workgroup), at least 4, which
+// may take more.  Windows whose unpadded chunk of 4 exceeds kLdsMax are refused.
+static int pick_chunk(int prefer, int tpy, int hc, int np, int sw, int wx, int tcols_per, int tcols, bool beam) {
+    const size_t least = (size_t)tpy * hc * 5 * sizeof(cf32) + (tcols ? 16 : 0) +
+                         (size_t)(wx + 1) * (tcols ? tcols : 4 * tcols_per) * (beam ? 8 : 4);
+    if (least > kLdsMax) fail(UFSS_ERR_UNSUPPORTED, "aperture window too wide for the GEMM path");
+    int ch = prefer == 8 ? 8 : 16;
+    while (ch > 4 && gemm_lds(tpy, hc, np, sw, ch, wx, tcols ? tcols : ch * tcols_per, beam, (size_t)ch * 4) > kLdsMax)
+        ch /= 2;
+    return ch;
 }
 
 // Descriptor of one plan's forward GEMM launch; returns the block count.
@@ -748,17 +880,11 @@ static int fwd_args(const Plan& P, const cf32* x, FwdArgs& a, size_t& lds, int n
     a.split = P.fwd_split;
     a.npos = P.npos;
     const int hc = tpx + 2 * a.wx;
-    int zc = P.fwd_zc == 8 ? 8 : 16;
-    const size_t tab = P.d_amp ? 8 : 4;      // delay (+ beam) table bytes per entry
-    auto lds_of = [&](int z) {
-        return (size_t)tpy * hc * (z + 1) * sizeof(cf32) + (size_t)(a.wx + 1) * z * tab;
-    };
-    while (zc > 4 && lds_of(zc) > kLdsMax) zc /= 2;   // powers of two: the staging needs zc | blockDim
-    lds = lds_of(zc);
-    if (lds > kLdsMax) fail(UFSS_ERR_UNSUPPORTED, "aperture window too wide for the GEMM path");
+    a.zc = pick_chunk(P.fwd_zc, tpy, hc, np, a.sw, a.wx, 1, 0, P.d_amp != nullptr);
+    lds = gemm_lds(tpy, hc, np, a.sw, a.zc, a.wx, a.zc, P.d_amp != nullptr, 0);
     if (a.ft) lds = std::max(lds, (size_t)4 * np * 8 * 64 * sizeof(float));   // the folded sums
-    a.zc = zc;
     a.zsplit = std::max(1, P.fwd_zsplit);
+    a.top = top_work(P, np);
     a.nblk = a.ntx * a.nty * a.nbt * a.split * a.zsplit;
     return a.nblk;
 }
@@ -781,27 +907,41 @@ static int adj_args(const Plan& P, cf32* out, AdjArgs& a, size_t& lds, int np, i
     const int tpx = a.sw * np, tpy = 16 / a.sw;
     a.ntx = (a.nx + tpx - 1) / tpx;
     a.nty = (a.ny + tpy - 1) / tpy;
-    const int zspan = 16 * nw * kAdjNZ;
+    const int zspan = 16 * nw;
     a.nzt = (a.nz + zspan - 1) / zspan;
     const int hc = tpx + 2 * a.wx;
-    int kc = P.adj_kc == 8 ? 8 : 16;
-    const size_t tab = P.d_amp ? 8 : 4;      // delay (+ beam) table bytes per entry
-    auto lds_of = [&](int k) {
-        return (size_t)tpy * hc * (k + 1) * sizeof(cf32) + (size_t)(a.wx + 1) * zspan * tab +
-               (size_t)k * 4;
-    };
-    while (kc > 4 && lds_of(kc) > kLdsMax) kc /= 2;   // powers of two (staging)
-    if (lds_of(kc) > kLdsMax) fail(UFSS_ERR_UNSUPPORTED, "aperture window too wide for the GEMM path");
-    a.kc = kc;
-    a.kcons = 1;                              // a band without gaps (the C-scan unions)
-    for (size_t t = 1; t < P.ubins_h.size(); ++t)
-        if (P.ubins_h[t] != P.ubins_h[t - 1] + 1) a.kcons = 0;
-    lds = lds_of(kc);
+    a.kc = pick_chunk(P.adj_kc, tpy, hc, np, a.sw, a.wx, 0, zspan, P.d_amp != nullptr);
+    lds = gemm_lds(tpy, hc, np, a.sw, a.kc, a.wx, zspan, P.d_amp != nullptr, (size_t)a.kc * 4);
     a.split = P.adj_split;
+    a.top = top_work(P, np);
     a.part = P.d_gpart;
     a.nvox = P.nvox;
     a.nblk = a.ntx * a.nty * a.nzt * a.split;
     return a.nblk;
+}
+
+// A kernel may use up to 160 KiB of LDS per workgroup; above 64 KiB it has to be
+// asked for (only windows whose smallest chunk needs more come here).
+template <class K, class A>
+static void launch_with_lds(K kernel, dim3 grid, dim3 block, size_t lds, hipStream_t s, const A& a) {
+    if (lds > kLdsMax)
+        UFSS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipLaunchKernelGGL(kernel, grid, block, lds, s, a);
+    UFSS_HIP(hipGetLastError());
+}
+
+template <int NP, int ZC, int SW, bool DIR>
+static void launch_fwd(const FwdArgs& a, size_t lds, hipStream_t s) {
+    const dim3 grid(a.nblk), block(64 * a.nw);
+    if (a.ft) launch_with_lds(fwd_gemm_f32_kernel<NP, ZC, SW, DIR, true>, grid, block, lds, s, a);
+    else launch_with_lds(fwd_gemm_f32_kernel<NP, ZC, SW, DIR, false>, grid, block, lds, s, a);
+}
+
+template <int NP, int SW, bool DIR>
+static void launch_fwd_zc(const FwdArgs& a, size_t lds, hipStream_t s) {
+    if (a.zc == 16) launch_fwd<NP, 16, SW, DIR>(a, lds, s);
+    else if (a.zc == 8) launch_fwd<NP, 8, SW, DIR>(a, lds, s);
+    else launch_fwd<NP, 4, SW, DIR>(a, lds, s);
 }
 
 void launch_forward_gemm(const Plan& P, const cf32* x, hipStream_t s) {
@@ -809,68 +949,50 @@ void launch_forward_gemm(const Plan& P, const cf32* x, hipStream_t s) {
     size_t lds;
     const int np = fwd_tile_np(P);
     fwd_args(P, x, a, lds, np);
-    const dim3 grid(a.nblk), block(64 * a.nw);
-#define UFSS_FWD(NPV, ZCV)                                                                                   \
-    do {                                                                                                     \
-        if (a.ft) hipLaunchKernelGGL((fwd_gemm_f32_kernel<NPV, ZCV, false, true>), grid, block, lds, s, a); \
-        else hipLaunchKernelGGL((fwd_gemm_f32_kernel<NPV, ZCV>), grid, block, lds, s, a);                   \
-    } while (0)
-#define UFSS_FWDG(NPV, ZCV)                                                                                 \
-    do {                                                                                                    \
-        if (a.ft) hipLaunchKernelGGL((fwd_gemm_f32_kernel<NPV, ZCV, true, true>), grid, block, lds, s, a); \
-        else hipLaunchKernelGGL((fwd_gemm_f32_kernel<NPV, ZCV, true>), grid, block, lds, s, a);            \
-    } while (0)
-    if (a.amp) {
-        if (np == 4) {
-            if (a.zc == 16) UFSS_FWDG(4, 16); else if (a.zc == 8) UFSS_FWDG(4, 8); else UFSS_FWDG(4, 4);
-        } else {
-            if (a.zc == 16) UFSS_FWDG(2, 16); else if (a.zc == 8) UFSS_FWDG(2, 8); else UFSS_FWDG(2, 4);
-        }
-    } else if (np == 4) {
-        if (a.zc == 16) UFSS_FWD(4, 16); else if (a.zc == 8) UFSS_FWD(4, 8); else UFSS_FWD(4, 4);
+    auto go = [&](auto npc, auto swc) {
+        constexpr int NP = decltype(npc)::value, SW = decltype(swc)::value;
+        if (a.amp) launch_fwd_zc<NP, SW, true>(a, lds, s);
+        else launch_fwd_zc<NP, SW, false>(a, lds, s);
+    };
+    using I2 = std::integral_constant<int, 2>;
+    using I4 = std::integral_constant<int, 4>;
+    using I16 = std::integral_constant<int, 16>;
+    if (np == 4) {
+        if (a.sw == 4) go(I4{}, I4{}); else go(I4{}, I16{});
     } else {
-        if (a.zc == 16) UFSS_FWD(2, 16); else if (a.zc == 8) UFSS_FWD(2, 8); else UFSS_FWD(2, 4);
+        if (a.sw == 4) go(I2{}, I4{}); else go(I2{}, I16{});
     }
-#undef UFSS_FWDG
-#undef UFSS_FWD
-    UFSS_HIP(hipGetLastError());
+}
+
+template <int NP, int SW, bool DIR, int NW>
+static void launch_adj_kc(const AdjArgs& a, size_t lds, hipStream_t s) {
+    const dim3 grid(a.nblk), block(64 * NW);
+    if (a.kc == 16) launch_with_lds(adj_gemm_f32_kernel<NP, 16, SW, DIR, NW>, grid, block, lds, s, a);
+    else if (a.kc == 8) launch_with_lds(adj_gemm_f32_kernel<NP, 8, SW, DIR, NW>, grid, block, lds, s, a);
+    else launch_with_lds(adj_gemm_f32_kernel<NP, 4, SW, DIR, NW>, grid, block, lds, s, a);
 }
 
 void launch_adjoint_gemm(const Plan& P, cf32* out, hipStream_t s, bool sum) {
     AdjArgs a;
     size_t lds;
-    const int np = adj_tile_np(P);
-    const int nw = adj_waves(P);
+    const int np = adj_tile_np(P), nw = adj_waves(P);
     adj_args(P, out, a, lds, np, nw);
-    const dim3 grid(a.nblk), block(64 * nw);
-#define UFSS_ADJ(NPV, KCV) hipLaunchKernelGGL((adj_gemm_f32_kernel<NPV, kAdjNZ, KCV>), grid, block, lds, s, a)
-#define UFSS_ADJ2(KCV)                                                                                       \
-    do {                                                                                                     \
-        if (nw == 8) hipLaunchKernelGGL((adj_gemm_f32_kernel_np2<kAdjNZ, KCV, false, 8>), grid, block, lds, s, a); \
-        else hipLaunchKernelGGL((adj_gemm_f32_kernel_np2<kAdjNZ, KCV>), grid, block, lds, s, a);              \
-    } while (0)
-#define UFSS_ADJG(NPV, KCV) hipLaunchKernelGGL((adj_gemm_f32_kernel<NPV, kAdjNZ, KCV, true>), grid, block, lds, s, a)
-#define UFSS_ADJ2G(KCV)                                                                                      \
-    do {                                                                                                     \
-        if (nw == 8) hipLaunchKernelGGL((adj_gemm_f32_kernel_np2<kAdjNZ, KCV, true, 8>), grid, block, lds, s, a); \
-        else hipLaunchKernelGGL((adj_gemm_f32_kernel_np2<kAdjNZ, KCV, true>), grid, block, lds, s, a);        \
-    } while (0)
-    if (a.amp) {
-        if (np == 4) {
-            if (a.kc == 16) UFSS_ADJG(4, 16); else if (a.kc == 8) UFSS_ADJG(4, 8); else UFSS_ADJG(4, 4);
-        } else {
-            if (a.kc == 16) UFSS_ADJ2G(16); else if (a.kc == 8) UFSS_ADJ2G(8); else UFSS_ADJ2G(4);
-        }
-    } else if (np == 4) {
-        if (a.kc == 16) UFSS_ADJ(4, 16); else if (a.kc == 8) UFSS_ADJ(4, 8); else UFSS_ADJ(4, 4);
+    auto go = [&](auto npc, auto swc, auto nwc) {
+        constexpr int NP = decltype(npc)::value, SW = decltype(swc)::value, NW = decltype(nwc)::value;
+        if (a.amp) launch_adj_kc<NP, SW, true, NW>(a, lds, s);
+        else launch_adj_kc<NP, SW, false, NW>(a, lds, s);
+    };
+    using I2 = std::integral_constant<int, 2>;
+    using I4 = std::integral_constant<int, 4>;
+    using I8 = std::integral_constant<int, 8>;
+    using I16 = std::integral_constant<int, 16>;
+    if (np == 4) {
+        if (a.sw == 4) go(I4{}, I4{}, I4{}); else go(I4{}, I16{}, I4{});
+    } else if (nw == 8) {
+        if (a.sw == 4) go(I2{}, I4{}, I8{}); else go(I2{}, I16{}, I8{});
     } else {
-        if (a.kc == 16) UFSS_ADJ2(16); else if (a.kc == 8) UFSS_ADJ2(8); else UFSS_ADJ2(4);
+        if (a.sw == 4) go(I2{}, I4{}, I4{}); else go(I2{}, I16{}, I4{});
     }
-#undef UFSS_ADJ2G
-#undef UFSS_ADJG
-#undef UFSS_ADJ2
-#undef UFSS_ADJ
-    UFSS_HIP(hipGetLastError());
     if (a.split > 1 && sum) launch_sum_parts(P.d_gpart, a.split, P.nvox, out, s);
 }
 
@@ -905,16 +1027,21 @@ int make_desc(GemmKind k, const Plan& P, const void* in, void* out, void* desc, 
 void launch_grouped(GemmKind k, const void* descs, const int2* blk, int nblocks, size_t lds, int threads,
                     hipStream_t s) {
     if (nblocks <= 0) return;
+    auto raise = [&](const void* kernel) {
+        if (lds > kLdsMax) UFSS_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    };
     switch (k) {
         case GemmKind::FwdF32:
             if (threads < 64 || threads > 512 || threads % 64)
                 fail(UFSS_ERR_INVALID_ARG, "grouped forward: workgroup size must be 64 to 512 in steps of 64");
+            raise(reinterpret_cast<const void*>(fwd_gemm_f32_kernel_grouped<kGroupNP>));
             hipLaunchKernelGGL(fwd_gemm_f32_kernel_grouped<kGroupNP>, dim3(nblocks), dim3(threads), lds, s,
                                static_cast<const FwdArgs*>(descs), blk);
             break;
         case GemmKind::AdjF32:
-            hipLaunchKernelGGL((adj_gemm_f32_kernel_grouped<kGroupNP, kAdjNZ>), dim3(nblocks), dim3(256),
-                               lds, s, static_cast<const AdjArgs*>(descs), blk);
+            raise(reinterpret_cast<const void*>(adj_gemm_f32_kernel_grouped<kGroupNP>));
+            hipLaunchKernelGGL(adj_gemm_f32_kernel_grouped<kGroupNP>, dim3(nblocks), dim3(256), lds, s,
+                               static_cast<const AdjArgs*>(descs), blk);
             break;
         default: bf16_launch_grouped(k, descs, blk, nblocks, lds, s); return;
     }

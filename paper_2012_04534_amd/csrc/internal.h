@@ -172,6 +172,7 @@ int launch_forward_post(const Plan& P, cf32* y, const cf32* ymeas, double* part,
 void launch_adjoint_pre(const Plan& P, const cf32* r, hipStream_t s);
 void launch_to_bf16(const cf32* x, void* out, int64_t n, hipStream_t s);
 int gemm_split(const Plan& P);
+int gemm_zsplit(const Plan& P);
 int adj_split(const Plan& P);
 // Sets the split factors (and reallocates the split workspace when they change).
 void plan_set_splits(Plan& P, int fs, int as, int zs);

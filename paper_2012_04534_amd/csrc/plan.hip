@@ -509,10 +509,11 @@ Plan* plan_create(const ufss_geom* g, int m, int per_position, const int32_t* bi
             P->adj_split = bf16_adj_split(*P);
         } else {
             P->fwd_split = (algo == UFSS_ALGO_GEMM) ? gemm_split(*P) : 1;
+            P->fwd_zsplit = (algo == UFSS_ALGO_GEMM) ? gemm_zsplit(*P) : 1;
             P->adj_split = (algo == UFSS_ALGO_GEMM) ? adj_split(*P) : 1;
         }
         if (P->adj_split > 1) P->d_gpart = dalloc<cf32>(*P, (size_t)P->adj_split * P->nvox);
-        P->d_yraw = dalloc<cf32>(*P, (size_t)P->fwd_split * npos * mu);
+        P->d_yraw = dalloc<cf32>(*P, (size_t)P->fwd_split * P->fwd_zsplit * npos * mu);
         P->d_rop = dalloc<cf32>(*P, (size_t)npos * opw);
         if (algo == UFSS_ALGO_GEMM && P->dtype == UFSS_BF16) P->d_xop = dalloc<cf32>(*P, (size_t)(P->nvox + 1) / 2 + 1);
         if (algo == UFSS_ALGO_GEMM && P->dtype == UFSS_BF16) bf16_set_tables(*P, 1);
