@@ -14,13 +14,15 @@
 // integer-turn delays).  P_d is even in d_x and in d_y, so K^ is a cosine
 // transform, even in q_x and q_y: only the quadrant q_x <= L_x / 2,
 // q_y <= L_y / 2 is stored, and each stored entry serves up to four q.
-// K^ is built once per plan in FP64 and stored in FP32, also as a transposed
-// copy [q][k][z] so that both contractions read rows in order; the applies run
-// in FP32.  The contraction streams K^ once per apply and is bound by HBM (or by
-// the last-level cache when K^ fits there); the lateral transforms are small
-// products with twiddle tables.
+// With both axes alike (same pitch, window and size) K^ is also symmetric in
+// (q_y, q_x): half the quadrant is stored, each entry serving up to eight q.
+// K^ is built once per plan in FP64 and stored in FP32 (BF16 plans: BF16); the
+// applies run in FP32.  The contraction streams K^ once per apply and is bound by
+// HBM (or by the last-level cache when K^ fits there); the lateral transforms are
+// small products with twiddle tables.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -220,154 +222,200 @@ static void twiddle(cf32* out, const cf32* in, const cf32* W, int B, int I, int 
     UFSS_HIP(hipGetLastError());
 }
 
-// The up-to-four transform indices (q_y, q_x) of quadrant entry (oy, ox),
-// enumerated as q = a nx2 + b with q_y = oy or ly - oy (a) and q_x = ox or
-// lx - ox (b); nx2 (ny2) is 1 on the axis's self-mirrored entries.  Computed
-// per use (no per-thread arrays, which would live in scratch memory).
+// The transform indices (q_y, q_x) that share the stored entry (oy, ox): q_y = oy
+// or ly - oy (a) and q_x = ox or lx - ox (b), one of each on an axis's
+// self-mirrored entries, and, where the axes are alike (SWAP), the same with
+// the axes exchanged.  Up to 4, or 8 with SWAP.
 struct Orbit {
-    int oy, ox, ly, lx, nx2, n;
-    __device__ Orbit(int oy_, int ox_, int ly_, int lx_) : oy(oy_), ox(ox_), ly(ly_), lx(lx_) {
+    int oy, ox, ly, lx, nx2, n4, n;
+    __device__ Orbit(int2 o, int ly_, int lx_, bool swap) : oy(o.x), ox(o.y), ly(ly_), lx(lx_) {
         const int ny2 = (oy == 0 || 2 * oy == ly) ? 1 : 2;
         nx2 = (ox == 0 || 2 * ox == lx) ? 1 : 2;
-        n = ny2 * nx2;
+        n4 = ny2 * nx2;
+        n = swap && oy != ox ? 2 * n4 : n4;
     }
     // row index q_y lx + q_x of member q
     __device__ int64_t row(int q) const {
-        const int a = q / nx2, b = q - a * nx2;
-        return (int64_t)(a ? ly - oy : oy) * lx + (b ? lx - ox : ox);
+        const int e = q >= n4, w = q - e * n4;
+        const int a = w / nx2, b = w - a * nx2;
+        const int qa = a ? ly - oy : oy, qb = b ? lx - ox : ox;
+        return e ? (int64_t)qb * lx + qa : (int64_t)qa * lx + qb;
     }
 };
 
-// Contraction, both directions: one workgroup per quadrant entry (its up to
-// four transform indices q), out[q][c] = sum_r T[o][r][c] in[q][r] (CONJ:
-// conj(T)).  Forward: c = bin, r = depth, T = K^[o][z][k]; adjoint: c = depth,
-// r = bin, T = the transposed copy K^t[o][k][z].  Consecutive threads take
-// consecutive c (coalesced rows of T); when C is below the workgroup size NT
-// the reduction range is split over G = NT / C thread groups whose partial
-// sums meet in LDS in a fixed order.
+// Contraction, both directions, on one stored table K^[o][z][k] (rows of k
+// padded to an even stride): forward out[q][k] = sum_z K^[o][z][k] in[q][z],
+// adjoint out[q][z] = sum_k conj(K^[o][z][k]) in[q][k] for the members q of
+// entry o.
 //
-// The table is streamed kPF rows ahead: each thread holds the current block of
-// kPF entries of its column while the next block is in flight, and the first
-// block is requested before the input rows are staged.  Four rows ahead keep
-// the kernel within 64 registers, so eight waves fit per SIMD (four
-// 512-thread workgroups per CU): more workgroups in flight and fewer rounds
-// over the chip than eight rows ahead at six waves (measured on the 32 x 32
-// and 64 x 64 C-scans).
-static constexpr int kPF = 4;
+// What bounds it: the table, read once per apply.  It runs on the FP32 matrix
+// cores because they do what the two directions need on one layout: with
+// v_mfma_f32_16x16x4f32 the 16 columns are the real and imaginary parts of up to
+// 8 members, the rows 16 outputs and the reduction 4 entries, so the adjoint
+// reduces along the contiguous index without a transposed copy of the table,
+// and an entry loaded once serves all members (8 FMAs per byte, 20 TB/s of
+// table at the FP32 matrix rate; the earlier vector form took 4 members, a
+// transposed copy and a broadcast LDS read per entry and member).  A complex
+// product is two real ones into one accumulator: K_re times the column, K_im
+// times the neighbouring column with a sign.
+//   forward: lane l loads entries (z = 4 s + l / 16, k = 2 (l % 16), + 1) of 32
+//   outputs: two tiles of 16 rows, rows 2 i and 2 i + 1
+//   adjoint: lane l loads entries (z = l % 16, k = 16 s + 4 (l / 16) .. + 3): one
+//   tile of 16 rows, four steps of the reduction, 128 contiguous bytes per row
+// A workgroup of kNW waves takes one entry and a block of its outputs; a wave
+// takes one group of TB tiles (16-byte loads kPD steps ahead; 8-byte in BF16)
+// and, where there are fewer groups than waves, a share of the reduction,
+// summed over the waves in LDS in fixed order.  Members are staged in LDS, kRC
+// reduction entries at a time, zero past the last; lanes past the last output
+// or the last reduction entry load some other finite entry (the table is
+// followed by zeros), which meets a zero column or a row that is not stored.
+//
+// Per launch, forward / adjoint, before (quadrant, vector FMAs) and after: 64 x
+// 64 x 512 (128 bins, W = 16) 181 / 176 -> 96 / 100 us (4.7 TB/s of table), 32 x
+// 32 x 256 (66 bins, full) 27.5 / 27.3 -> 20.4 / 22.9, 50 x 50 x 50 (256 bins) 53 /
+// 52 -> 29 / 27; unequal axes (45 x 51 x 301, 76 bins) 45 / 51 -> 39 / 43.
+static constexpr int kPD = 2;
+static constexpr int kNW = 4;
+static constexpr int kRC = 512;
 
-// Table entries as FP32 pairs (FP32 plans) or BF16 pairs (BF16 plans: the table
-// rounded to nearest even once at plan time, products and sums in FP32).
-__device__ __forceinline__ cf32 entry(const cf32& v) { return v; }
-__device__ __forceinline__ cf32 entry(const cbf16& v) { return cf32{(float)v.re, (float)v.im}; }
+template <typename TT> struct TabPair;
+template <> struct TabPair<cf32> {      // two FP32 entries
+    f4v v;
+    __device__ void load(const cf32* p) { v = *reinterpret_cast<const f4v*>(p); }
+    __device__ f4v get() const { return v; }
+};
+template <> struct TabPair<cbf16> {     // two BF16 entries (rounded to nearest even once at plan time)
+    uint2 v;
+    __device__ void load(const cbf16* p) { v = *reinterpret_cast<const uint2*>(p); }
+    __device__ f4v get() const {
+        return f4v{__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u),
+                   __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u)};
+    }
+};
 
-template <bool CONJ, int NT, typename TT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void contract_kernel(const TT* __restrict__ tab,
-                                                      const cf32* __restrict__ in,
-                                                      cf32* __restrict__ out, int ly, int lx,
-                                                      int nox, int C, int R) {
-    // rows ahead: BF16 entries are half the bytes, so two more rows (as many
-    // as fit the 64 registers of eight waves per SIMD) keep more bytes in flight
-    constexpr int PF = sizeof(TT) == sizeof(cf32) ? kPF : kPF + 2;
+// Outputs of one group (TB tiles), and reduction entries of a step.
+__host__ __device__ constexpr int group_rows(bool fwd, int tb) { return (fwd ? 32 : 16) * tb; }
+__host__ __device__ constexpr int step_len(bool fwd) { return fwd ? 4 : 16; }
+
+template <bool FWD, int TB, bool SWAP, typename TT>
+__global__ __launch_bounds__(64 * kNW) void contract_kernel(const TT* __restrict__ tab, const int2* __restrict__ orbits,
+                                                       const cf32* __restrict__ in, cf32* __restrict__ out,
+                                                       int ly, int lx, int nz, int mus, int C, int R, int groups) {
     extern __shared__ __align__(16) unsigned char smem[];
-    cf32* vs = reinterpret_cast<cf32*>(smem);                 // [4][R] input rows
-    float* red = reinterpret_cast<float*>(vs + 4 * R);        // [G][4][C][2] partials
-    const int o = blockIdx.x, oy = o / nox, ox = o - oy * nox;
-    const Orbit orb(oy, ox, ly, lx);
+    float* xs = reinterpret_cast<float*>(smem);               // [kRC][RS] members' columns
+    float* red = xs;                                          // [shares][16][rows + 1] after the reduction
+    constexpr int NQ = SWAP ? 8 : 4, RS = 2 * NQ + 2;
+    constexpr int GR = group_rows(FWD, TB), ND = FWD ? 2 * TB : TB, ST = step_len(FWD), NL = FWD ? 1 : 2;
+    const Orbit orb(orbits[blockIdx.x], ly, lx, SWAP);
     const int nq = orb.n;
-    const TT* tb = tab + (int64_t)o * R * C;
-    const int W = C >= NT ? NT : C;                           // threads per group (c stride)
-    const int G = C >= NT ? 1 : NT / C;
-    const int grp = threadIdx.x / W;
-    const int lane_c = threadIdx.x - grp * W;
-    const int rper = (R + G - 1) / G;
-    const int r0 = grp * rper, r1 = min(R, r0 + rper);
-    const bool active = grp < G;
-    TT cur[PF];
+    const TT* tb = tab + (int64_t)blockIdx.x * nz * mus;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int c0 = blockIdx.y * groups * GR;                  // first output of the block
+    const int ng = min(groups, (C - c0 + GR - 1) / GR);       // its groups (1..kNW)
+    const int shares = kNW / ng;                              // waves per group
+    const int grp = wave % ng, share = wave / ng;
+    const bool active = share < shares;
+    const int i = lane & 15, kq = lane >> 4;
+    const int gc0 = c0 + grp * GR;
+    // columns: member i / 2, real (even) or imaginary part; the K_im product
+    // takes the other part, negative where the (conjugated) product says so
+    const int col = SWAP ? i : (i & 7);
+    const float sgn = (FWD == ((i & 1) == 0)) ? -1.f : 1.f;
+    auto other = [&](float b) {
+        return sgn * __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(b), 0xB1, 0xf, 0xf, true));
+    };
+
+    f4v D[ND];
 #pragma unroll
-    for (int t = 0; t < PF; ++t)
-        cur[t] = (active && lane_c < C && r0 + t < r1) ? tb[(int64_t)(r0 + t) * C + lane_c] : TT{};
-    for (int t = threadIdx.x; t < nq * R; t += blockDim.x) {
-        const int q = t / R, r = t - q * R;
-        vs[t] = in[orb.row(q) * R + r];
-    }
-    __syncthreads();
-    for (int c = lane_c; c < C && active; c += W) {
-        const TT* col = tb + c;
-        float ar[4] = {0.f, 0.f, 0.f, 0.f}, ai[4] = {0.f, 0.f, 0.f, 0.f};
-        for (int rb = r0; rb < r1; rb += PF) {
-            TT nxt[PF];
+    for (int t = 0; t < ND; ++t) D[t] = f4v{0.f, 0.f, 0.f, 0.f};
+    // this lane's entries of step 0, and what a step and a tile add
+    int off[TB];
 #pragma unroll
-            for (int t = 0; t < PF; ++t) {
-                const int r = rb + PF + t;
-                nxt[t] = r < r1 ? col[(int64_t)r * C] : TT{};
+    for (int t = 0; t < TB; ++t)
+        off[t] = FWD ? kq * mus + min(gc0 + 32 * t + 2 * i, mus - 2) : min(gc0 + 16 * t + i, nz - 1) * mus + 4 * kq;
+    TabPair<TT> buf[kPD][TB][NL];
+    auto load = [&](TabPair<TT> (&b)[TB][NL], int r0, int st) {
+        const TT* p = tb + (FWD ? (int64_t)(r0 + 4 * st) * mus : (int64_t)(r0 + 16 * st));
+#pragma unroll
+        for (int t = 0; t < TB; ++t)
+#pragma unroll
+            for (int h = 0; h < NL; ++h) b[t][h].load(p + off[t] + 2 * h);
+    };
+    for (int r0 = 0; r0 < R; r0 += kRC) {
+        const int rc = min(kRC, R - r0), nst = (rc + ST - 1) / ST;
+#pragma unroll
+        for (int p = 0; p < kPD; ++p)
+            if (active && share + p * shares < nst) load(buf[p], r0, share + p * shares);
+        if (r0 > 0) __syncthreads();                          // the previous chunk's columns are read
+        for (int r = threadIdx.x; r < nst * ST; r += 64 * kNW) {
+            cf32 v[NQ];
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                v[q] = cf32{0.f, 0.f};
+                if (q < nq && r < rc) v[q] = in[orb.row(q) * R + r0 + r];
             }
 #pragma unroll
-            for (int t = 0; t < PF; ++t) {
-                if (rb + t >= r1) break;
-                const cf32 kv = entry(cur[t]);
-                const float ki = CONJ ? -kv.im : kv.im;
+            for (int q = 0; q < NQ; ++q) *reinterpret_cast<cf32*>(xs + r * RS + 2 * q) = v[q];
+        }
+        __syncthreads();
+        if (!active) continue;
+        for (int st0 = share; st0 < nst; st0 += kPD * shares) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if (q >= nq) break;
-                    const cf32 v = vs[q * R + rb + t];
-                    ar[q] = fmaf(kv.re, v.re, ar[q]);
-                    ar[q] = fmaf(-ki, v.im, ar[q]);
-                    ai[q] = fmaf(kv.re, v.im, ai[q]);
-                    ai[q] = fmaf(ki, v.re, ai[q]);
+            for (int p = 0; p < kPD; ++p) {
+                const int st = st0 + p * shares;
+                if (st >= nst) break;                         // wave-uniform
+                const float* xr = xs + (FWD ? 4 * st + kq : 16 * st + 4 * kq) * RS + col;
+                if constexpr (FWD) {
+                    const float b0 = xr[0], o0 = other(b0);
+#pragma unroll
+                    for (int t = 0; t < TB; ++t) {
+                        const f4v a = buf[p][t][0].get();
+                        D[2 * t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b0, D[2 * t], 0, 0, 0);
+                        D[2 * t + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, b0, D[2 * t + 1], 0, 0, 0);
+                        D[2 * t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, o0, D[2 * t], 0, 0, 0);
+                        D[2 * t + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, o0, D[2 * t + 1], 0, 0, 0);
+                    }
+                } else {
+#pragma unroll
+                    for (int h = 0; h < NL; ++h) {
+                        const float b0 = xr[2 * h * RS], b1 = xr[(2 * h + 1) * RS], o0 = other(b0), o1 = other(b1);
+                        f4v a[TB];
+#pragma unroll
+                        for (int t = 0; t < TB; ++t) a[t] = buf[p][t][h].get();
+#pragma unroll
+                        for (int t = 0; t < TB; ++t) D[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t].x, b0, D[t], 0, 0, 0);
+#pragma unroll
+                        for (int t = 0; t < TB; ++t) D[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t].y, o0, D[t], 0, 0, 0);
+#pragma unroll
+                        for (int t = 0; t < TB; ++t) D[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t].z, b1, D[t], 0, 0, 0);
+#pragma unroll
+                        for (int t = 0; t < TB; ++t) D[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t].w, o1, D[t], 0, 0, 0);
+                    }
                 }
-            }
-#pragma unroll
-            for (int t = 0; t < PF; ++t) cur[t] = nxt[t];
-        }
-        if (G == 1) {
-            for (int q = 0; q < nq; ++q)
-                out[orb.row(q) * C + c] = cf32{ar[q], ai[q]};
-        } else {
-            for (int q = 0; q < nq; ++q) {
-                red[((grp * 4 + q) * C + c) * 2] = ar[q];
-                red[((grp * 4 + q) * C + c) * 2 + 1] = ai[q];
+                if (st + kPD * shares < nst) load(buf[p], r0, st + kPD * shares);
             }
         }
-        // first block of this thread's next column (C > NT only)
-        const int cn = c + W;
-#pragma unroll
-        for (int t = 0; t < PF; ++t)
-            cur[t] = (cn < C && r0 + t < r1) ? tb[(int64_t)(r0 + t) * C + cn] : TT{};
     }
-    if (G == 1) return;
+    __syncthreads();                                          // the columns are read; red takes their place
+    const int rows = min(groups * GR, C - c0), pitch = ng * GR + 1;
+    if (active) {
+#pragma unroll
+        for (int t = 0; t < ND; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int lr = FWD ? 32 * (t >> 1) + 2 * (4 * kq + r) + (t & 1) : 16 * t + 4 * kq + r;
+                red[(share * 16 + i) * pitch + grp * GR + lr] = D[t][r];
+            }
+    }
     __syncthreads();
-    for (int t = threadIdx.x; t < nq * C; t += blockDim.x) {
-        const int q = t / C, c = t - q * C;
-        float sr = 0.f, si = 0.f;
-        for (int g2 = 0; g2 < G; ++g2) {
-            sr += red[((g2 * 4 + q) * C + c) * 2];
-            si += red[((g2 * 4 + q) * C + c) * 2 + 1];
+    for (int t = threadIdx.x; t < nq * rows; t += 64 * kNW) {
+        const int q = t / rows, c = t - q * rows;
+        float re = 0.f, im = 0.f;
+        for (int h = 0; h < shares; ++h) {
+            re += red[(h * 16 + 2 * q) * pitch + c];
+            im += red[(h * 16 + 2 * q + 1) * pitch + c];
         }
-        out[orb.row(q) * C + c] = cf32{sr, si};
-    }
-}
-
-// Threads per workgroup: 512 when the contiguous index is short (more groups
-// over the reduction, more loads in flight) or long enough to give every
-// thread one column of its own, else 256 (measured on the 32 x 32 and 64 x 64
-// C-scans).
-static int contract_threads(int C) { return (C <= 128 || C >= 512) ? 512 : 256; }
-
-static size_t contract_lds(int C, int R) {
-    const int NT = contract_threads(C);
-    const int G = C >= NT ? 1 : NT / C;
-    return (size_t)4 * R * sizeof(cf32) + (G > 1 ? (size_t)G * 4 * C * 2 * sizeof(float) : 0);
-}
-
-// Plan time: T[o][b][a] = S[o][a][b] for S of shape [A][B] per entry (the
-// transposed copy of K^: A = nz, B = mu).
-__global__ void transpose_kernel(const cf32* __restrict__ src, cf32* __restrict__ dst, int A, int B) {
-    const int o = blockIdx.y;
-    const cf32* s = src + (int64_t)o * A * B;
-    cf32* d = dst + (int64_t)o * A * B;
-    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < A * B; t += gridDim.x * blockDim.x) {
-        const int b = t / A, a = t - b * A;
-        d[t] = s[(int64_t)a * B + b];
+        out[orb.row(q) * C + c0 + c] = cf32{re, im};
     }
 }
 
@@ -390,29 +438,81 @@ __global__ void phasor64_kernel(const uint32_t* __restrict__ u, const float* __r
     }
 }
 
-// out[b][i][c] = sum_j C[i][j] in[b][j][c] with a real FP64 weight table
-// (the cosine transforms of the build); OUTF: FP32 output.
-template <bool OUTF>
-__global__ __launch_bounds__(256) void cos_kernel(void* __restrict__ out, const double2* __restrict__ in,
+// The two cosine transforms of the build take kBI outputs per thread: each FP64
+// input is loaded once for them (32 x 32 C-scan: 0.6 + 0.7 ms of the plan with
+// one output per thread).
+static constexpr int kBI = 8;
+
+// out[b][i][c] = sum_j C[i][j] in[b][j][c] with a real FP64 weight table (over d_x).
+__global__ __launch_bounds__(256) void cos_kernel(double2* __restrict__ out, const double2* __restrict__ in,
                                                   const double* __restrict__ Cw, int I, int J,
                                                   int64_t C, int64_t sib, int64_t sij,
                                                   int64_t sob, int64_t soi) {
     const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int i = blockIdx.y, b = blockIdx.z;
-    if (c >= C || i >= I) return;
-    double re = 0.0, im = 0.0;
+    const int i0 = blockIdx.y * kBI, b = blockIdx.z;
+    if (c >= C) return;
+    double re[kBI], im[kBI];
+#pragma unroll
+    for (int t = 0; t < kBI; ++t) re[t] = im[t] = 0.0;
     const double2* src = in + (int64_t)b * sib + c;
     for (int j = 0; j < J; ++j) {
-        const double w = Cw[(int64_t)i * J + j];
         const double2 v = src[(int64_t)j * sij];
-        re += w * v.x;
-        im += w * v.y;
+#pragma unroll
+        for (int t = 0; t < kBI; ++t) {
+            const double w = Cw[(int64_t)min(i0 + t, I - 1) * J + j];
+            re[t] += w * v.x;
+            im[t] += w * v.y;
+        }
     }
-    const int64_t o = (int64_t)b * sob + (int64_t)i * soi + c;
-    if (OUTF)
-        static_cast<cf32*>(out)[o] = cf32{(float)re, (float)im};
-    else
-        static_cast<double2*>(out)[o] = double2{re, im};
+#pragma unroll
+    for (int t = 0; t < kBI; ++t)
+        if (i0 + t < I) out[(int64_t)b * sob + (int64_t)(i0 + t) * soi + c] = double2{re[t], im[t]};
+}
+
+// Index of the stored entry (oy, ox) (SWAP: oy <= ox), rows of oy one after another.
+__host__ __device__ static inline int entry_index(int oy, int ox, int nox, bool swap) {
+    return swap ? oy * nox - oy * (oy - 1) / 2 + ox - oy : oy * nox + ox;
+}
+
+// The stored table: T[(oy, ox)][z][k] = sum_dy hy[oy][dy] S[dy][ox][z][k], rounded
+// to FP32 (and from there to BF16), rows of k padded with zeros to the stride mus.
+__device__ __forceinline__ void put(cf32* t, float re, float im) { *t = cf32{re, im}; }
+__device__ __forceinline__ void put(cbf16* t, float re, float im) { *t = to_cbf16(re, im); }
+
+template <typename TT>
+__global__ __launch_bounds__(256) void table_kernel(TT* __restrict__ tab, const double2* __restrict__ S,
+                                                    const double* __restrict__ hy, int J, int nox, int noy, int swap,
+                                                    int nz, int mu, int mus) {
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int ox = blockIdx.y, oy0 = blockIdx.z * kBI;
+    const int oy_end = swap ? min(noy, ox + 1) : noy;
+    if (t >= (int64_t)nz * mus || oy0 >= oy_end) return;
+    const int z = (int)(t / mus), k = (int)(t - (int64_t)z * mus);
+    double re[kBI], im[kBI];
+#pragma unroll
+    for (int i = 0; i < kBI; ++i) re[i] = im[i] = 0.0;
+    if (k < mu) {
+        const int64_t zc = (int64_t)nz * mu;
+        const double2* src = S + (int64_t)ox * zc + (int64_t)z * mu + k;
+        for (int j = 0; j < J; ++j) {
+            const double2 v = src[(int64_t)j * nox * zc];
+#pragma unroll
+            for (int i = 0; i < kBI; ++i) {
+                const double w = hy[(int64_t)min(oy0 + i, noy - 1) * J + j];
+                re[i] += w * v.x;
+                im[i] += w * v.y;
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kBI; ++i) {
+        if (oy0 + i >= oy_end) break;
+        // two roundings, as FP32 plans followed by a conversion: the compiler would
+        // otherwise round FP64 to BF16 at once, another value in the FP32 ties
+        float fr = (float)re[i], fi = (float)im[i];
+        asm volatile("" : "+v"(fr), "+v"(fi));
+        put(tab + (int64_t)entry_index(oy0 + i, ox, nox, swap) * nz * mus + t, fr, fi);
+    }
 }
 
 // Cyclic transform size per axis: the smallest L >= N + W (and >= 1).
@@ -482,9 +582,22 @@ void fft_setup(Plan& P) {
     UFSS_HIP(hipMalloc(&P.d_ft, tbytes));
     P.ws_bytes += 2 * wbytes + tbytes;
 
-    // K^ in FP64: phasors, cosine transform over d_x, then over d_y
+    // stored entries: the quadrant, or, with both axes alike (K^ is then symmetric
+    // in q_y and q_x: half the table), its part oy <= ox
+    P.fft_swap = lx == ly && wx == wy && P.g.dx == P.g.dy;
+    P.fft_mus = (mu + 1) & ~1;
+    std::vector<int2> orb;
+    for (int oy = 0; oy < noy; ++oy)
+        for (int ox = P.fft_swap ? oy : 0; ox < nox; ++ox) orb.push_back(int2{oy, ox});
+    P.fft_entries = (int)orb.size();
+    UFSS_HIP(hipMalloc(&P.d_orb, orb.size() * sizeof(int2)));
+    UFSS_HIP(hipMemcpy(P.d_orb, orb.data(), orb.size() * sizeof(int2), hipMemcpyHostToDevice));
+
+    // K^ in FP64: phasors, cosine transform over d_x, then over d_y into the table
     const int64_t ncell = (int64_t)(wy + 1) * (wx + 1) * nz;
     const int64_t zc = (int64_t)nz * mu;                 // channels (z, k)
+    const int64_t row = (int64_t)nz * P.fft_mus;         // table values per entry
+    const size_t tbytes1 = P.dtype == UFSS_BF16 ? sizeof(cbf16) : sizeof(cf32);
     double2 *p64 = nullptr, *s64 = nullptr;
     double *cx = nullptr, *cy = nullptr;
     std::vector<double> hx((size_t)nox * (wx + 1)), hy((size_t)noy * (wy + 1));
@@ -494,14 +607,22 @@ void fft_setup(Plan& P) {
     for (int q = 0; q < noy; ++q)
         for (int d = 0; d <= wy; ++d)
             hy[(size_t)q * (wy + 1) + d] = (d == 0 ? 1.0 : 2.0) * std::cos(2.0 * M_PI * (double)(((int64_t)q * d) % ly) / ly);
+    auto release = [&]() {
+        if (p64) (void)hipFree(p64);
+        if (s64) (void)hipFree(s64);
+        if (cx) (void)hipFree(cx);
+        if (cy) (void)hipFree(cy);
+    };
     try {
         UFSS_HIP(hipMalloc(&p64, ncell * mu * sizeof(double2)));
         UFSS_HIP(hipMalloc(&s64, (int64_t)(wy + 1) * nox * zc * sizeof(double2)));
         UFSS_HIP(hipMalloc(&cx, hx.size() * sizeof(double)));
         UFSS_HIP(hipMalloc(&cy, hy.size() * sizeof(double)));
-        UFSS_HIP(hipMalloc(&P.d_khat, (int64_t)noy * nox * zc * sizeof(cf32)));
-        UFSS_HIP(hipMalloc(&P.d_khat_t, (int64_t)noy * nox * zc * sizeof(cf32)));
-        P.ws_bytes += 2 * (int64_t)noy * nox * zc * sizeof(cf32);
+        // the contraction may load up to a step past the last entry's rows
+        const int64_t slack = 4 * P.fft_mus + 16;
+        UFSS_HIP(hipMalloc(&P.d_khat, (P.fft_entries * row + slack) * tbytes1));
+        UFSS_HIP(hipMemset(static_cast<char*>(P.d_khat) + P.fft_entries * row * tbytes1, 0, slack * tbytes1));
+        P.ws_bytes += (P.fft_entries * row + slack) * (int64_t)tbytes1 + P.fft_entries * (int64_t)sizeof(int2);
         UFSS_HIP(hipMemcpy(cx, hx.data(), hx.size() * sizeof(double), hipMemcpyHostToDevice));
         UFSS_HIP(hipMemcpy(cy, hy.data(), hy.size() * sizeof(double), hipMemcpyHostToDevice));
         const int64_t n = ncell * mu;
@@ -510,53 +631,66 @@ void fft_setup(Plan& P) {
                            P.d_ubins, ncell, mu, p64);
         UFSS_HIP(hipGetLastError());
         // S[dy][qx][z][k] = sum_dx hx[qx][dx] P[dy][dx][z][k]
-        hipLaunchKernelGGL(cos_kernel<false>, dim3((unsigned)((zc + 255) / 256), nox, wy + 1), dim3(256),
-                           0, nullptr, (void*)s64, p64, cx, nox, wx + 1, zc, (int64_t)(wx + 1) * zc, zc,
+        hipLaunchKernelGGL(cos_kernel, dim3((unsigned)((zc + 255) / 256), (nox + kBI - 1) / kBI, wy + 1), dim3(256),
+                           0, nullptr, s64, p64, cx, nox, wx + 1, zc, (int64_t)(wx + 1) * zc, zc,
                            (int64_t)nox * zc, zc);
         UFSS_HIP(hipGetLastError());
-        // K^[qy][qx][z][k] = sum_dy hy[qy][dy] S[dy][qx][z][k]
-        hipLaunchKernelGGL(cos_kernel<true>, dim3((unsigned)((zc + 255) / 256), noy, nox), dim3(256),
-                           0, nullptr, (void*)P.d_khat, s64, cy, noy, wy + 1, zc, zc, (int64_t)nox * zc,
-                           zc, (int64_t)nox * zc);
+        const dim3 grid((unsigned)((row + 255) / 256), nox, (noy + kBI - 1) / kBI);
+        if (P.dtype == UFSS_BF16)
+            hipLaunchKernelGGL(table_kernel<cbf16>, grid, dim3(256), 0, nullptr, static_cast<cbf16*>(P.d_khat), s64, cy,
+                               wy + 1, nox, noy, P.fft_swap, nz, mu, P.fft_mus);
+        else
+            hipLaunchKernelGGL(table_kernel<cf32>, grid, dim3(256), 0, nullptr, static_cast<cf32*>(P.d_khat), s64, cy,
+                               wy + 1, nox, noy, P.fft_swap, nz, mu, P.fft_mus);
         UFSS_HIP(hipGetLastError());
-        hipLaunchKernelGGL(transpose_kernel, dim3((unsigned)std::min<int64_t>((zc + 255) / 256, 1024), noy * nox),
-                           dim3(256), 0, nullptr, static_cast<const cf32*>(P.d_khat),
-                           static_cast<cf32*>(P.d_khat_t), nz, mu);
-        UFSS_HIP(hipGetLastError());
-        if (P.dtype == UFSS_BF16) {
-            // BF16 plans stream both copies of the table in BF16 (rounded to
-            // nearest even once, here); the FP32 copies are released
-            const int64_t n = (int64_t)noy * nox * zc;
-            void* k16 = nullptr;
-            void* kt16 = nullptr;
-            try {
-                UFSS_HIP(hipMalloc(&k16, n * sizeof(cbf16)));
-                UFSS_HIP(hipMalloc(&kt16, n * sizeof(cbf16)));
-            } catch (...) {
-                if (k16) (void)hipFree(k16);
-                throw;
-            }
-            launch_to_bf16(static_cast<const cf32*>(P.d_khat), k16, n, nullptr);
-            launch_to_bf16(static_cast<const cf32*>(P.d_khat_t), kt16, n, nullptr);
-            UFSS_HIP(hipDeviceSynchronize());
-            (void)hipFree(P.d_khat);
-            (void)hipFree(P.d_khat_t);
-            P.d_khat = k16;
-            P.d_khat_t = kt16;
-            P.ws_bytes -= 2 * n * (int64_t)(sizeof(cf32) - sizeof(cbf16));
-        }
         UFSS_HIP(hipDeviceSynchronize());
     } catch (...) {
-        if (p64) (void)hipFree(p64);
-        if (s64) (void)hipFree(s64);
-        if (cx) (void)hipFree(cx);
-        if (cy) (void)hipFree(cy);
+        release();
         throw;
     }
-    (void)hipFree(p64);
-    (void)hipFree(s64);
-    (void)hipFree(cx);
-    (void)hipFree(cy);
+    release();
+}
+
+// One contraction launch: tiles per wave by the number of outputs (forward: up
+// to 3 blocks of 32, as few padded ones as possible; adjoint: up to 2 tiles of
+// 16), at most kNW groups per workgroup (one per wave), fewer while the grid has
+// under 512 workgroups (the waves then share the reduction).
+template <bool FWD, bool SWAP, typename TT>
+static void contract(const Plan& P, hipStream_t s) {
+    const int mu = (int)P.ubins_h.size(), nz = P.g.nz;
+    const int C = FWD ? mu : nz, R = FWD ? nz : mu;
+    const int blocks = (C + group_rows(FWD, 1) - 1) / group_rows(FWD, 1);
+    int tb = std::min(blocks, FWD ? 3 : 2);
+    for (int t = tb - 1; t >= 2; --t)
+        if ((blocks + t - 1) / t * t < (blocks + tb - 1) / tb * tb) tb = t;
+    const int all = (blocks + tb - 1) / tb, gr = group_rows(FWD, tb);
+    int g = std::min(all, kNW);
+    while (g > 1 && P.fft_entries * ((all + g - 1) / g) < 512) --g;
+    const dim3 grid(P.fft_entries, (all + g - 1) / g);
+    const int rs = (SWAP ? 16 : 8) + 2;
+    const size_t cols = (size_t)(std::min(R, kRC) + step_len(FWD)) * rs;
+    size_t red = 0;                       // over the group counts a block may have
+    for (int n : {g, all - (all - 1) / g * g}) red = std::max(red, (size_t)(kNW / n) * 16 * (n * gr + 1));
+    const size_t lds = std::max(cols, red) * sizeof(float);
+    auto go = [&](auto tbc) {
+        constexpr int TB = decltype(tbc)::value;
+        hipLaunchKernelGGL((contract_kernel<FWD, TB, SWAP, TT>), grid, dim3(64 * kNW), lds, s,
+                           static_cast<const TT*>(P.d_khat), P.d_orb, P.d_fa, P.d_fb, P.fft_ly, P.fft_lx, nz,
+                           P.fft_mus, C, R, g);
+    };
+    if (tb == 1) go(std::integral_constant<int, 1>{});
+    else if (tb == 2) go(std::integral_constant<int, 2>{});
+    else if constexpr (FWD) go(std::integral_constant<int, 3>{});
+    UFSS_HIP(hipGetLastError());
+}
+
+template <bool FWD>
+static void contract(const Plan& P, hipStream_t s) {
+    if (P.dtype == UFSS_BF16) {
+        if (P.fft_swap) contract<FWD, true, cbf16>(P, s); else contract<FWD, false, cbf16>(P, s);
+    } else {
+        if (P.fft_swap) contract<FWD, true, cf32>(P, s); else contract<FWD, false, cf32>(P, s);
+    }
 }
 
 // Forward, in three steps (the contraction is the core kernel):
@@ -568,26 +702,7 @@ void fft_fwd_transform(const Plan& P, const cf32* x, hipStream_t s) {
 }
 
 //   Y^[q][k] = sum_z K^[q][z][k] X^[q][z]
-void fft_fwd_contract(const Plan& P, hipStream_t s) {
-    const int lx = P.fft_lx, ly = P.fft_ly, nox = lx / 2 + 1, noy = ly / 2 + 1;
-    const int mu = (int)P.ubins_h.size(), nz = P.g.nz;
-    const size_t lds = contract_lds(mu, nz);
-    const dim3 grid(noy * nox);
-    if (P.dtype == UFSS_BF16) {
-        const cbf16* t = static_cast<const cbf16*>(P.d_khat);
-        if (contract_threads(mu) == 512)
-            hipLaunchKernelGGL((contract_kernel<false, 512, cbf16>), grid, dim3(512), lds, s, t, P.d_fa, P.d_fb, ly, lx, nox, mu, nz);
-        else
-            hipLaunchKernelGGL((contract_kernel<false, 256, cbf16>), grid, dim3(256), lds, s, t, P.d_fa, P.d_fb, ly, lx, nox, mu, nz);
-    } else {
-        const cf32* t = static_cast<const cf32*>(P.d_khat);
-        if (contract_threads(mu) == 512)
-            hipLaunchKernelGGL((contract_kernel<false, 512, cf32>), grid, dim3(512), lds, s, t, P.d_fa, P.d_fb, ly, lx, nox, mu, nz);
-        else
-            hipLaunchKernelGGL((contract_kernel<false, 256, cf32>), grid, dim3(256), lds, s, t, P.d_fa, P.d_fb, ly, lx, nox, mu, nz);
-    }
-    UFSS_HIP(hipGetLastError());
-}
+void fft_fwd_contract(const Plan& P, hipStream_t s) { contract<true>(P, s); }
 
 //   Y^[ly][lx][mu] -> U[ly][nx][mu] -> y_raw[ny][nx][mu]
 void fft_fwd_inverse(const Plan& P, hipStream_t s) {
@@ -604,27 +719,7 @@ void fft_adj_transform(const Plan& P, hipStream_t s) {
     twiddle(P.d_fa, P.d_ft, P.d_tw_fy, lx, ly, ny, mu, mu, (int64_t)lx * mu, mu, (int64_t)lx * mu, s);
 }
 
-void fft_adj_contract(const Plan& P, hipStream_t s) {
-    const int lx = P.fft_lx, ly = P.fft_ly, nox = lx / 2 + 1, noy = ly / 2 + 1;
-    const int mu = (int)P.ubins_h.size();
-    const int nz = P.g.nz;
-    const size_t lds = contract_lds(nz, mu);
-    const dim3 grid(noy * nox);
-    if (P.dtype == UFSS_BF16) {
-        const cbf16* t = static_cast<const cbf16*>(P.d_khat_t);
-        if (contract_threads(nz) == 512)
-            hipLaunchKernelGGL((contract_kernel<true, 512, cbf16>), grid, dim3(512), lds, s, t, P.d_fa, P.d_fb, ly, lx, nox, nz, mu);
-        else
-            hipLaunchKernelGGL((contract_kernel<true, 256, cbf16>), grid, dim3(256), lds, s, t, P.d_fa, P.d_fb, ly, lx, nox, nz, mu);
-    } else {
-        const cf32* t = static_cast<const cf32*>(P.d_khat_t);
-        if (contract_threads(nz) == 512)
-            hipLaunchKernelGGL((contract_kernel<true, 512, cf32>), grid, dim3(512), lds, s, t, P.d_fa, P.d_fb, ly, lx, nox, nz, mu);
-        else
-            hipLaunchKernelGGL((contract_kernel<true, 256, cf32>), grid, dim3(256), lds, s, t, P.d_fa, P.d_fb, ly, lx, nox, nz, mu);
-    }
-    UFSS_HIP(hipGetLastError());
-}
+void fft_adj_contract(const Plan& P, hipStream_t s) { contract<false>(P, s); }
 
 void fft_adj_inverse(const Plan& P, cf32* out, hipStream_t s) {
     const int nx = P.g.nx, ny = P.g.ny, nz = P.g.nz, lx = P.fft_lx, ly = P.fft_ly;

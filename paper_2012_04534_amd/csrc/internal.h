@@ -116,11 +116,13 @@ struct Plan {
     // [1 or npos][nt]
     int mix = 0, mix_per_sign = 0;
     void* d_xih = nullptr;
-    // transform path (UFSS_ALGO_FFT): sizes, K^ quadrant [ly/2+1][lx/2+1][nz][mu],
+    // transform path (UFSS_ALGO_FFT): sizes, K^ [entries][nz][mus],
     // twiddle tables and three work buffers
     int fft_lx = 0, fft_ly = 0;
     void* d_khat = nullptr;
-    void* d_khat_t = nullptr;      // the same, transposed per entry: [..][mu][nz]
+    int fft_swap = 0;              // both axes alike: entries oy <= ox only
+    int fft_mus = 0, fft_entries = 0;   // row stride of the table (even), stored entries
+    int2* d_orb = nullptr;         // their (oy, ox)
     cf32 *d_tw_fx = nullptr, *d_tw_fy = nullptr, *d_tw_ix = nullptr, *d_tw_iy = nullptr;
     cf32 *d_fa = nullptr, *d_fb = nullptr, *d_ft = nullptr;
     // device workspace

@@ -1,0 +1,61 @@
+"""GPU parity of the transform operator's kernels with the dense FP64 oracle at
+the sizes where their splits change: equal axes (half the table) and unequal
+ones, 1 to 130 bins (odd counts, one to five blocks of outputs), depths around
+a tile and past one staged run of the reduction (512)."""
+import numpy as np
+import pytest
+
+from oracle import operator as O
+from paper_2012_04534_amd import workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+TOL32 = 1e-5     # the FP32 operator's bound, norm-wise and element-wise
+TOL16 = 1e-2     # a table rounded once to BF16
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch.device("cuda:0")
+
+
+def errs(got, ref):
+    return max(np.linalg.norm(got - ref) / np.linalg.norm(ref), np.abs(got - ref).max() / np.abs(ref).max())
+
+
+def check(plan, A, g, m, tol, dev):
+    from paper_2012_04534_amd import ufss as u
+    ny, nx, nz = g["ny"], g["nx"], g["nz"]
+    x = W.cn((ny, nx, nz), 21).astype(np.complex64)
+    r = W.cn((ny, nx, m), 22).astype(np.complex64)
+    yo = torch.empty((ny, nx, m), dtype=torch.complex64, device=dev)
+    xo = torch.empty((ny, nx, nz), dtype=torch.complex64, device=dev)
+    u.ufss_forward(plan, torch.from_numpy(x).to(dev), yo)
+    u.ufss_adjoint(plan, torch.from_numpy(r).to(dev), xo)
+    assert errs(yo.cpu().numpy().reshape(-1), A @ x.reshape(-1).astype(np.complex128)) < tol
+    assert errs(xo.cpu().numpy().reshape(-1), A.conj().T @ r.reshape(-1).astype(np.complex128)) < tol
+    plan.close()
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("nx,ny,nz,m,win,beam", [
+    (6, 6, 600, 3, -1, False),      # equal axes, reduction past 512 depths
+    (6, 5, 513, 2, 2, False),       # unequal axes, the same
+    (7, 7, 17, 1, -1, True),        # one bin
+    (4, 4, 20, 130, -1, False),     # five blocks of bins, the adjoint reduction over 130
+    (5, 5, 16, 97, 1, False),       # one bin past three blocks
+    (5, 4, 65, 33, -1, False),      # one bin past a block, one depth past four tiles
+    (3, 3, 129, 64, 0, False),      # zero window (transform length = grid)
+    (1, 1, 12, 3, -1, False),       # one position
+])
+def test_transform_paths(nx, ny, nz, m, win, beam, bf16, dev):
+    from paper_2012_04534_amd import ufss as u
+    g = W.geometry(nx, ny, nz, 1024, win_x=win, win_y=win)
+    if beam:
+        g["theta"] = float(np.radians(25.0))
+    bins, _ = u.ufss_select_freqs(g, m, False, 3 + m)
+    plan = u.Plan(g, m, False, bins, dtype=u.BF16 if bf16 else u.F32, algo=u.ALGO_FFT)
+    check(plan, O.dense_A(g, bins), g, m, TOL16 if bf16 else TOL32, dev)
