@@ -28,196 +28,144 @@
 
 namespace ufss {
 
-static constexpr int kTwT = 256;   // threads of the twiddle products (channels)
-
-// out[b][i][c] = sum_j W[i][j] in[b][j][c]  (complex, FP32; c contiguous).  TI
-// outputs per thread along the transformed axis; the launch picks TI so the
-// product has enough threads to cover the chip.  The walk over j loads kTwJ
-// inputs before using them, so that many loads are in flight per thread; the
-// twiddle rows in LDS are padded with zeros to a multiple of kTwJ.
-static constexpr int kTwJ = 8;
-
-__host__ __device__ static inline int tw_stride(int J) { return (J + kTwJ - 1) / kTwJ * kTwJ; }
-
-template <int TI>
-__global__ __launch_bounds__(kTwT) void twiddle_kernel(cf32* __restrict__ out,
-                                                      const cf32* __restrict__ in,
-                                                      const cf32* __restrict__ W, int I, int J,
-                                                      int C, int64_t sib, int64_t sij,
-                                                      int64_t sob, int64_t soi) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    cf32* wl = reinterpret_cast<cf32*>(smem);          // [TI][Jp]
-    const int Jp = tw_stride(J);
-    const int c = blockIdx.x * kTwT + threadIdx.x;
-    const int i0 = blockIdx.y * TI;
-    const int b = blockIdx.z;
-    for (int t = threadIdx.x; t < TI * Jp; t += kTwT) {
-        const int ii = t / Jp, j = t - ii * Jp;
-        wl[t] = (i0 + ii < I && j < J) ? W[(int64_t)(i0 + ii) * J + j] : cf32{0.f, 0.f};
-    }
-    __syncthreads();
-    if (c >= C) return;
-    float ar[TI], ai[TI];
-#pragma unroll
-    for (int ii = 0; ii < TI; ++ii) ar[ii] = ai[ii] = 0.f;
-    const cf32* src = in + (int64_t)b * sib + c;
-    for (int j0 = 0; j0 < J; j0 += kTwJ) {
-        cf32 v[kTwJ];
-#pragma unroll
-        for (int t = 0; t < kTwJ; ++t)
-            v[t] = (j0 + t < J) ? src[(int64_t)(j0 + t) * sij] : cf32{0.f, 0.f};
-#pragma unroll
-        for (int t = 0; t < kTwJ; ++t) {
-#pragma unroll
-            for (int ii = 0; ii < TI; ++ii) {
-                // four FMAs per complex product (no separate multiplies and adds)
-                const cf32 w = wl[ii * Jp + j0 + t];
-                ar[ii] = fmaf(w.re, v[t].re, ar[ii]);
-                ar[ii] = fmaf(-w.im, v[t].im, ar[ii]);
-                ai[ii] = fmaf(w.re, v[t].im, ai[ii]);
-                ai[ii] = fmaf(w.im, v[t].re, ai[ii]);
-            }
-        }
-    }
-    cf32* dst = out + (int64_t)b * sob + c;
-#pragma unroll
-    for (int ii = 0; ii < TI; ++ii)
-        if (i0 + ii < I) dst[(int64_t)(i0 + ii) * soi] = cf32{ar[ii], ai[ii]};
-}
-
-// The same product on the FP32 matrix cores (v_mfma_f32_16x16x4f32: rows i,
-// columns c, reduction over j four at a time; four real products per complex
-// one, the imaginary part of W negated for the real accumulator).  A workgroup
-// is 4 waves on 4 consecutive 16-column tiles of one b and one block of 16 NI
-// rows.  The plan keeps each twiddle table also in operand order,
-//   Wop[(T ks + s) 64 + lane] = W[16 T + lane % 16][4 s + lane / 16]
-// (row tile T, reduction step s, ks = ceil(J / 4) steps, zero outside I x J),
-// so a block's tiles are one contiguous range: it is copied to LDS with 16-byte
-// loads and each lane then reads 8 contiguous bytes per operand.  Each lane
-// streams its column of the input kTmPK reduction steps ahead.
+// Lateral products on the FP32 matrix cores (v_mfma_f32_16x16x4f32: rows i,
+// columns c of contiguous channels, reduction over j four at a time), in the
+// real tables cos(2 pi i j / L) and sin(2 pi i j / L) with the index mirrored
+// about L folded away: with C = sum_j cos v_j and S = sum_j sin v_j
+//   forward (v on the grid, j < n):   out[i] = C - j S, out[L - i] = C + j S,
+//     rows i <= L / 2 only;
+//   inverse (v over the L indices, folded to j <= L / 2 as E = v_j + v_{L-j}
+//     and O = v_j - v_{L-j}):         out[p] = sum_j cos E_j + j sin O_j, / L.
+// Either way half the products of the complex table (64 x 64 x 512: the depth
+// transforms of an apply pair 25 + 29 + 30 + 24 us with it, 18 + 20 + 21 + 17 us
+// so; 50 x 50 with 256 bins 32 + 14 + 16 + 37 -> 18 + 10 + 10 + 16 us).
+//
+// What bounds it: on a small scan the latency of one pass (so the loads of a
+// wave's column are issued before the tables are staged, kTwPK steps ahead, and
+// a wave takes few row tiles), on a large one the traffic of its operands.
+// A workgroup is 4 waves on 4 consecutive (b, 16-channel) columns and one block
+// of NI row tiles.  The plan keeps each table in operand order,
+//   tab[(T ks + s) 64 + lane] = (cos, sin) at row 16 T + lane % 16, j = 4 s + lane / 16
+// (row tile T, reduction step s of ks, zero outside the table), staged in LDS
+// kTwKS steps at a time: each lane then reads 8 contiguous bytes per operand.
 typedef float f4v __attribute__((ext_vector_type(4)));
-static constexpr int kTmMaxNI = 8;
-static constexpr int kTmPK = 4;
-static constexpr size_t kTmLds = 64 * 1024;   // bytes of staged twiddles per workgroup
+static constexpr int kTwPK = 8;
+static constexpr int kTwKS = 16;
+static constexpr int kTwMaxNI = 4;
 
-template <int NI>
-__global__ __launch_bounds__(256) void twiddle_mfma_kernel(cf32* __restrict__ out,
-                                                           const cf32* __restrict__ in,
-                                                           const cf32* __restrict__ Wop, int I, int J,
-                                                           int C, int64_t sib, int64_t sij,
-                                                           int64_t sob, int64_t soi) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    cf32* wl = reinterpret_cast<cf32*>(smem);            // [NI][ks][64]
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int ks = (J + 3) / 4;
-    const int tiles = (I + 15) / 16;
-    const int t0 = blockIdx.y * NI, i0 = 16 * t0;
-    const int b = blockIdx.z;
-    {
-        // this block's tiles: a contiguous run of 32-byte pairs of entries,
-        // zero past the last tile of W
-        const int nvalid = min(NI, tiles - t0) * ks * 32;   // 16-byte units present
-        const int nall = NI * ks * 32;
-        const float4* src4 = reinterpret_cast<const float4*>(Wop + (int64_t)t0 * ks * 64);
-        float4* dst4 = reinterpret_cast<float4*>(wl);
-        for (int t = threadIdx.x; t < nall; t += 256)
-            dst4[t] = t < nvalid ? src4[t] : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-    __syncthreads();
-    const int c0 = (blockIdx.x * 4 + wave) * 16;
-    if (c0 >= C) return;                                  // wave-uniform
-    const int c = c0 + (lane & 15), kq = lane >> 4;
-    const bool cok = c < C;
-    const cf32* src = in + (int64_t)b * sib + (cok ? c : 0);
-    f4v ar[NI], ai[NI];
-#pragma unroll
-    for (int t = 0; t < NI; ++t) ar[t] = ai[t] = f4v{0.f, 0.f, 0.f, 0.f};
-    cf32 cur[kTmPK];
-#pragma unroll
-    for (int p = 0; p < kTmPK; ++p) {
-        const int j = 4 * p + kq;
-        cur[p] = (cok && j < J) ? src[(int64_t)j * sij] : cf32{0.f, 0.f};
-    }
-    for (int s0 = 0; s0 < ks; s0 += kTmPK) {
-        cf32 nxt[kTmPK];
-#pragma unroll
-        for (int p = 0; p < kTmPK; ++p) {
-            const int j = 4 * (s0 + kTmPK + p) + kq;
-            nxt[p] = (cok && j < J) ? src[(int64_t)j * sij] : cf32{0.f, 0.f};
+template <int NI, bool INV>
+__global__ __launch_bounds__(256) void twiddle_kernel(cf32* __restrict__ out, const cf32* __restrict__ in,
+                                                      const cf32* __restrict__ tab, int L, int n, int ks, int tiles,
+                                                      int units, int nct, int C, int64_t sib, int64_t sij,
+                                                      int64_t sob, int64_t soi) {
+    __shared__ __align__(16) cf32 wl[NI * kTwKS * 64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int unit = blockIdx.x * 4 + wave, b = unit / nct;
+    const int c = (unit - b * nct) * 16 + (lane & 15), kq = lane >> 4;
+    const bool active = unit < units, ok = active && c < C;
+    const int t0 = blockIdx.y * NI;
+    const int J = INV ? L / 2 + 1 : n;                    // reduction length
+    const cf32* src = in + (int64_t)b * sib + c;
+    // this lane's column at reduction step s (INV: folded into E and O)
+    struct Col { cf32 e, o; };
+    auto fetch = [&](int s) {
+        Col v{{0.f, 0.f}, {0.f, 0.f}};
+        const int j = 4 * s + kq;
+        if (ok && j < J) {
+            v.e = src[(int64_t)j * sij];
+            if (INV && j > 0 && 2 * j < L) v.o = src[(int64_t)(L - j) * sij];
         }
+        return v;
+    };
+    Col cur[kTwPK];
 #pragma unroll
-        for (int p = 0; p < kTmPK; ++p) {
-            const int st = s0 + p;
-            if (st >= ks) break;                          // wave-uniform
-            const cf32 bv = cur[p];
+    for (int p = 0; p < kTwPK; ++p) cur[p] = fetch(p);
+    // forward: C and S (real, imaginary); inverse: the output's real and imaginary part
+    constexpr int NA = INV ? 2 : 4;
+    f4v acc[NI][NA];
 #pragma unroll
-            for (int t = 0; t < NI; ++t) {
-                const cf32 a = wl[(t * ks + st) * 64 + lane];
-                ar[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.re, bv.re, ar[t], 0, 0, 0);
-                ar[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(-a.im, bv.im, ar[t], 0, 0, 0);
-                ai[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.re, bv.im, ai[t], 0, 0, 0);
-                ai[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.im, bv.re, ai[t], 0, 0, 0);
+    for (int t = 0; t < NI; ++t)
+#pragma unroll
+        for (int q = 0; q < NA; ++q) acc[t][q] = f4v{0.f, 0.f, 0.f, 0.f};
+    for (int k0 = 0; k0 < ks; k0 += kTwKS) {
+        const int kn = min(kTwKS, ks - k0);
+        if (k0 > 0) __syncthreads();
+        for (int t = 0; t < NI; ++t) {
+            float4* dst4 = reinterpret_cast<float4*>(wl + t * kTwKS * 64);
+            const float4* src4 = reinterpret_cast<const float4*>(tab + ((int64_t)(t0 + t) * ks + k0) * 64);
+            for (int q = threadIdx.x; q < kn * 32; q += 256)
+                dst4[q] = t0 + t < tiles ? src4[q] : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        __syncthreads();
+        if (!active) continue;
+        for (int s0 = 0; s0 < kn; s0 += kTwPK) {
+#pragma unroll
+            for (int p = 0; p < kTwPK; ++p) {
+                const int st = s0 + p;
+                if (st >= kn) break;                      // wave-uniform
+                const Col v = cur[p];
+                cur[p] = fetch(k0 + st + kTwPK);
+                float er = v.e.re, ei = v.e.im, orr = 0.f, oi = 0.f;
+                if constexpr (INV) {
+                    // an unmirrored index (0, L / 2) has sin = 0: its O is not used
+                    er += v.o.re;
+                    ei += v.o.im;
+                    orr = v.e.re - v.o.re;
+                    oi = v.o.im - v.e.im;                 // -O.im
+                }
+#pragma unroll
+                for (int t = 0; t < NI; ++t) {
+                    const cf32 w = wl[(t * kTwKS + st) * 64 + lane];   // (cos, sin)
+                    if constexpr (INV) {
+                        acc[t][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.re, er, acc[t][0], 0, 0, 0);
+                        acc[t][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.re, ei, acc[t][1], 0, 0, 0);
+                        acc[t][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.im, oi, acc[t][0], 0, 0, 0);
+                        acc[t][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.im, orr, acc[t][1], 0, 0, 0);
+                    } else {
+                        acc[t][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.re, er, acc[t][0], 0, 0, 0);
+                        acc[t][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.re, ei, acc[t][1], 0, 0, 0);
+                        acc[t][2] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.im, er, acc[t][2], 0, 0, 0);
+                        acc[t][3] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.im, ei, acc[t][3], 0, 0, 0);
+                    }
+                }
             }
         }
-#pragma unroll
-        for (int p = 0; p < kTmPK; ++p) cur[p] = nxt[p];
     }
-    if (!cok) return;
+    if (!ok) return;
     cf32* dst = out + (int64_t)b * sob + c;
 #pragma unroll
     for (int t = 0; t < NI; ++t)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int i = i0 + 16 * t + 4 * kq + r;
-            if (i < I) dst[(int64_t)i * soi] = cf32{ar[t][r], ai[t][r]};
+            const int i = 16 * (t0 + t) + 4 * kq + r;
+            if constexpr (INV) {
+                if (i < n) dst[(int64_t)i * soi] = cf32{acc[t][0][r], acc[t][1][r]};
+            } else {
+                const float cr = acc[t][0][r], ci = acc[t][1][r], sr = acc[t][2][r], si = acc[t][3][r];
+                if (2 * i <= L) dst[(int64_t)i * soi] = cf32{cr + si, ci - sr};
+                if (i > 0 && 2 * i < L) dst[(int64_t)(L - i) * soi] = cf32{cr - si, ci + sr};
+            }
         }
 }
 
-// Row tiles per wave for the matrix-core product: enough to cover I (at most
-// kTmMaxNI), no more than the LDS budget holds; 0 when not even one fits.
-static int tm_tiles(int I, int J) {
-    const int ks = (J + 3) / 4;
-    const int by_lds = (int)(kTmLds / ((size_t)ks * 64 * sizeof(cf32)));
-    return std::min(std::min(kTmMaxNI, (I + 15) / 16), by_lds);
-}
-
-static void twiddle(cf32* out, const cf32* in, const cf32* W, int B, int I, int J, int C,
-                    int64_t sib, int64_t sij, int64_t sob, int64_t soi, hipStream_t s) {
-    // row tiles per wave: as many as fit, then fewer (more waves, each input
-    // column read by more of them) while the launch has under 2048 waves
-    int ni = tm_tiles(I, J);
-    {
-        const int64_t tiles = (I + 15) / 16, col_waves = (int64_t)((C + 15) / 16) * B;
-        while (ni > 1 && col_waves * ((tiles + ni - 1) / ni) < 2048) --ni;
-    }
-    if (ni >= 1) {
-        const dim3 grid((C + 63) / 64, (I + 16 * ni - 1) / (16 * ni), B);
-        const size_t lds = (size_t)((J + 3) / 4) * ni * 64 * sizeof(cf32);
-        const cf32* Wop = W + (((int64_t)I * J + 1) & ~(int64_t)1);   // operand-order copy (16-byte aligned)
-#define UFSS_TM(T) hipLaunchKernelGGL(twiddle_mfma_kernel<T>, grid, dim3(256), lds, s, out, in, Wop, I, J, C, sib, sij, sob, soi)
-        switch (ni) {
-            case 1: UFSS_TM(1); break;
-            case 2: UFSS_TM(2); break;
-            case 3: UFSS_TM(3); break;
-            case 4: UFSS_TM(4); break;
-            case 5: UFSS_TM(5); break;
-            case 6: UFSS_TM(6); break;
-            case 7: UFSS_TM(7); break;
-            default: UFSS_TM(8); break;
-        }
-#undef UFSS_TM
-        UFSS_HIP(hipGetLastError());
-        return;
-    }
-    // vector-ALU product for twiddle blocks too large for LDS
-    // outputs per thread: as many as keep at least ~64K threads in flight
-    const int64_t base = (int64_t)B * C;
-    int ti = 8;
-    while (ti > 1 && base * ((I + ti - 1) / ti) < 65536) ti /= 2;
-    const dim3 grid((C + kTwT - 1) / kTwT, (I + ti - 1) / ti, B);
-    const size_t lds = (size_t)ti * tw_stride(J) * sizeof(cf32);
-#define UFSS_TW(T) hipLaunchKernelGGL(twiddle_kernel<T>, grid, dim3(kTwT), lds, s, out, in, W, I, J, C, sib, sij, sob, soi)
-    if (ti == 8) UFSS_TW(8); else if (ti == 4) UFSS_TW(4); else if (ti == 2) UFSS_TW(2); else UFSS_TW(1);
+// One lateral product over B batches of C channels: forward n -> L indices or
+// inverse L -> n.
+template <bool INV>
+static void twiddle(cf32* out, const cf32* in, const cf32* tab, int B, int L, int n, int C, int64_t sib,
+                    int64_t sij, int64_t sob, int64_t soi, hipStream_t s) {
+    const int rows = INV ? n : L / 2 + 1, J = INV ? L / 2 + 1 : n;
+    const int tiles = (rows + 15) / 16, ks = (J + 3) / 4;
+    const int nct = (C + 15) / 16;
+    const int64_t units = (int64_t)B * nct;
+    // row tiles per wave: as many as the accumulators allow, fewer (more waves,
+    // each input column read by more of them) while the launch has under 2048 waves
+    int ni = std::min(tiles, kTwMaxNI);
+    while (ni > 1 && units * ((tiles + ni - 1) / ni) < 2048) --ni;
+    while (ni > 1 && (tiles + ni - 2) / (ni - 1) == (tiles + ni - 1) / ni) --ni;   // the same rounds with fewer
+    const dim3 grid((unsigned)((units + 3) / 4), (tiles + ni - 1) / ni);
+#define UFSS_TW(T) hipLaunchKernelGGL((twiddle_kernel<T, INV>), grid, dim3(256), 0, s, out, in, tab, L, n, ks, tiles, \
+                                      (int)units, nct, C, sib, sij, sob, soi)
+    if (ni == 1) UFSS_TW(1); else if (ni == 2) UFSS_TW(2); else if (ni == 3) UFSS_TW(3); else UFSS_TW(4);
 #undef UFSS_TW
     UFSS_HIP(hipGetLastError());
 }
@@ -537,14 +485,21 @@ void fft_setup(Plan& P) {
         fail(UFSS_ERR_UNSUPPORTED, "grid too large for the transform path (L <= 1024, nz and bins <= 1536)");
     P.fft_lx = lx;
     P.fft_ly = ly;
-    // twiddle tables (FP64 angles from exact integer products, stored FP32)
-    auto tw = [](int rows, int cols, int L, double sign, double scale) {
-        std::vector<cf32> t((size_t)rows * cols);
-        for (int r = 0; r < rows; ++r)
-            for (int c = 0; c < cols; ++c) {
-                const double a = 2.0 * M_PI * (double)(((int64_t)r * c) % L) / L;
-                t[(size_t)r * cols + c] = cf32{(float)(scale * std::cos(a)), (float)(scale * sign * std::sin(a))};
-            }
+    // twiddle tables (FP64 angles from exact integer products, stored FP32) in
+    // operand order (see twiddle_kernel)
+    auto tw = [](int rows, int cols, int L, double scale) {
+        const int tiles = (rows + 15) / 16, ks = (cols + 3) / 4;
+        std::vector<cf32> t((size_t)tiles * ks * 64, cf32{0.f, 0.f});
+        for (int T = 0; T < tiles; ++T)
+            for (int st = 0; st < ks; ++st)
+                for (int l = 0; l < 64; ++l) {
+                    const int r = 16 * T + (l & 15), c = 4 * st + (l >> 4);
+                    if (r >= rows || c >= cols) continue;
+                    const int64_t k = ((int64_t)r * c) % L;
+                    const double a = 2.0 * M_PI * (double)k / L;
+                    // sin(pi) and sin(0) exactly zero: those indices have no mirror
+                    t[((size_t)T * ks + st) * 64 + l] = cf32{(float)(scale * std::cos(a)), 2 * k % L == 0 ? 0.f : (float)(scale * std::sin(a))};
+                }
         return t;
     };
     auto up = [&](const std::vector<cf32>& h) {
@@ -554,26 +509,10 @@ void fft_setup(Plan& P) {
         P.ws_bytes += h.size() * sizeof(cf32);
         return static_cast<cf32*>(d);
     };
-    // each table [rows][cols] is followed, from the next even entry (16-byte
-    // alignment), by its copy in matrix-core operand order
-    // [ceil(rows/16)][ceil(cols/4)][64] (see twiddle_mfma_kernel)
-    auto with_op = [](std::vector<cf32> t, int rows, int cols) {
-        const int tiles = (rows + 15) / 16, ks = (cols + 3) / 4;
-        const size_t base = (t.size() + 1) & ~(size_t)1;
-        t.resize(base + (size_t)tiles * ks * 64, cf32{0.f, 0.f});
-        for (int T = 0; T < tiles; ++T)
-            for (int st = 0; st < ks; ++st)
-                for (int l = 0; l < 64; ++l) {
-                    const int r = 16 * T + (l & 15), c = 4 * st + (l >> 4);
-                    if (r < rows && c < cols)
-                        t[base + ((size_t)T * ks + st) * 64 + l] = t[(size_t)r * cols + c];
-                }
-        return t;
-    };
-    P.d_tw_fx = up(with_op(tw(lx, nx, lx, -1.0, 1.0), lx, nx));          // [qx][nx]
-    P.d_tw_fy = up(with_op(tw(ly, ny, ly, -1.0, 1.0), ly, ny));          // [qy][ny]
-    P.d_tw_ix = up(with_op(tw(nx, lx, lx, +1.0, 1.0 / lx), nx, lx));     // [px][qx]
-    P.d_tw_iy = up(with_op(tw(ny, ly, ly, +1.0, 1.0 / ly), ny, ly));     // [py][qy]
+    P.d_tw_fx = up(tw(lx / 2 + 1, nx, lx, 1.0));          // [qx][nx]
+    P.d_tw_fy = up(tw(ly / 2 + 1, ny, ly, 1.0));          // [qy][ny]
+    P.d_tw_ix = up(tw(nx, lx / 2 + 1, lx, 1.0 / lx));     // [px][qx]
+    P.d_tw_iy = up(tw(ny, ly / 2 + 1, ly, 1.0 / ly));     // [py][qy]
     const int64_t cmax = std::max(nz, mu);
     const int64_t wbytes = (int64_t)ly * lx * cmax * sizeof(cf32);
     const int64_t tbytes = (int64_t)std::max((int64_t)ny * lx, (int64_t)ly * nx) * cmax * sizeof(cf32);
@@ -697,8 +636,8 @@ static void contract(const Plan& P, hipStream_t s) {
 //   x[ny][nx][nz] -> T[ny][lx][nz] -> X^[ly][lx][nz]
 void fft_fwd_transform(const Plan& P, const cf32* x, hipStream_t s) {
     const int nx = P.g.nx, ny = P.g.ny, nz = P.g.nz, lx = P.fft_lx, ly = P.fft_ly;
-    twiddle(P.d_ft, x, P.d_tw_fx, ny, lx, nx, nz, (int64_t)nx * nz, nz, (int64_t)lx * nz, nz, s);
-    twiddle(P.d_fa, P.d_ft, P.d_tw_fy, lx, ly, ny, nz, nz, (int64_t)lx * nz, nz, (int64_t)lx * nz, s);
+    twiddle<false>(P.d_ft, x, P.d_tw_fx, ny, lx, nx, nz, (int64_t)nx * nz, nz, (int64_t)lx * nz, nz, s);
+    twiddle<false>(P.d_fa, P.d_ft, P.d_tw_fy, lx, ly, ny, nz, nz, (int64_t)lx * nz, nz, (int64_t)lx * nz, s);
 }
 
 //   Y^[q][k] = sum_z K^[q][z][k] X^[q][z]
@@ -707,24 +646,24 @@ void fft_fwd_contract(const Plan& P, hipStream_t s) { contract<true>(P, s); }
 //   Y^[ly][lx][mu] -> U[ly][nx][mu] -> y_raw[ny][nx][mu]
 void fft_fwd_inverse(const Plan& P, hipStream_t s) {
     const int nx = P.g.nx, ny = P.g.ny, lx = P.fft_lx, ly = P.fft_ly, mu = (int)P.ubins_h.size();
-    twiddle(P.d_ft, P.d_fb, P.d_tw_ix, ly, nx, lx, mu, (int64_t)lx * mu, mu, (int64_t)nx * mu, mu, s);
-    twiddle(P.d_yraw, P.d_ft, P.d_tw_iy, nx, ny, ly, mu, mu, (int64_t)nx * mu, mu, (int64_t)nx * mu, s);
+    twiddle<true>(P.d_ft, P.d_fb, P.d_tw_ix, ly, lx, nx, mu, (int64_t)lx * mu, mu, (int64_t)nx * mu, mu, s);
+    twiddle<true>(P.d_yraw, P.d_ft, P.d_tw_iy, nx, ly, ny, mu, mu, (int64_t)nx * mu, mu, (int64_t)nx * mu, s);
 }
 
 // Adjoint, in three steps; the operand is the H-scaled union-bin rows in P.d_rop.
 void fft_adj_transform(const Plan& P, hipStream_t s) {
     const int nx = P.g.nx, ny = P.g.ny, lx = P.fft_lx, ly = P.fft_ly, mu = (int)P.ubins_h.size();
     const cf32* r = static_cast<const cf32*>(P.d_rop);
-    twiddle(P.d_ft, r, P.d_tw_fx, ny, lx, nx, mu, (int64_t)nx * mu, mu, (int64_t)lx * mu, mu, s);
-    twiddle(P.d_fa, P.d_ft, P.d_tw_fy, lx, ly, ny, mu, mu, (int64_t)lx * mu, mu, (int64_t)lx * mu, s);
+    twiddle<false>(P.d_ft, r, P.d_tw_fx, ny, lx, nx, mu, (int64_t)nx * mu, mu, (int64_t)lx * mu, mu, s);
+    twiddle<false>(P.d_fa, P.d_ft, P.d_tw_fy, lx, ly, ny, mu, mu, (int64_t)lx * mu, mu, (int64_t)lx * mu, s);
 }
 
 void fft_adj_contract(const Plan& P, hipStream_t s) { contract<false>(P, s); }
 
 void fft_adj_inverse(const Plan& P, cf32* out, hipStream_t s) {
     const int nx = P.g.nx, ny = P.g.ny, nz = P.g.nz, lx = P.fft_lx, ly = P.fft_ly;
-    twiddle(P.d_ft, P.d_fb, P.d_tw_ix, ly, nx, lx, nz, (int64_t)lx * nz, nz, (int64_t)nx * nz, nz, s);
-    twiddle(out, P.d_ft, P.d_tw_iy, nx, ny, ly, nz, nz, (int64_t)nx * nz, nz, (int64_t)nx * nz, s);
+    twiddle<true>(P.d_ft, P.d_fb, P.d_tw_ix, ly, lx, nx, nz, (int64_t)lx * nz, nz, (int64_t)nx * nz, nz, s);
+    twiddle<true>(out, P.d_ft, P.d_tw_iy, nx, ly, ny, nz, nz, (int64_t)nx * nz, nz, (int64_t)nx * nz, s);
 }
 
 }  // namespace ufss

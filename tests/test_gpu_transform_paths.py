@@ -1,7 +1,8 @@
 """GPU parity of the transform operator's kernels with the dense FP64 oracle at
 the sizes where their splits change: equal axes (half the table) and unequal
 ones, 1 to 130 bins (odd counts, one to five blocks of outputs), depths around
-a tile and past one staged run of the reduction (512)."""
+a tile and past one staged run of the reduction (512), and transform lengths past
+one staged run of the lateral tables (64)."""
 import numpy as np
 import pytest
 
@@ -49,6 +50,8 @@ def check(plan, A, g, m, tol, dev):
     (5, 5, 16, 97, 1, False),       # one bin past three blocks
     (5, 4, 65, 33, -1, False),      # one bin past a block, one depth past four tiles
     (3, 3, 129, 64, 0, False),      # zero window (transform length = grid)
+    (150, 1, 9, 4, -1, False),      # transform length 299: several staged runs of the lateral tables
+    (520, 1, 5, 2, 3, False),       # more than 512 positions on an axis
     (1, 1, 12, 3, -1, False),       # one position
 ])
 def test_transform_paths(nx, ny, nz, m, win, beam, bf16, dev):
