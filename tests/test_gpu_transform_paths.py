@@ -1,11 +1,13 @@
 """GPU parity of the transform operator's kernels with the dense FP64 oracle at
 the sizes where their splits change: equal axes (half the table) and unequal
 ones, 1 to 130 bins (odd counts, one to five blocks of outputs), depths around
-a tile and past one staged run of the reduction (512), and transform lengths past
-one staged run of the lateral tables (64)."""
+a tile and past one staged run of the reduction (512), transform lengths past
+one staged run of the lateral tables (64), and the mixing pass with one to many
+lanes per measurement."""
 import numpy as np
 import pytest
 
+from oracle import mixing as MX
 from oracle import operator as O
 from paper_2012_04534_amd import workloads as W
 
@@ -62,3 +64,13 @@ def test_transform_paths(nx, ny, nz, m, win, beam, bf16, dev):
     bins, _ = u.ufss_select_freqs(g, m, False, 3 + m)
     plan = u.Plan(g, m, False, bins, dtype=u.BF16 if bf16 else u.F32, algo=u.ALGO_FFT)
     check(plan, O.dense_A(g, bins), g, m, TOL16 if bf16 else TOL32, dev)
+
+
+@pytest.mark.parametrize("nt,m", [(32, 1), (64, 3), (64, 32), (128, 128), (32, 16)])
+def test_mixing_lanes_per_measurement(nt, m, dev):
+    from paper_2012_04534_amd import ufss as u
+    g = W.geometry(4, 3, 10, nt)
+    bins = W.uniform_subsets(nt, m, (3, 4), 6)
+    signs = W.rademacher((3, 4, nt), 7)
+    plan = u.Plan(g, m, True, bins, algo=u.ALGO_FFT, signs=signs)
+    check(plan, MX.dense_A_mixed(g, bins, signs), g, m, TOL32, dev)
