@@ -23,6 +23,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "internal.h"
@@ -39,25 +40,58 @@ struct Dims {
 
 static int nblk(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(1024, (n + kLT - 1) / kLT)); }
 
-// Grid coordinates of voxel v, computed once per voxel in 32-bit arithmetic
-// (a network's grid holds fewer than 2^31 voxels).
-struct VoxC {
-    int z, x, y;
+// The convolution kernels give a thread a run of XV columns x at one (y, z):
+// lanes are consecutive depths, so every load is coalesced, the XV + 2 columns
+// of a neighbour row (e_y, e_z) serve the 3 XV products of each weight, and a
+// weight read from LDS serves the whole run.  The channel count is a template
+// constant (accumulators in registers).  What bounds them is the latency of the
+// neighbour loads, a row at a time.  32 x 32 x 256, 8 channels, before (one voxel
+// per thread, run-time channel count) and after: conv1 46 -> 10.6 us, conv2 17 + 5
+// (the extrapolation's own pass) -> 15.9, their transposes 52 -> 13.7 and 17 ->
+// 14.7; rows unrolled by 3 leave too few registers (conv2 23).
+static constexpr int kXC = 2;            // the convolutions: more, shorter runs (4: 14-20 us, latency shows)
+static constexpr int kXW = 4;            // the weight gradients: more products per load (2: 22 us)
+
+struct Run {
+    int z, x, y;            // depth, first column of the run
+    int64_t v;              // its voxel (column x + k: v + k nz)
 };
-__device__ __forceinline__ VoxC vox_coords(const Dims& d, int64_t v) {
-    const int vi = (int)v, t = vi / d.nz;
-    return VoxC{vi - t * d.nz, t % d.nx, t / d.nx};
+template <int XV>
+__host__ __device__ static inline int64_t run_count(const Dims& d) {
+    return (int64_t)d.ny * ((d.nx + XV - 1) / XV) * d.nz;
+}
+// (a network's grid holds fewer than 2^31 voxels: 32-bit arithmetic)
+template <int XV>
+__device__ __forceinline__ Run run_at(const Dims& d, int64_t t) {
+    const int nxr = (d.nx + XV - 1) / XV, c = (int)t / d.nz;
+    Run r;
+    r.z = (int)t - c * d.nz;
+    r.y = c / nxr;
+    r.x = (c - r.y * nxr) * XV;
+    r.v = ((int64_t)r.y * d.nx + r.x) * d.nz + r.z;
+    return r;
 }
 
-// Neighbour w = v + e of voxel v (coordinates p) for offset index e; false
-// outside the grid.  With the offset loops unrolled, e is a constant.
-__device__ __forceinline__ bool nb(const Dims& d, const VoxC& p, int64_t v, int e, int64_t& w) {
-    const int ez = e % 3 - 1, ex = (e / 3) % 3 - 1, ey = e / 9 - 1;
-    if ((unsigned)(p.y + ey) >= (unsigned)d.ny || (unsigned)(p.x + ex) >= (unsigned)d.nx ||
-        (unsigned)(p.z + ez) >= (unsigned)d.nz)
-        return false;
-    w = v + ((int64_t)ey * d.nx + ex) * d.nz + ez;
-    return true;
+// Row (e_y, e_z) = (row / 3 - 1, row % 3 - 1) of the neighbours: whether it is
+// inside the grid, and the offset to it.  Tap e of a row is e_x = e - 1, offset
+// index tap_index(row, e).
+__device__ __forceinline__ bool row_inside(const Dims& d, const Run& r, int row, int64_t& o) {
+    const int ey = row / 3 - 1, ez = row % 3 - 1;
+    o = (int64_t)ey * d.nx * d.nz + ez;
+    return (unsigned)(r.y + ey) < (unsigned)d.ny && (unsigned)(r.z + ez) < (unsigned)d.nz;
+}
+__device__ __forceinline__ int tap_index(int row, int e) { return row / 3 * 9 + 3 * e + row % 3; }
+
+// The row's values at columns x - 1 .. x + N - 2; zero outside the grid.  at(o): the
+// value at voxel r.v + o.
+template <class T, int N, class F>
+__device__ __forceinline__ void row_values(const Dims& d, const Run& r, bool in, int64_t off, F at, T (&v)[N]) {
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const int x = r.x + k - 1;
+        v[k] = T{};
+        if (in && x >= 0 && x < d.nx) v[k] = at(off + (int64_t)(k - 1) * d.nz);
+    }
 }
 
 // --- forward kernels ---------------------------------------------------------
@@ -87,57 +121,112 @@ __global__ __launch_bounds__(kLT) void k_prox(int64_t n, const cf32* __restrict_
     }
 }
 
-// h[co][v] = relu(b1[co] + sum_{c, e} W1[co][c][e] u_c(v + e) / c),  c = lam / L
-__global__ __launch_bounds__(kLT) void k_conv1(Dims d, int ch, const cf32* __restrict__ u,
-                                               const float* __restrict__ W1, const float* __restrict__ b1,
-                                               const double* __restrict__ lam, float invL,
-                                               float* __restrict__ h) {
-    const float ic = 1.0f / ((float)lam[0] * invL);
-    __shared__ float w[kMaxCh * 54 + kMaxCh];
-    for (int t = threadIdx.x; t < ch * 54; t += kLT) w[t] = W1[t];
-    for (int t = threadIdx.x; t < ch; t += kLT) w[ch * 54 + t] = b1[t];
-    __syncthreads();
-    const float* uf = reinterpret_cast<const float*>(u);
-    for (int64_t v = (int64_t)blockIdx.x * kLT + threadIdx.x; v < d.n; v += (int64_t)gridDim.x * kLT) {
-        float acc[kMaxCh];
-        for (int o = 0; o < ch; ++o) acc[o] = w[ch * 54 + o];
-        const VoxC pc = vox_coords(d, v);
-#pragma unroll
-        for (int e = 0; e < 27; ++e) {
-            int64_t q;
-            if (!nb(d, pc, v, e, q)) continue;
-            const float ur = uf[2 * q] * ic, ui = uf[2 * q + 1] * ic;
-            for (int o = 0; o < ch; ++o) acc[o] += w[o * 54 + e] * ur + w[o * 54 + 27 + e] * ui;
-        }
-        for (int o = 0; o < ch; ++o) h[(int64_t)o * d.n + v] = fmaxf(acc[o], 0.f);
+// Weights in LDS: w[(row * 3 + tap) * CH + channel] = the pair for (Re, Im).
+// src(o, c, e): the weight of channel `o` and part c at offset index e.
+template <int CH, class F>
+__device__ __forceinline__ void stage_weights(float2* w, F src) {
+    for (int t = threadIdx.x; t < 27 * CH; t += kLT) {
+        const int i = t / CH, o = t - i * CH, e = tap_index(i / 3, i % 3);
+        w[t] = make_float2(src(o, 0, e), src(o, 1, e));
     }
 }
 
-// xout = u + c (b2 + sum_{c, e} W2[o][c][e] h_c(v + e)) as complex (o = re, im)
-__global__ __launch_bounds__(kLT) void k_conv2(Dims d, int ch, const float* __restrict__ h,
+// h[co][v] = relu(b1[co] + sum_{c, e} W1[co][c][e] u_c(v + e) / c),  c = lam / L
+template <int CH>
+__global__ __launch_bounds__(kLT) void k_conv1(Dims d, const cf32* __restrict__ u,
+                                               const float* __restrict__ W1, const float* __restrict__ b1,
+                                               const double* __restrict__ lam, float invL,
+                                               float* __restrict__ h) {
+    __shared__ __align__(16) float2 w[27 * CH];
+    const float ic = 1.0f / ((float)lam[0] * invL);
+    stage_weights<CH>(w, [&](int o, int c, int e) { return W1[o * 54 + c * 27 + e]; });
+    __syncthreads();
+    const int64_t n = run_count<kXC>(d), nz = d.nz;
+    for (int64_t t = (int64_t)blockIdx.x * kLT + threadIdx.x; t < n; t += (int64_t)gridDim.x * kLT) {
+        const Run r = run_at<kXC>(d, t);
+        float acc[kXC][CH];
+#pragma unroll
+        for (int k = 0; k < kXC; ++k)
+#pragma unroll
+            for (int o = 0; o < CH; ++o) acc[k][o] = b1[o];
+#pragma unroll 1
+        for (int row = 0; row < 9; ++row) {
+            int64_t off;
+            const bool in = row_inside(d, r, row, off);
+            cf32 v[kXC + 2];
+            row_values(d, r, in, off, [&](int64_t at) { return u[r.v + at]; }, v);
+#pragma unroll
+            for (int k = 0; k < kXC + 2; ++k) v[k] = cf32{v[k].re * ic, v[k].im * ic};
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+#pragma unroll
+                for (int o = 0; o < CH; ++o) {
+                    const float2 a = w[(row * 3 + e) * CH + o];
+#pragma unroll
+                    for (int k = 0; k < kXC; ++k) acc[k][o] += a.x * v[k + e].re + a.y * v[k + e].im;
+                }
+        }
+#pragma unroll
+        for (int o = 0; o < CH; ++o)
+#pragma unroll
+            for (int k = 0; k < kXC; ++k)
+                if (r.x + k < d.nx) h[(int64_t)o * d.n + r.v + k * nz] = fmaxf(acc[k][o], 0.f);
+    }
+}
+
+// xout = u + c (b2 + sum_{c, e} W2[o][c][e] h_c(v + e)) as complex (o = re, im), and,
+// with gam, the next stage's extrapolation gam = xout + beta (xout - xcur) in the
+// same pass.
+template <int CH>
+__global__ __launch_bounds__(kLT) void k_conv2(Dims d, const float* __restrict__ h,
                                                const float* __restrict__ W2, const float* __restrict__ b2,
                                                const double* __restrict__ lam, float invL,
-                                               const cf32* __restrict__ u, cf32* __restrict__ xout) {
+                                               const cf32* __restrict__ u, cf32* __restrict__ xout,
+                                               const cf32* __restrict__ xcur, float beta, cf32* __restrict__ gam) {
+    __shared__ __align__(16) float2 w[27 * CH];
     const float cs = (float)lam[0] * invL;
-    __shared__ float w[2 * kMaxCh * 27 + 2];
-    for (int t = threadIdx.x; t < 2 * ch * 27; t += kLT) w[t] = W2[t];
-    if (threadIdx.x < 2) w[2 * ch * 27 + threadIdx.x] = b2[threadIdx.x];
+    stage_weights<CH>(w, [&](int c, int o, int e) { return W2[(o * CH + c) * 27 + e]; });
     __syncthreads();
-    for (int64_t v = (int64_t)blockIdx.x * kLT + threadIdx.x; v < d.n; v += (int64_t)gridDim.x * kLT) {
-        float ar = w[2 * ch * 27], ai = w[2 * ch * 27 + 1];
-        const VoxC pc = vox_coords(d, v);
+    const int64_t n = run_count<kXC>(d), nz = d.nz;
+    for (int64_t t = (int64_t)blockIdx.x * kLT + threadIdx.x; t < n; t += (int64_t)gridDim.x * kLT) {
+        const Run r = run_at<kXC>(d, t);
+        float ar[kXC], ai[kXC];
 #pragma unroll
-        for (int e = 0; e < 27; ++e) {
-            int64_t q;
-            if (!nb(d, pc, v, e, q)) continue;
-            for (int c = 0; c < ch; ++c) {
-                const float hv = h[(int64_t)c * d.n + q];
-                ar += w[c * 27 + e] * hv;
-                ai += w[(ch + c) * 27 + e] * hv;
+        for (int k = 0; k < kXC; ++k) {
+            ar[k] = b2[0];
+            ai[k] = b2[1];
+        }
+#pragma unroll 1
+        for (int row = 0; row < 9; ++row) {
+            int64_t off;
+            const bool in = row_inside(d, r, row, off);
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                float v[kXC + 2];
+                row_values(d, r, in, off, [&](int64_t at) { return h[(int64_t)c * d.n + r.v + at]; }, v);
+#pragma unroll
+                for (int e = 0; e < 3; ++e) {
+                    const float2 a = w[(row * 3 + e) * CH + c];
+#pragma unroll
+                    for (int k = 0; k < kXC; ++k) {
+                        ar[k] += a.x * v[k + e];
+                        ai[k] += a.y * v[k + e];
+                    }
+                }
             }
         }
-        const cf32 uu = u[v];
-        xout[v] = cf32{uu.re + cs * ar, uu.im + cs * ai};
+#pragma unroll
+        for (int k = 0; k < kXC; ++k) {
+            if (r.x + k >= d.nx) break;
+            const int64_t v = r.v + k * nz;
+            const cf32 uu = u[v];
+            const cf32 x{uu.re + cs * ar[k], uu.im + cs * ai[k]};
+            xout[v] = x;
+            if (gam) {
+                const cf32 b = xcur[v];
+                gam[v] = cf32{x.re + beta * (x.re - b.re), x.im + beta * (x.im - b.im)};
+            }
+        }
     }
 }
 
@@ -164,112 +253,199 @@ __global__ __launch_bounds__(kLT) void k_loss_grad(int64_t n, const cf32* __rest
 }
 
 // dh[c][v] = (h[c][v] > 0) * sum_{o, e} W2[o][c][e] dx_o(v - e)
-__global__ __launch_bounds__(kLT) void k_conv2_bwd(Dims d, int ch, const cf32* __restrict__ dx,
+template <int CH>
+__global__ __launch_bounds__(kLT) void k_conv2_bwd(Dims d, const cf32* __restrict__ dx,
                                                    const float* __restrict__ W2, const float* __restrict__ h,
                                                    float* __restrict__ dh) {
-    __shared__ float w[2 * kMaxCh * 27];
-    for (int t = threadIdx.x; t < 2 * ch * 27; t += kLT) w[t] = W2[t];
+    __shared__ __align__(16) float2 w[27 * CH];
+    stage_weights<CH>(w, [&](int c, int o, int e) { return W2[(o * CH + c) * 27 + 26 - e]; });   // mirrored: v - e
     __syncthreads();
-    for (int64_t v = (int64_t)blockIdx.x * kLT + threadIdx.x; v < d.n; v += (int64_t)gridDim.x * kLT) {
-        float acc[kMaxCh];
-        for (int c = 0; c < ch; ++c) acc[c] = 0.f;
-        const VoxC pc = vox_coords(d, v);
+    const int64_t n = run_count<kXC>(d), nz = d.nz;
+    for (int64_t t = (int64_t)blockIdx.x * kLT + threadIdx.x; t < n; t += (int64_t)gridDim.x * kLT) {
+        const Run r = run_at<kXC>(d, t);
+        float acc[kXC][CH];
 #pragma unroll
-        for (int e = 0; e < 27; ++e) {
-            int64_t q;
-            if (!nb(d, pc, v, 26 - e, q)) continue;     // v - e
-            const cf32 g = dx[q];
-            for (int c = 0; c < ch; ++c) acc[c] += w[c * 27 + e] * g.re + w[(ch + c) * 27 + e] * g.im;
+        for (int k = 0; k < kXC; ++k)
+#pragma unroll
+            for (int c = 0; c < CH; ++c) acc[k][c] = 0.f;
+#pragma unroll 1
+        for (int row = 0; row < 9; ++row) {
+            int64_t off;
+            const bool in = row_inside(d, r, row, off);
+            cf32 v[kXC + 2];
+            row_values(d, r, in, off, [&](int64_t at) { return dx[r.v + at]; }, v);
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+#pragma unroll
+                for (int c = 0; c < CH; ++c) {
+                    const float2 a = w[(row * 3 + e) * CH + c];
+#pragma unroll
+                    for (int k = 0; k < kXC; ++k) acc[k][c] += a.x * v[k + e].re + a.y * v[k + e].im;
+                }
         }
-        for (int c = 0; c < ch; ++c)
-            dh[(int64_t)c * d.n + v] = h[(int64_t)c * d.n + v] > 0.f ? acc[c] : 0.f;
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+#pragma unroll
+            for (int k = 0; k < kXC; ++k)
+                if (r.x + k < d.nx) {
+                    const int64_t o = (int64_t)c * d.n + r.v + k * nz;
+                    dh[o] = h[o] > 0.f ? acc[k][c] : 0.f;
+                }
     }
 }
 
 // du = dx + sum_{o, e} W1[o][c][e] dh_o(v - e)
-__global__ __launch_bounds__(kLT) void k_conv1_bwd(Dims d, int ch, const float* __restrict__ dh,
+template <int CH>
+__global__ __launch_bounds__(kLT) void k_conv1_bwd(Dims d, const float* __restrict__ dh,
                                                    const float* __restrict__ W1, const cf32* __restrict__ dx,
                                                    cf32* __restrict__ du) {
-    __shared__ float w[kMaxCh * 54];
-    for (int t = threadIdx.x; t < ch * 54; t += kLT) w[t] = W1[t];
+    __shared__ __align__(16) float2 w[27 * CH];
+    stage_weights<CH>(w, [&](int o, int c, int e) { return W1[o * 54 + c * 27 + 26 - e]; });     // mirrored: v - e
     __syncthreads();
-    for (int64_t v = (int64_t)blockIdx.x * kLT + threadIdx.x; v < d.n; v += (int64_t)gridDim.x * kLT) {
-        float ar = 0.f, ai = 0.f;
-        const VoxC pc = vox_coords(d, v);
+    const int64_t n = run_count<kXC>(d), nz = d.nz;
+    for (int64_t t = (int64_t)blockIdx.x * kLT + threadIdx.x; t < n; t += (int64_t)gridDim.x * kLT) {
+        const Run r = run_at<kXC>(d, t);
+        float ar[kXC], ai[kXC];
 #pragma unroll
-        for (int e = 0; e < 27; ++e) {
-            int64_t q;
-            if (!nb(d, pc, v, 26 - e, q)) continue;
-            for (int o = 0; o < ch; ++o) {
-                const float gv = dh[(int64_t)o * d.n + q];
-                ar += w[o * 54 + e] * gv;
-                ai += w[o * 54 + 27 + e] * gv;
+        for (int k = 0; k < kXC; ++k) ar[k] = ai[k] = 0.f;
+#pragma unroll 1
+        for (int row = 0; row < 9; ++row) {
+            int64_t off;
+            const bool in = row_inside(d, r, row, off);
+#pragma unroll
+            for (int o = 0; o < CH; ++o) {
+                float v[kXC + 2];
+                row_values(d, r, in, off, [&](int64_t at) { return dh[(int64_t)o * d.n + r.v + at]; }, v);
+#pragma unroll
+                for (int e = 0; e < 3; ++e) {
+                    const float2 a = w[(row * 3 + e) * CH + o];
+#pragma unroll
+                    for (int k = 0; k < kXC; ++k) {
+                        ar[k] += a.x * v[k + e];
+                        ai[k] += a.y * v[k + e];
+                    }
+                }
             }
         }
-        const cf32 g = dx[v];
-        du[v] = cf32{g.re + ar, g.im + ai};
+#pragma unroll
+        for (int k = 0; k < kXC; ++k)
+            if (r.x + k < d.nx) {
+                const cf32 g = dx[r.v + k * nz];
+                du[r.v + k * nz] = cf32{g.re + ar[k], g.im + ai[k]};
+            }
     }
 }
 
-// Weight-gradient partials: block (r, oc) with oc = o * cin + c sums, over its
-// voxel range r, dout_o(v) in_c(v + e) for the 27 offsets e and dout_o(v) (slot
-// 27, the bias), into part[(oc * nsplit + r) * 28 + slot] in FP64.
-// Channel accessors: value = base[c * cstride + v * vstride].
-__global__ __launch_bounds__(kLT) void k_wgrad(Dims d, const float* __restrict__ dout, int64_t ocs,
-                                               int ovs, const float* __restrict__ in, int64_t ics,
-                                               int ivs, int cin, int nsplit, double* __restrict__ part) {
-    __shared__ double red[28][kLT / 64];
-    const int oc = blockIdx.y, o = oc / cin, c = oc % cin;
-    const int64_t chunk = (d.n + nsplit - 1) / nsplit;
-    const int64_t v0 = (int64_t)blockIdx.x * chunk, v1 = std::min<int64_t>(d.n, v0 + chunk);
-    float acc[28];
-    for (int e = 0; e < 28; ++e) acc[e] = 0.f;
-    for (int64_t v = v0 + threadIdx.x; v < v1; v += kLT) {
-        const float g = dout[o * ocs + v * ovs];
-        if (g == 0.f) continue;
-        const VoxC pc = vox_coords(d, v);
+// Weight gradients: gW[o][c][e] = sum_v dout_o(v) in_c(v + e), gb[o] = sum_v dout_o(v),
+// where one of dout / in is a complex field (2 parts) and the other CH planes.
+// What bounds it: the loads of both fields per product.  Block (r, row) takes a
+// range of voxels and one row (e_y, e_z): every thread forms the 2 CH x 3 products of
+// its voxels (each loaded value is used 3 to 3 CH times) in FP32 over at most
+// kWgRun runs, then the block sums each of them over its threads in FP64 through
+// LDS in fixed order, into part[(r * 9 + row) * (6 CH + CH') + slot]; slots past
+// the products are the bias (row 4, the centre, only).  32 x 32 x 256, 8
+// channels: 17.5 (gW1) and 15.0 us (gW2) per launch, 98 with one (o, c) pair per
+// block, whose 27 products per voxel each took a load of their own; the sum over
+// the ranges 4.5 us, 18 with one thread per slot.  PLANES_OUT: dout is the planes (gW1), else in (gW2).
+static constexpr int kWgRun = 2;                       // runs of kXW voxels per thread
+template <int CH, bool PLANES_OUT>
+__global__ __launch_bounds__(kLT) void k_wgrad(Dims d, const float* __restrict__ planes, const cf32* __restrict__ field,
+                                               double* __restrict__ part) {
+    constexpr int NB = PLANES_OUT ? CH : 2, NV = 6 * CH + NB;
+    __shared__ float sv[NV][kLT + 1];
+    __shared__ double sd[NV][4];
+    const int row = blockIdx.y;
+    const int64_t n = run_count<kXW>(d), nz = d.nz;
+    float acc[2 * CH][3], bias[NB];
 #pragma unroll
-        for (int e = 0; e < 27; ++e) {
-            int64_t q;
-            if (nb(d, pc, v, e, q)) acc[e] += g * in[c * ics + q * ivs];
+    for (int p = 0; p < 2 * CH; ++p)
+#pragma unroll
+        for (int e = 0; e < 3; ++e) acc[p][e] = 0.f;
+#pragma unroll
+    for (int o = 0; o < NB; ++o) bias[o] = 0.f;
+    for (int q = 0; q < kWgRun; ++q) {
+        const int64_t t = ((int64_t)blockIdx.x * kWgRun + q) * kLT + threadIdx.x;
+        if (t >= n) break;
+        const Run r = run_at<kXW>(d, t);
+        int64_t off;
+        const bool in = row_inside(d, r, row, off);
+        if (PLANES_OUT) {
+            cf32 f[kXW + 2];
+            row_values(d, r, in, off, [&](int64_t at) { return field[r.v + at]; }, f);
+#pragma unroll
+            for (int o = 0; o < CH; ++o)
+#pragma unroll
+                for (int k = 0; k < kXW; ++k) {
+                    const float g = r.x + k < d.nx ? planes[(int64_t)o * d.n + r.v + k * nz] : 0.f;
+                    bias[o % NB] += g;
+#pragma unroll
+                    for (int e = 0; e < 3; ++e) {
+                        acc[2 * o][e] += g * f[k + e].re;
+                        acc[2 * o + 1][e] += g * f[k + e].im;
+                    }
+                }
+        } else {
+            cf32 g[kXW];
+#pragma unroll
+            for (int k = 0; k < kXW; ++k) {
+                g[k] = r.x + k < d.nx ? field[r.v + k * nz] : cf32{0.f, 0.f};
+                bias[0] += g[k].re;
+                bias[1 % NB] += g[k].im;
+            }
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                float v[kXW + 2];
+                row_values(d, r, in, off, [&](int64_t at) { return planes[(int64_t)c * d.n + r.v + at]; }, v);
+#pragma unroll
+                for (int k = 0; k < kXW; ++k)
+#pragma unroll
+                    for (int e = 0; e < 3; ++e) {
+                        acc[c][e] += g[k].re * v[k + e];
+                        acc[CH + c][e] += g[k].im * v[k + e];
+                    }
+            }
         }
-        acc[27] += g;
     }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int e = 0; e < 28; ++e) {
-        double x = acc[e];
-        for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-        if (lane == 0) red[e][wave] = x;
+#pragma unroll
+    for (int p = 0; p < 2 * CH; ++p)
+#pragma unroll
+        for (int e = 0; e < 3; ++e) sv[p * 3 + e][threadIdx.x] = acc[p][e];
+#pragma unroll
+    for (int o = 0; o < NB; ++o) sv[6 * CH + o][threadIdx.x] = bias[o];
+    __syncthreads();
+    for (int t = threadIdx.x; t < 4 * NV; t += kLT) {
+        const int w = t >> 2, q = t & 3;
+        double s = 0.0;
+        for (int i = 0; i < kLT / 4; ++i) s += (double)sv[w][4 * i + q];
+        sd[w][q] = s;
     }
     __syncthreads();
-    if (threadIdx.x < 28) {
-        double s = 0.0;
-        for (int i = 0; i < kLT / 64; ++i) s += red[threadIdx.x][i];
-        part[((int64_t)oc * nsplit + blockIdx.x) * 28 + threadIdx.x] = s;
-    }
+    for (int w = threadIdx.x; w < NV; w += kLT)
+        part[((int64_t)blockIdx.x * 9 + row) * NV + w] = (sd[w][0] + sd[w][1]) + (sd[w][2] + sd[w][3]);
 }
 
-// grad[(o * cin + c) * 27 + e] += sum over the ranges of the partials (fixed
-// order); bias[o] += the slot-27 sum of channel 0; each optionally times
-// c = lam / L (the correction's scale, see the stage definition).
-__global__ void k_wgrad_sum(const double* __restrict__ part, int nsplit, int cin,
-                            float* __restrict__ gW, float* __restrict__ gb,
-                            const double* __restrict__ lam, float invL, int scale_w, int scale_b) {
-    const int oc = blockIdx.x, o = oc / cin, c = oc % cin, e = threadIdx.x;
-    if (e >= 28) return;
-    const double cs = lam[0] * (double)invL;
+// gW[pair * 27 + tap_index(row, e)] += the sum over the voxel ranges of slot (row, pair,
+// e), gb[o] += that of the bias; each optionally times c = lam / L (the
+// correction's scale, see the stage definition).  One wave per slot: lane l sums
+// the ranges l, l + 64, ..., then a fixed tree.
+__global__ __launch_bounds__(kLT) void k_wgrad_sum(const double* __restrict__ part, int nsplit, int nw, int nb,
+                                                   float* __restrict__ gW, float* __restrict__ gb,
+                                                   const double* __restrict__ lam, float invL, int scale_w, int scale_b) {
+    const int slot = blockIdx.x * (kLT / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int nv = nw + nb;
+    if (slot >= 9 * nw + nb) return;
+    const int row = slot < 9 * nw ? slot / nw : 4, w = slot < 9 * nw ? slot - row * nw : nw + slot - 9 * nw;
     double s = 0.0;
-    for (int r = 0; r < nsplit; ++r) s += part[((int64_t)oc * nsplit + r) * 28 + e];
-    if (e < 27) gW[oc * 27 + e] += (float)(scale_w ? cs * s : s);
-    else if (c == 0) gb[o] += (float)(scale_b ? cs * s : s);
+    for (int r = lane; r < nsplit; r += 64) s += part[((int64_t)r * 9 + row) * nv + w];
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (lane != 0) return;
+    const double cs = lam[0] * (double)invL;
+    if (w < nw) gW[(w / 3) * 27 + tap_index(row, w % 3)] += (float)(scale_w ? cs * s : s);
+    else gb[w - nw] += (float)(scale_b ? cs * s : s);
 }
 
-// Voxel ranges per weight-gradient launch: about 16 voxels per thread, at
-// most kWgSplit ranges (with 2 ch <= 16 (o, c) pairs, up to 2048 workgroups).
-static constexpr int kWgSplit = 128;
-static int wgrad_split(int64_t n) {
-    return (int)std::max<int64_t>(1, std::min<int64_t>(kWgSplit, (n + 16 * kLT - 1) / (16 * kLT)));
-}
+// Voxel ranges of a weight-gradient launch.
+static int wgrad_split(const Dims& d) { return (int)((run_count<kXW>(d) + (int64_t)kLT * kWgRun - 1) / ((int64_t)kLT * kWgRun)); }
 
 // Soft-threshold backward and the step-size gradient partials.
 __global__ __launch_bounds__(kLT) void k_soft_bwd(int64_t n, const cf32* __restrict__ z,
@@ -447,7 +623,7 @@ Net* net_create(Plan* P, int S, int ch, double L, double mu, uint64_t seed) {
         N->d_lam = nalloc<double>(*N, 4);
         N->d_part = nalloc<double>(*N, 4096);
         N->d_sc = nalloc<double>(*N, 16);
-        N->d_wpart = nalloc<double>(*N, (size_t)2 * kMaxCh * kWgSplit * 28);
+        N->d_wpart = nalloc<double>(*N, (size_t)wgrad_split(Dims{P->g.nx, P->g.ny, P->g.nz, nv}) * 9 * (6 * ch + std::max(ch, 2)));
         // FISTA momentum weights (stage i = iteration i + 1)
         double t = 1.0;
         for (int i = 0; i < S; ++i) {
@@ -496,6 +672,21 @@ static Dims dims_of(const Net& N) {
     return Dims{N.P->g.nx, N.P->g.ny, N.P->g.nz, N.P->nvox};
 }
 
+// Calls f with the channel count as a compile-time constant.
+template <class F>
+static void with_channels(int ch, F f) {
+    switch (ch) {
+        case 1: f(std::integral_constant<int, 1>{}); break;
+        case 2: f(std::integral_constant<int, 2>{}); break;
+        case 3: f(std::integral_constant<int, 3>{}); break;
+        case 4: f(std::integral_constant<int, 4>{}); break;
+        case 5: f(std::integral_constant<int, 5>{}); break;
+        case 6: f(std::integral_constant<int, 6>{}); break;
+        case 7: f(std::integral_constant<int, 7>{}); break;
+        default: f(std::integral_constant<int, kMaxCh>{}); break;
+    }
+}
+
 // Forward pass; activations kept for the backward pass.  Result in N.x[S].
 static void net_forward(Net& N, const cf32* y, hipStream_t s) {
     Plan& P = *N.P;
@@ -508,19 +699,25 @@ static void net_forward(Net& N, const cf32* y, hipStream_t s) {
     hipLaunchKernelGGL(k_mul_scalar, dim3(1), dim3(64), 0, s, N.d_lam, N.mu);
     const Dims d = dims_of(N);
     const int ch = N.ch;
+    // the first extrapolation is x_0 itself; every further one is formed by the
+    // previous stage's last kernel
+    hipLaunchKernelGGL(k_momentum, dim3(nblk(n)), dim3(kLT), 0, s, n, N.x[0], N.x[0], N.beta[0], N.gam[0]);
+    const int nbr = nblk(run_count<kXC>(d));
     for (int i = 0; i < N.S; ++i) {
         const float* par = N.d_par + (int64_t)i * N.sn;
-        const cf32* xprev = i > 0 ? N.x[i - 1] : N.x[0];
-        hipLaunchKernelGGL(k_momentum, dim3(nblk(n)), dim3(kLT), 0, s, n, N.x[i], xprev, N.beta[i], N.gam[i]);
         op_forward(P, N.gam[i], P.d_r, y, nullptr, s);
         op_adjoint(P, P.d_r, N.g[i], s);
         hipLaunchKernelGGL(k_prox, dim3(nblk(n)), dim3(kLT), 0, s, n, N.gam[i], N.g[i], par, invL,
                            N.d_lam, N.z[i], N.u[i]);
-        hipLaunchKernelGGL(k_conv1, dim3(nblk(n)), dim3(kLT), 0, s, d, ch, N.u[i], par + 2,
-                           par + 2 + ch * 54, N.d_lam, invL, N.h[i]);
-        hipLaunchKernelGGL(k_conv2, dim3(nblk(n)), dim3(kLT), 0, s, d, ch, N.h[i],
-                           par + 2 + ch * 54 + ch, par + 2 + ch * 54 + ch + 2 * ch * 27, N.d_lam, invL,
-                           N.u[i], N.x[i + 1]);
+        const bool more = i + 1 < N.S;
+        with_channels(ch, [&](auto chc) {
+            constexpr int CH = decltype(chc)::value;
+            hipLaunchKernelGGL(k_conv1<CH>, dim3(nbr), dim3(kLT), 0, s, d, N.u[i], par + 2, par + 2 + CH * 54,
+                               N.d_lam, invL, N.h[i]);
+            hipLaunchKernelGGL(k_conv2<CH>, dim3(nbr), dim3(kLT), 0, s, d, N.h[i], par + 2 + CH * 54 + CH,
+                               par + 2 + CH * 54 + CH + 2 * CH * 27, N.d_lam, invL, N.u[i], N.x[i + 1], N.x[i],
+                               more ? N.beta[i + 1] : 0.f, more ? N.gam[i + 1] : nullptr);
+        });
     }
     UFSS_HIP(hipGetLastError());
 }
@@ -532,7 +729,7 @@ static void net_backward(Net& N, const cf32* aref, hipStream_t s) {
     const float invL = (float)(1.0 / N.L);
     const Dims d = dims_of(N);
     const int ch = N.ch;
-    const int nsp = wgrad_split(n);
+    const int nsp = wgrad_split(d), nbr = nblk(run_count<kXC>(d));
     int nb = launch_norm2(n, aref, P.d_part, s);
     launch_reduce(P.d_part, nb, 2, N.d_sc + 2, s);   // [2] = ||a_ref||^2
     for (int i = 0; i <= N.S; ++i) UFSS_HIP(hipMemsetAsync(N.dxs[i], 0, n * sizeof(cf32), s));
@@ -550,17 +747,20 @@ static void net_backward(Net& N, const cf32* aref, hipStream_t s) {
         float* gW2 = gb1 + ch;
         float* gb2 = gW2 + 2 * ch * 27;
         // conv correction backward
-        hipLaunchKernelGGL(k_conv2_bwd, dim3(nbl), dim3(kLT), 0, s, d, ch, N.dxs[i + 1], W2, N.h[i], N.dh);
-        hipLaunchKernelGGL(k_wgrad, dim3(nsp, 2 * ch), dim3(kLT), 0, s, d,
-                           reinterpret_cast<const float*>(N.dxs[i + 1]), (int64_t)1, 2, N.h[i], (int64_t)n, 1,
-                           ch, nsp, N.d_wpart);
-        hipLaunchKernelGGL(k_wgrad_sum, dim3(2 * ch), dim3(64), 0, s, N.d_wpart, nsp, ch, gW2, gb2,
-                           N.d_lam, invL, 1, 1);
-        hipLaunchKernelGGL(k_wgrad, dim3(nsp, ch * 2), dim3(kLT), 0, s, d, N.dh, (int64_t)n, 1,
-                           reinterpret_cast<const float*>(N.u[i]), (int64_t)1, 2, 2, nsp, N.d_wpart);
-        hipLaunchKernelGGL(k_wgrad_sum, dim3(ch * 2), dim3(64), 0, s, N.d_wpart, nsp, 2, gW1, gb1,
-                           N.d_lam, invL, 0, 1);
-        hipLaunchKernelGGL(k_conv1_bwd, dim3(nbl), dim3(kLT), 0, s, d, ch, N.dh, W1, N.dxs[i + 1], N.du);
+        with_channels(ch, [&](auto chc) {
+            constexpr int CH = decltype(chc)::value;
+            auto sum = [&](int nb, float* gW, float* gb, int scale_w) {
+                const int slots = 9 * 6 * CH + nb;
+                hipLaunchKernelGGL(k_wgrad_sum, dim3((slots + kLT / 64 - 1) / (kLT / 64)), dim3(kLT), 0, s, N.d_wpart,
+                                   nsp, 6 * CH, nb, gW, gb, N.d_lam, invL, scale_w, 1);
+            };
+            hipLaunchKernelGGL(k_conv2_bwd<CH>, dim3(nbr), dim3(kLT), 0, s, d, N.dxs[i + 1], W2, N.h[i], N.dh);
+            hipLaunchKernelGGL((k_wgrad<CH, false>), dim3(nsp, 9), dim3(kLT), 0, s, d, N.h[i], N.dxs[i + 1], N.d_wpart);
+            sum(2, gW2, gb2, 1);
+            hipLaunchKernelGGL((k_wgrad<CH, true>), dim3(nsp, 9), dim3(kLT), 0, s, d, N.dh, N.u[i], N.d_wpart);
+            sum(CH, gW1, gb1, 0);
+            hipLaunchKernelGGL(k_conv1_bwd<CH>, dim3(nbr), dim3(kLT), 0, s, d, N.dh, W1, N.dxs[i + 1], N.du);
+        });
         // soft threshold backward, theta / step partials
         hipLaunchKernelGGL(k_soft_bwd, dim3(nbl), dim3(kLT), 0, s, n, N.z[i], N.du, N.g[i], par, invL,
                            N.d_lam, N.dz, N.d_part);
