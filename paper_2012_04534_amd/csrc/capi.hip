@@ -74,14 +74,8 @@ static void ktime_end(Plan& P, int w, hipStream_t s) {
     ++P.kev_used[w];
 }
 
-int op_forward_partials(Plan& P, const cf32* x, cf32* y, const cf32* ymeas, double* part,
-                        hipStream_t s) {
-    if (P.algo == UFSS_ALGO_PHASOR) {
-        ktime_begin(P, 0, s);
-        launch_forward_phasor(P, x, y, ymeas, part, s);
-        ktime_end(P, 0, s);
-        return phasor_forward_blocks(P);
-    }
+// The forward operator up to the raw sums over the union bins (P.d_yraw).
+static void forward_core(Plan& P, const cf32* x, hipStream_t s) {
     if (P.algo == UFSS_ALGO_FFT) {
         fft_fwd_transform(P, x, s);
         ktime_begin(P, 0, s);
@@ -98,6 +92,17 @@ int op_forward_partials(Plan& P, const cf32* x, cf32* y, const cf32* ymeas, doub
         launch_forward_gemm(P, x, s);
         ktime_end(P, 0, s);
     }
+}
+
+int op_forward_partials(Plan& P, const cf32* x, cf32* y, const cf32* ymeas, double* part,
+                        hipStream_t s) {
+    if (P.algo == UFSS_ALGO_PHASOR) {
+        ktime_begin(P, 0, s);
+        launch_forward_phasor(P, x, y, ymeas, part, s);
+        ktime_end(P, 0, s);
+        return phasor_forward_blocks(P);
+    }
+    forward_core(P, x, s);
     return P.mix ? launch_mix_post(P, y, ymeas, part, s) : launch_forward_post(P, y, ymeas, part, s);
 }
 
@@ -107,16 +112,18 @@ void op_forward(Plan& P, const cf32* x, cf32* y, const cf32* ymeas, double* res2
     if (res2_out) launch_reduce(P.d_part, nb, 1, res2_out, s);
 }
 
-int op_adjoint(Plan& P, const cf32* y, cf32* x, hipStream_t s, bool defer_sum) {
-    if (P.mix)
-        launch_mix_pre(P, y, s);
-    else
-        launch_adjoint_pre(P, y, s);
+// The transform path's adjoint up to the last lateral product.
+static void fft_adjoint_core(Plan& P, hipStream_t s) {
+    fft_adj_transform(P, s);
+    ktime_begin(P, 1, s);
+    fft_adj_contract(P, s);
+    ktime_end(P, 1, s);
+}
+
+// The adjoint from its operand (P.d_rop) on.
+static int adjoint_core(Plan& P, cf32* x, hipStream_t s, bool defer_sum) {
     if (P.algo == UFSS_ALGO_FFT) {
-        fft_adj_transform(P, s);
-        ktime_begin(P, 1, s);
-        fft_adj_contract(P, s);
-        ktime_end(P, 1, s);
+        fft_adjoint_core(P, s);
         fft_adj_inverse(P, x, s);
         return 1;
     }
@@ -133,6 +140,27 @@ int op_adjoint(Plan& P, const cf32* y, cf32* x, hipStream_t s, bool defer_sum) {
     ktime_end(P, 1, s);
     if (P.adj_split > 1 && !defer_sum) launch_sum_parts(P.d_gpart, P.adj_split, P.nvox, x, s);
     return (defer_sum && P.adj_split > 1) ? P.adj_split : 1;
+}
+
+int op_adjoint(Plan& P, const cf32* y, cf32* x, hipStream_t s, bool defer_sum) {
+    if (P.mix)
+        launch_mix_pre(P, y, s);
+    else
+        launch_adjoint_pre(P, y, s);
+    return adjoint_core(P, x, s, defer_sum);
+}
+
+int op_residual(Plan& P, const cf32* x, const cf32* ymeas, double* part, const StatsJob& job, hipStream_t s) {
+    if (!post_pre_ok(P)) {
+        if (job.stats) launch_reduce_fista_stats(job, s);
+        return op_forward_partials(P, x, P.d_r, ymeas, part, s);
+    }
+    forward_core(P, x, s);
+    return launch_post_pre(P, ymeas, part, job, s);
+}
+
+int op_adjoint_residual(Plan& P, cf32* x, hipStream_t s, bool defer_sum) {
+    return post_pre_ok(P) ? adjoint_core(P, x, s, defer_sum) : op_adjoint(P, P.d_r, x, s, defer_sum);
 }
 
 static void sync(hipStream_t s) { UFSS_HIP(hipStreamSynchronize(s)); }
@@ -180,8 +208,9 @@ double lipschitz(Plan& P, int max_iters, double rtol, double margin, uint64_t se
     for (int it0 = 1; it0 <= max_iters && !done; it0 += kBlock) {
         const int nit = std::min(kBlock, max_iters - it0 + 1);
         for (int j = 0; j < nit; ++j) {
-            op_forward(P, P.d_v, P.d_r, nullptr, rho_dev + j, s);      // rho = ||A v||^2
-            op_adjoint(P, P.d_r, P.d_g, s);
+            const int nbr = op_residual(P, P.d_v, nullptr, P.d_part_res, StatsJob{}, s);
+            launch_reduce(P.d_part_res, nbr, 1, rho_dev + j, s);       // rho = ||A v||^2
+            op_adjoint_residual(P, P.d_g, s);
             nb = launch_norm2(P.nvox, P.d_g, P.d_part, s);
             launch_reduce(P.d_part, nb, 2, nrm, s);
             launch_copy(P.nvox, P.d_g, P.d_v, s);
@@ -257,19 +286,52 @@ int fista(Plan& P, const cf32* y, double lambda, double L, int iters, double tol
     }
     const float step = (float)(1.0 / L), thresh = (float)(lambda / L);
     int done = 0;
+    StatsJob job;                                   // the last iteration's statistics, if not reduced yet
+    auto finish_job = [&]() {
+        if (job.stats) launch_reduce_fista_stats(job, s);
+        job.stats = nullptr;
+    };
     for (int k = 0; k < iters; ++k) {
-        // the residual's partials wait in their own buffer for the statistics kernel
-        const int nbr = op_forward_partials(P, gamma, P.d_r, y, P.d_part_res, s);
-        // the adjoint's split-K partials are summed inside the update (its epilogue)
-        const int ns = op_adjoint(P, P.d_r, P.d_g, s, true);
+        // the residual's partials wait in a buffer of their own for the statistics,
+        // which the next iteration's post pass reduces beside its own work (two
+        // buffers in turn: that pass writes the next ones)
+        double* res_part = P.d_part_res + (k & 1) * (P.part_cap / 2);
+        const bool two = post_pre_ok(P);
+        if (!two) finish_job();
+        const int nbr = op_residual(P, gamma, y, two ? res_part : P.d_part_res, job, s);
         const double tn = 0.5 * (1.0 + std::sqrt(1.0 + 4.0 * tk * tk));
         const double beta = accel ? (tk - 1.0) / tn : 0.0;
-        int nb = launch_update(P.nvox, gamma, ns > 1 ? P.d_gpart : P.d_g, ns, x, step, thresh,
+        int nb = 0;
+        if (P.algo == UFSS_ALGO_FFT && two) {
+            // the update in the transform path's last product
+            fft_adjoint_core(P, s);
+            nb = fft_adj_inverse_update(P, UpdateArgs{gamma, x, aref, P.d_part, step, thresh, (float)beta, real},
+                                        P.part_cap, s);
+            if (nb == 0) {
+                fft_adj_inverse(P, P.d_g, s);
+                nb = launch_update(P.nvox, gamma, P.d_g, 1, x, step, thresh, (float)beta, aref, P.d_part, s, real);
+            }
+        } else {
+            // the adjoint's split-K partials are summed inside the update (its epilogue)
+            const int ns = op_adjoint_residual(P, P.d_g, s, true);
+            nb = launch_update(P.nvox, gamma, ns > 1 ? P.d_gpart : P.d_g, ns, x, step, thresh,
                                (float)beta, aref, P.d_part, s, real);
-        launch_reduce_fista_stats(P.d_part_res, nbr, P.d_scalars + 0, P.d_part, nb, P.d_scalars + 8,
-                                  P.d_stats, k, g1, lambda, aref ? 1 : 0, ref2, s);
+        }
+        job.res_part = two ? res_part : P.d_part_res;
+        job.res_nblk = nbr;
+        job.res2_out = P.d_scalars + 0;
+        job.part = P.d_part;
+        job.nblk = nb;
+        job.upd_out = P.d_scalars + 8;
+        job.stats = P.d_stats;
+        job.k = k;
+        job.g1 = g1;
+        job.lam = lambda;
+        job.have_ref = aref ? 1 : 0;
+        job.ref2 = ref2;
         tk = tn;
         done = k + 1;
+        if (!two || k + 1 == iters || (tol > 0 && done % 8 == 0)) finish_job();
         if (tol > 0 && (done % 8 == 0)) {
             double rc = read_scalar(P.d_stats + 4 * (int64_t)k + 2, s);
             if (rc <= tol) break;

@@ -53,11 +53,13 @@ static constexpr int kTwPK = 8;
 static constexpr int kTwKS = 16;
 static constexpr int kTwMaxNI = 4;
 
-template <int NI, bool INV>
+// UPD (inverse): the FISTA update of update_kernel applied to each result g in place
+// of storing it (one pass and one launch less), five FP64 partials per block.
+template <int NI, bool INV, bool UPD = false>
 __global__ __launch_bounds__(256) void twiddle_kernel(cf32* __restrict__ out, const cf32* __restrict__ in,
                                                       const cf32* __restrict__ tab, int L, int n, int ks, int tiles,
                                                       int units, int nct, int C, int64_t sib, int64_t sij,
-                                                      int64_t sob, int64_t soi) {
+                                                      int64_t sob, int64_t soi, UpdateArgs upd) {
     __shared__ __align__(16) cf32 wl[NI * kTwKS * 64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int unit = blockIdx.x * 4 + wave, b = unit / nct;
@@ -131,6 +133,38 @@ __global__ __launch_bounds__(256) void twiddle_kernel(cf32* __restrict__ out, co
             }
         }
     }
+    if constexpr (UPD) {
+        double sum[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int t = 0; t < NI; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int i = 16 * (t0 + t) + 4 * kq + r;
+                if (ok && i < n) {
+                    const int64_t v = (int64_t)b * sob + c + (int64_t)i * soi;
+                    cf32 an, gn;
+                    fista_step(upd.gamma[v], upd.a[v], cf32{acc[t][0][r], acc[t][1][r]}, upd.step, upd.thresh,
+                               upd.beta, upd.real, upd.aref ? upd.aref + v : nullptr, an, gn, sum);
+                    upd.a[v] = an;
+                    upd.gamma[v] = gn;
+                }
+            }
+        double* red = reinterpret_cast<double*>(wl);          // [5][4], tables read
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < 5; ++w) {
+            double x = sum[w];
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+            if (lane == 0) red[w * 4 + wave] = x;
+        }
+        __syncthreads();
+        if (threadIdx.x < 5) {
+            const double* q = red + threadIdx.x * 4;
+            upd.part[((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 5 + threadIdx.x] = ((q[0] + q[1]) + q[2]) + q[3];
+        }
+        return;
+    }
     if (!ok) return;
     cf32* dst = out + (int64_t)b * sob + c;
 #pragma unroll
@@ -148,26 +182,32 @@ __global__ __launch_bounds__(256) void twiddle_kernel(cf32* __restrict__ out, co
         }
 }
 
+// Row tiles per wave: as many as the accumulators allow, fewer (more waves, each
+// input column read by more of them) while the launch has under 2048 waves.
+static int row_tiles(int tiles, int64_t units) {
+    int ni = std::min(tiles, kTwMaxNI);
+    while (ni > 1 && units * ((tiles + ni - 1) / ni) < 2048) --ni;
+    while (ni > 1 && (tiles + ni - 2) / (ni - 1) == (tiles + ni - 1) / ni) --ni;   // the same rounds with fewer
+    return ni;
+}
+
 // One lateral product over B batches of C channels: forward n -> L indices or
-// inverse L -> n.
-template <bool INV>
-static void twiddle(cf32* out, const cf32* in, const cf32* tab, int B, int L, int n, int C, int64_t sib,
-                    int64_t sij, int64_t sob, int64_t soi, hipStream_t s) {
+// inverse L -> n (UPD: the update in place of the stores).  Returns its blocks.
+template <bool INV, bool UPD = false>
+static int twiddle(cf32* out, const cf32* in, const cf32* tab, int B, int L, int n, int C, int64_t sib,
+                    int64_t sij, int64_t sob, int64_t soi, hipStream_t s, const UpdateArgs& upd = UpdateArgs{}) {
     const int rows = INV ? n : L / 2 + 1, J = INV ? L / 2 + 1 : n;
     const int tiles = (rows + 15) / 16, ks = (J + 3) / 4;
     const int nct = (C + 15) / 16;
     const int64_t units = (int64_t)B * nct;
-    // row tiles per wave: as many as the accumulators allow, fewer (more waves,
-    // each input column read by more of them) while the launch has under 2048 waves
-    int ni = std::min(tiles, kTwMaxNI);
-    while (ni > 1 && units * ((tiles + ni - 1) / ni) < 2048) --ni;
-    while (ni > 1 && (tiles + ni - 2) / (ni - 1) == (tiles + ni - 1) / ni) --ni;   // the same rounds with fewer
+    const int ni = row_tiles(tiles, units);
     const dim3 grid((unsigned)((units + 3) / 4), (tiles + ni - 1) / ni);
-#define UFSS_TW(T) hipLaunchKernelGGL((twiddle_kernel<T, INV>), grid, dim3(256), 0, s, out, in, tab, L, n, ks, tiles, \
-                                      (int)units, nct, C, sib, sij, sob, soi)
+#define UFSS_TW(T) hipLaunchKernelGGL((twiddle_kernel<T, INV, UPD>), grid, dim3(256), 0, s, out, in, tab, L, n, ks, tiles, \
+                                      (int)units, nct, C, sib, sij, sob, soi, upd)
     if (ni == 1) UFSS_TW(1); else if (ni == 2) UFSS_TW(2); else if (ni == 3) UFSS_TW(3); else UFSS_TW(4);
 #undef UFSS_TW
     UFSS_HIP(hipGetLastError());
+    return (int)(grid.x * grid.y);
 }
 
 // The transform indices (q_y, q_x) that share the stored entry (oy, ox): q_y = oy
@@ -659,6 +699,15 @@ void fft_adj_transform(const Plan& P, hipStream_t s) {
 }
 
 void fft_adj_contract(const Plan& P, hipStream_t s) { contract<false>(P, s); }
+
+int fft_adj_inverse_update(const Plan& P, const UpdateArgs& u, int cap, hipStream_t s) {
+    const int nx = P.g.nx, ny = P.g.ny, nz = P.g.nz, lx = P.fft_lx, ly = P.fft_ly;
+    const int64_t units = (int64_t)nx * ((nz + 15) / 16);
+    const int tiles = (ny + 15) / 16, ni = row_tiles(tiles, units);
+    if ((units + 3) / 4 * ((tiles + ni - 1) / ni) * 5 > cap) return 0;      // the last product's blocks
+    twiddle<true>(P.d_ft, P.d_fb, P.d_tw_ix, ly, lx, nx, nz, (int64_t)lx * nz, nz, (int64_t)nx * nz, nz, s);
+    return twiddle<true, true>(nullptr, P.d_ft, P.d_tw_iy, nx, ly, ny, nz, nz, (int64_t)nx * nz, nz, (int64_t)nx * nz, s, u);
+}
 
 void fft_adj_inverse(const Plan& P, cf32* out, hipStream_t s) {
     const int nx = P.g.nx, ny = P.g.ny, nz = P.g.nz, lx = P.fft_lx, ly = P.fft_ly;

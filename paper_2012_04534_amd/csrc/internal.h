@@ -109,6 +109,8 @@ struct Plan {
     int* d_ubins = nullptr;        // union bins [mu]
     int* d_map = nullptr;          // per (p, m): index into the union list
     float* d_hsel = nullptr;       // H_k per selection entry [m] or [npos*m]
+    int* d_inv = nullptr;          // per-position plans: (p, j) -> the m with map(p, m) = j, or -1
+    float* d_hu = nullptr;         // H_k per union bin [mu]
     uint32_t* d_u = nullptr;       // integer-turn delay table [wy+1][wx+1][nz]
     float* d_amp = nullptr;        // Gaussian beam amplitude, same layout (theta > 0)
     // random mixing (Rademacher signs): the union is every DFT index (signed
@@ -172,6 +174,27 @@ void launch_adjoint_phasor(const Plan& P, cf32* out, hipStream_t s);     // P.d_
 int launch_forward_post(const Plan& P, cf32* y, const cf32* ymeas, double* part, hipStream_t s);
 // rop[p][j] = sum over m with map(p,m) = j of H * r[p][m] (zero elsewhere).
 void launch_adjoint_pre(const Plan& P, const cf32* r, hipStream_t s);
+// A FISTA iteration's statistics: the residual's and the update's partials and
+// where their sums go (see reduce_fista_stats_kernel); stats == nullptr: none.
+struct StatsJob {
+    const double* res_part = nullptr;
+    int res_nblk = 0;
+    double* res2_out = nullptr;
+    const double* part = nullptr;
+    int nblk = 0;
+    double* upd_out = nullptr;
+    double* stats = nullptr;
+    int k = 0;
+    double* g1 = nullptr;
+    double lam = 0.0;
+    int have_ref = 0;
+    double ref2 = 0.0;
+};
+// The forward post pass and the adjoint pre pass of the same values in one launch:
+// rop <- the adjoint's operand of A x (- ymeas), FP64 partials of its norm in
+// part (count returned); `job`: an earlier iteration's statistics, by one more block.
+bool post_pre_ok(const Plan& P);
+int launch_post_pre(const Plan& P, const cf32* ymeas, double* part, const StatsJob& job, hipStream_t s);
 void launch_to_bf16(const cf32* x, void* out, int64_t n, hipStream_t s);
 int gemm_split(const Plan& P);
 int gemm_zsplit(const Plan& P);
@@ -227,9 +250,7 @@ void launch_copy(int64_t n, const cf32* src, cf32* dst, hipStream_t s);
 // columns into upd_out, then the FISTA statistics of iteration k (objective,
 // residual, relative change, error vs a reference) and the next ||gamma||_1,
 // in one launch
-void launch_reduce_fista_stats(const double* res_part, int res_nblk, double* res2_out,
-                               const double* part, int nblk, double* upd_out, double* stats, int k,
-                               double* g1, double lam, int have_ref, double ref2, hipStream_t s);
+void launch_reduce_fista_stats(const StatsJob& job, hipStream_t s);
 
 // Transform path (fft.hip).
 void fft_setup(Plan& P);
@@ -240,6 +261,42 @@ void fft_fwd_inverse(const Plan& P, hipStream_t s);
 void fft_adj_transform(const Plan& P, hipStream_t s);
 void fft_adj_contract(const Plan& P, hipStream_t s);
 void fft_adj_inverse(const Plan& P, cf32* out, hipStream_t s);
+// One voxel of the fused proximal-gradient update (see update_kernel): gamma gm,
+// iterate aa and gradient gg in, the new iterate and gamma out, the five sums.
+__device__ __forceinline__ void fista_step(cf32 gm, cf32 aa, cf32 gg, float step, float thresh, float beta, int real,
+                                           const cf32* __restrict__ aref, cf32& an, cf32& gn, double (&acc)[5]) {
+    // real: the reflectivity is real, the gradient step keeps Re (Re{H} model)
+    float zr = gm.re - step * gg.re, zi = real ? 0.f : gm.im - step * gg.im;
+    float mag = sqrtf(zr * zr + zi * zi);
+    float sc = mag > thresh ? 1.0f - thresh / mag : 0.0f;
+    float ar = zr * sc, ai = zi * sc;
+    float gr = ar + beta * (ar - aa.re), gi = ai + beta * (ai - aa.im);
+    an = cf32{ar, ai};
+    gn = cf32{gr, gi};
+    double dr = (double)ar - aa.re, di = (double)ai - aa.im;
+    acc[0] += sqrt((double)ar * ar + (double)ai * ai);
+    acc[1] += sqrt((double)gr * gr + (double)gi * gi);
+    acc[2] += dr * dr + di * di;
+    acc[3] += (double)ar * ar + (double)ai * ai;
+    if (aref) {
+        cf32 q = *aref;
+        double er = (double)ar - q.re, ei = (double)ai - q.im;
+        acc[4] += er * er + ei * ei;
+    }
+}
+// The FISTA update of launch_update applied to A^H's result as it is formed
+// (the last lateral product): x and gamma in place, 5 FP64 partials per block.
+struct UpdateArgs {
+    cf32* gamma = nullptr;
+    cf32* a = nullptr;
+    const cf32* aref = nullptr;
+    double* part = nullptr;
+    float step = 0.f, thresh = 0.f, beta = 0.f;
+    int real = 0;
+};
+// Returns the number of partial blocks, 0 if the grid has too many for `cap`
+// doubles (then nothing of the last product was launched).
+int fft_adj_inverse_update(const Plan& P, const UpdateArgs& u, int cap, hipStream_t s);
 
 // Random mixing passes (vec.hip): they replace launch_forward_post and
 // launch_adjoint_pre on mixed plans.
@@ -265,5 +322,12 @@ void op_forward(Plan& P, const cf32* x, cf32* y, const cf32* ymeas, double* res2
 // Returns 1 when x holds A^H y; with defer_sum, the number of split partials
 // left in P.d_gpart instead (> 1) for a consumer that sums them itself.
 int op_adjoint(Plan& P, const cf32* y, cf32* x, hipStream_t s, bool defer_sum = false);
+// A^H (A x - ymeas): the forward core, the fused post and pre pass (P.d_r is then
+// not written), and the adjoint core from the operand left in P.d_rop; for plans
+// whose passes cannot be fused, op_forward_partials and op_adjoint through P.d_r.
+// Returns the partial blocks of ||A x - ymeas||^2 in part.
+int op_residual(Plan& P, const cf32* x, const cf32* ymeas, double* part, const StatsJob& job, hipStream_t s);
+// The adjoint of what op_residual left; as op_adjoint.
+int op_adjoint_residual(Plan& P, cf32* x, hipStream_t s, bool defer_sum = false);
 
 }  // namespace ufss

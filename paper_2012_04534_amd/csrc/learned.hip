@@ -562,7 +562,7 @@ struct Net {
     int64_t adam_t = 0;
     std::vector<cf32*> x, gam, g, z, u, dxs;
     std::vector<float*> h;
-    cf32 *du = nullptr, *dz = nullptr, *tmp = nullptr, *rtmp = nullptr;
+    cf32 *du = nullptr, *dz = nullptr, *tmp = nullptr;
     float* dh = nullptr;
     double *d_lam = nullptr, *d_part = nullptr, *d_sc = nullptr, *d_wpart = nullptr;
     std::vector<float> beta;
@@ -599,7 +599,7 @@ Net* net_create(Plan* P, int S, int ch, double L, double mu, uint64_t seed) {
         N->L = L;
         N->mu = mu;
         N->np = (int64_t)S * N->sn;
-        const int64_t nv = P->nvox, nm = (int64_t)P->npos * P->m;
+        const int64_t nv = P->nvox;
         N->d_par = nalloc<float>(*N, N->np);
         N->d_grad = nalloc<float>(*N, N->np);
         N->d_m = nalloc<float>(*N, N->np);
@@ -618,7 +618,6 @@ Net* net_create(Plan* P, int S, int ch, double L, double mu, uint64_t seed) {
         N->du = nalloc<cf32>(*N, nv);
         N->dz = nalloc<cf32>(*N, nv);
         N->tmp = nalloc<cf32>(*N, nv);
-        N->rtmp = nalloc<cf32>(*N, nm);
         N->dh = nalloc<float>(*N, (size_t)ch * nv);
         N->d_lam = nalloc<double>(*N, 4);
         N->d_part = nalloc<double>(*N, 4096);
@@ -705,8 +704,8 @@ static void net_forward(Net& N, const cf32* y, hipStream_t s) {
     const int nbr = nblk(run_count<kXC>(d));
     for (int i = 0; i < N.S; ++i) {
         const float* par = N.d_par + (int64_t)i * N.sn;
-        op_forward(P, N.gam[i], P.d_r, y, nullptr, s);
-        op_adjoint(P, P.d_r, N.g[i], s);
+        op_residual(P, N.gam[i], y, P.d_part, StatsJob{}, s);
+        op_adjoint_residual(P, N.g[i], s);
         hipLaunchKernelGGL(k_prox, dim3(nblk(n)), dim3(kLT), 0, s, n, N.gam[i], N.g[i], par, invL,
                            N.d_lam, N.z[i], N.u[i]);
         const bool more = i + 1 < N.S;
@@ -766,8 +765,8 @@ static void net_backward(Net& N, const cf32* aref, hipStream_t s) {
                            N.d_lam, N.dz, N.d_part);
         hipLaunchKernelGGL(k_scalar_grads, dim3(1), dim3(kLT), 0, s, N.d_part, nbl, par, invL, N.d_lam, gpar);
         // gamma backward through I - s A^H A
-        op_forward(P, N.dz, N.rtmp, nullptr, nullptr, s);
-        op_adjoint(P, N.rtmp, N.tmp, s);
+        op_residual(P, N.dz, nullptr, P.d_part, StatsJob{}, s);
+        op_adjoint_residual(P, N.tmp, s);
         hipLaunchKernelGGL(k_dgamma, dim3(nbl), dim3(kLT), 0, s, n, N.dz, N.tmp, par, invL, N.beta[i],
                            N.dxs[i], i >= 1 ? N.dxs[i - 1] : nullptr);
     }

@@ -6,6 +6,7 @@
 // slot, and a single-block kernel sums the slots in a fixed order.  No float
 // atomics anywhere, so results are bitwise reproducible run to run.
 #include <algorithm>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -104,6 +105,98 @@ int launch_forward_post(const Plan& P, cf32* y, const cf32* ymeas, double* part,
 }
 
 // ---------------------------------------------------------------------------
+// Forward post pass and adjoint pre pass of the same residual in one launch:
+// over the union bins j of every position, with m the position's selection of j,
+//   v = H_j sum_s yraw[s][p][j] - ymeas[p][m],  rop[p][j] = H_j v,
+// zero where the position does not select j, plus FP64 partials of ||v||^2.  In
+// the solvers the residual itself has no other reader, so its buffer, one launch
+// and the zeroing of rop go.  The last block (job.stats) reduces an earlier
+// iteration's partials instead: a launch of its own on the critical path takes
+// 4-5 us, as much as either pass.
+// Measured with the update in the transform's last product (fft.hip): 20 FISTA
+// iterations of the 32 x 32 x 256 scan 2100 -> 1968 us on the transform plan, 20 of
+// the 32-position B-scan (GEMM) 792 -> 672 us.
+// ---------------------------------------------------------------------------
+__device__ void fista_stats(const StatsJob& job, double* red, double* upd);
+static constexpr int kStatsRed = 8 * kThreads;
+
+template <int PG, bool BF16>
+__global__ __launch_bounds__(kThreads) void post_pre_kernel(
+    const cf32* __restrict__ yraw, int split, int64_t npos, int mu, int m, const int* __restrict__ inv,
+    const float* __restrict__ hu, const cf32* __restrict__ ymeas, void* __restrict__ rop,
+    double* __restrict__ part, StatsJob job) {
+    __shared__ double red[kStatsRed];
+    __shared__ double upd[6];
+    const int nb = gridDim.x - (job.stats ? 1 : 0);
+    if ((int)blockIdx.x == nb) {
+        fista_stats(job, red, upd);
+        return;
+    }
+    double acc[1] = {0.0};
+    constexpr int per_wave = 64 / PG;                 // outputs of a wave
+    const int64_t n = npos * mu;
+    const int grp = (threadIdx.x & 63) / per_wave;
+    const int64_t first = ((int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6)) * per_wave + (threadIdx.x & (per_wave - 1));
+    for (int64_t i = first; i < n; i += (int64_t)nb * (kThreads / PG)) {
+        const int64_t p = i / mu;
+        const int j = (int)(i - p * mu);
+        const int mi = inv ? inv[i] : j;
+        cf32 sum{0.f, 0.f};
+        if (mi >= 0) sum = sum_parts_ordered(yraw + i + grp * n, PG * n, (split - grp + PG - 1) / PG);
+#pragma unroll
+        for (int off = per_wave; off < 64; off <<= 1) {
+            sum.re += __shfl_xor(sum.re, off, 64);
+            sum.im += __shfl_xor(sum.im, off, 64);
+        }
+        if (grp != 0) continue;
+        const float h = hu[j];
+        float re = 0.f, im = 0.f;
+        if (mi >= 0) {
+            re = sum.re * h;
+            im = sum.im * h;
+            if (ymeas) {
+                const cf32 q = ymeas[p * m + mi];
+                re -= q.re;
+                im -= q.im;
+            }
+        }
+        if (BF16) static_cast<cbf16*>(rop)[i] = to_cbf16(h * re, h * im);
+        else static_cast<cf32*>(rop)[i] = cf32{h * re, h * im};
+        acc[0] += (double)re * re + (double)im * im;
+    }
+    block_sum_write<1>(acc, part);
+}
+
+// GEMM and transform plans without mixing.
+bool post_pre_ok(const Plan& P) { return P.algo != UFSS_ALGO_PHASOR && !P.mix; }
+
+int launch_post_pre(const Plan& P, const cf32* ymeas, double* part, const StatsJob& job, hipStream_t s) {
+    const int mu = (int)P.ubins_h.size();
+    const int64_t n = (int64_t)P.npos * mu;
+    const int split = P.fwd_split * std::max(1, P.fwd_zsplit);
+    int pg = 1;                                       // as the forward post pass
+    while (pg < 8 && 8 * pg <= split && 2 * pg * n <= (int64_t)kMaxBlocks * kThreads) pg *= 2;
+    const int nb = blocks_for(n * pg);
+    const bool bf16 = P.dtype == UFSS_BF16 && P.algo == UFSS_ALGO_GEMM;
+    auto go = [&](auto pgc) {
+        constexpr int PG = decltype(pgc)::value;
+        const dim3 grid(nb + (job.stats ? 1 : 0));
+        if (bf16)
+            hipLaunchKernelGGL((post_pre_kernel<PG, true>), grid, dim3(kThreads), 0, s, P.d_yraw, split, (int64_t)P.npos,
+                               mu, P.m, P.d_inv, P.d_hu, ymeas, P.d_rop, part, job);
+        else
+            hipLaunchKernelGGL((post_pre_kernel<PG, false>), grid, dim3(kThreads), 0, s, P.d_yraw, split, (int64_t)P.npos,
+                               mu, P.m, P.d_inv, P.d_hu, ymeas, P.d_rop, part, job);
+    };
+    if (pg == 8) go(std::integral_constant<int, 8>{});
+    else if (pg == 4) go(std::integral_constant<int, 4>{});
+    else if (pg == 2) go(std::integral_constant<int, 2>{});
+    else go(std::integral_constant<int, 1>{});
+    UFSS_HIP(hipGetLastError());
+    return nb;
+}
+
+// ---------------------------------------------------------------------------
 // Adjoint pre pass: one block per scan position writes the row
 // rop[p][0..w) = 0 except rop[p][map(p, m)] = H_sel * r[p][m].
 // ---------------------------------------------------------------------------
@@ -184,24 +277,10 @@ __global__ __launch_bounds__(kThreads) void update_kernel(int64_t n, cf32* __res
         cf32 gm = gamma[i], aa = a[i];
         cf32 gg = g[i];
         if (nsplit > 1) gg = sum_parts_ordered(g + i, n, nsplit);
-        // real: the reflectivity is real, the gradient step keeps Re (Re{H} model)
-        float zr = gm.re - step * gg.re, zi = real ? 0.f : gm.im - step * gg.im;
-        float mag = sqrtf(zr * zr + zi * zi);
-        float sc = mag > thresh ? 1.0f - thresh / mag : 0.0f;
-        float ar = zr * sc, ai = zi * sc;
-        float gr = ar + beta * (ar - aa.re), gi = ai + beta * (ai - aa.im);
-        a[i] = cf32{ar, ai};
-        gamma[i] = cf32{gr, gi};
-        double dr = (double)ar - aa.re, di = (double)ai - aa.im;
-        acc[0] += sqrt((double)ar * ar + (double)ai * ai);
-        acc[1] += sqrt((double)gr * gr + (double)gi * gi);
-        acc[2] += dr * dr + di * di;
-        acc[3] += (double)ar * ar + (double)ai * ai;
-        if (aref) {
-            cf32 q = aref[i];
-            double er = (double)ar - q.re, ei = (double)ai - q.im;
-            acc[4] += er * er + ei * ei;
-        }
+        cf32 an, gn;
+        fista_step(gm, aa, gg, step, thresh, beta, real, aref ? aref + i : nullptr, an, gn, acc);
+        a[i] = an;
+        gamma[i] = gn;
     }
     block_sum_write<5>(acc, part);
 }
@@ -568,29 +647,27 @@ void launch_copy(int64_t n, const cf32* src, cf32* dst, hipStream_t s) {
 // {l1a, l1g, dA2, a2, ref2diff}, then with g1 = ||gamma_k||_1
 //   stats[k] = {1/2 res2 + lam g1, sqrt(res2), sqrt(dA2 / a2), sqrt(ref2diff / ref2)}
 // and g1 <- ||gamma_new||_1 for the next iteration.
-__global__ __launch_bounds__(kThreads) void reduce_fista_stats_kernel(
-    const double* __restrict__ res_part, int res_nblk, double* __restrict__ res2_out,
-    const double* __restrict__ part, int nblk, double* __restrict__ upd_out, double* stats, int k,
-    double* g1, double lam, int have_ref, double ref2) {
-    __shared__ double red[kRedW * kThreads];
-    __shared__ double upd[6];
-    block_reduce_cols(res_part, res_nblk, 1, res2_out, red, upd + 5);
-    block_reduce_cols(part, nblk, 5, upd_out, red, upd);
+__device__ void fista_stats(const StatsJob& job, double* red, double* upd) {
+    block_reduce_cols(job.res_part, job.res_nblk, 1, job.res2_out, red, upd + 5);
+    block_reduce_cols(job.part, job.nblk, 5, job.upd_out, red, upd);
     if (threadIdx.x != 0) return;
     const double r2 = upd[5];
-    double* st = stats + 4 * (int64_t)k;
-    st[0] = 0.5 * r2 + lam * g1[0];
+    double* st = job.stats + 4 * (int64_t)job.k;
+    st[0] = 0.5 * r2 + job.lam * job.g1[0];
     st[1] = sqrt(r2);
     st[2] = upd[3] > 0.0 ? sqrt(upd[2] / upd[3]) : 0.0;
-    st[3] = have_ref ? sqrt(upd[4] / ref2) : 0.0;
-    g1[0] = upd[1];
+    st[3] = job.have_ref ? sqrt(upd[4] / job.ref2) : 0.0;
+    job.g1[0] = upd[1];
 }
 
-void launch_reduce_fista_stats(const double* res_part, int res_nblk, double* res2_out,
-                               const double* part, int nblk, double* upd_out, double* stats, int k,
-                               double* g1, double lam, int have_ref, double ref2, hipStream_t s) {
-    hipLaunchKernelGGL(reduce_fista_stats_kernel, dim3(1), dim3(kThreads), 0, s, res_part, res_nblk,
-                       res2_out, part, nblk, upd_out, stats, k, g1, lam, have_ref, ref2);
+__global__ __launch_bounds__(kThreads) void reduce_fista_stats_kernel(StatsJob job) {
+    __shared__ double red[kStatsRed];
+    __shared__ double upd[6];
+    fista_stats(job, red, upd);
+}
+
+void launch_reduce_fista_stats(const StatsJob& job, hipStream_t s) {
+    hipLaunchKernelGGL(reduce_fista_stats_kernel, dim3(1), dim3(kThreads), 0, s, job);
     UFSS_HIP(hipGetLastError());
 }
 
