@@ -74,14 +74,20 @@ static void ktime_end(Plan& P, int w, hipStream_t s) {
     ++P.kev_used[w];
 }
 
-// The forward operator up to the raw sums over the union bins (P.d_yraw).
+// The transform path's forward contraction of the spectrum in P.d_fa.
+static void fft_forward_contract(Plan& P, hipStream_t s) {
+    ktime_begin(P, 0, s);
+    fft_fwd_contract(P, s);
+    ktime_end(P, 0, s);
+}
+
+// The forward operator up to the raw sums over the union bins: P.d_yraw, or on
+// transform plans with fused passes their lateral spectrum.
 static void forward_core(Plan& P, const cf32* x, hipStream_t s) {
     if (P.algo == UFSS_ALGO_FFT) {
         fft_fwd_transform(P, x, s);
-        ktime_begin(P, 0, s);
-        fft_fwd_contract(P, s);
-        ktime_end(P, 0, s);
-        fft_fwd_inverse(P, s);
+        fft_forward_contract(P, s);
+        if (!fft_fused(P)) fft_fwd_inverse(P, s);
     } else if (P.dtype == UFSS_BF16) {
         launch_to_bf16(x, P.d_xop, P.nvox, s);
         ktime_begin(P, 0, s);
@@ -103,6 +109,7 @@ int op_forward_partials(Plan& P, const cf32* x, cf32* y, const cf32* ymeas, doub
         return phasor_forward_blocks(P);
     }
     forward_core(P, x, s);
+    if (fft_fused(P)) return fft_post(P, y, ymeas, part, s);
     return P.mix ? launch_mix_post(P, y, ymeas, part, s) : launch_forward_post(P, y, ymeas, part, s);
 }
 
@@ -112,9 +119,10 @@ void op_forward(Plan& P, const cf32* x, cf32* y, const cf32* ymeas, double* res2
     if (res2_out) launch_reduce(P.d_part, nb, 1, res2_out, s);
 }
 
-// The transform path's adjoint up to the last lateral product.
+// The transform path's adjoint up to the last lateral products (fused passes: the
+// operand's spectrum is there already).
 static void fft_adjoint_core(Plan& P, hipStream_t s) {
-    fft_adj_transform(P, s);
+    if (!fft_fused(P)) fft_adj_transform(P, s);
     ktime_begin(P, 1, s);
     fft_adj_contract(P, s);
     ktime_end(P, 1, s);
@@ -145,6 +153,8 @@ static int adjoint_core(Plan& P, cf32* x, hipStream_t s, bool defer_sum) {
 int op_adjoint(Plan& P, const cf32* y, cf32* x, hipStream_t s, bool defer_sum) {
     if (P.mix)
         launch_mix_pre(P, y, s);
+    else if (fft_fused(P))
+        fft_pre(P, y, s);
     else
         launch_adjoint_pre(P, y, s);
     return adjoint_core(P, x, s, defer_sum);
@@ -156,6 +166,7 @@ int op_residual(Plan& P, const cf32* x, const cf32* ymeas, double* part, const S
         return op_forward_partials(P, x, P.d_r, ymeas, part, s);
     }
     forward_core(P, x, s);
+    if (fft_fused(P)) return fft_residual(P, ymeas, part, job, s);
     return launch_post_pre(P, ymeas, part, job, s);
 }
 
@@ -291,6 +302,9 @@ int fista(Plan& P, const cf32* y, double lambda, double L, int iters, double tol
         if (job.stats) launch_reduce_fista_stats(job, s);
         job.stats = nullptr;
     };
+    // fused transform plans: each update leaves the new gamma's spectrum
+    const bool chain = fft_fused(P);
+    if (chain && iters > 0) fft_fwd_transform(P, gamma, s);
     for (int k = 0; k < iters; ++k) {
         // the residual's partials wait in a buffer of their own for the statistics,
         // which the next iteration's post pass reduces beside its own work (two
@@ -298,19 +312,19 @@ int fista(Plan& P, const cf32* y, double lambda, double L, int iters, double tol
         double* res_part = P.d_part_res + (k & 1) * (P.part_cap / 2);
         const bool two = post_pre_ok(P);
         if (!two) finish_job();
-        const int nbr = op_residual(P, gamma, y, two ? res_part : P.d_part_res, job, s);
+        int nbr;
+        if (chain) {
+            fft_forward_contract(P, s);
+            nbr = fft_residual(P, y, res_part, job, s);
+        } else {
+            nbr = op_residual(P, gamma, y, two ? res_part : P.d_part_res, job, s);
+        }
         const double tn = 0.5 * (1.0 + std::sqrt(1.0 + 4.0 * tk * tk));
         const double beta = accel ? (tk - 1.0) / tn : 0.0;
         int nb = 0;
-        if (P.algo == UFSS_ALGO_FFT && two) {
-            // the update in the transform path's last product
+        if (chain) {
             fft_adjoint_core(P, s);
-            nb = fft_adj_inverse_update(P, UpdateArgs{gamma, x, aref, P.d_part, step, thresh, (float)beta, real},
-                                        P.part_cap, s);
-            if (nb == 0) {
-                fft_adj_inverse(P, P.d_g, s);
-                nb = launch_update(P.nvox, gamma, P.d_g, 1, x, step, thresh, (float)beta, aref, P.d_part, s, real);
-            }
+            nb = fft_update(P, UpdateArgs{gamma, x, aref, P.d_part, step, thresh, (float)beta, real}, k + 1 < iters, s);
         } else {
             // the adjoint's split-K partials are summed inside the update (its epilogue)
             const int ns = op_adjoint_residual(P, P.d_g, s, true);

@@ -53,13 +53,11 @@ static constexpr int kTwPK = 8;
 static constexpr int kTwKS = 16;
 static constexpr int kTwMaxNI = 4;
 
-// UPD (inverse): the FISTA update of update_kernel applied to each result g in place
-// of storing it (one pass and one launch less), five FP64 partials per block.
-template <int NI, bool INV, bool UPD = false>
+template <int NI, bool INV>
 __global__ __launch_bounds__(256) void twiddle_kernel(cf32* __restrict__ out, const cf32* __restrict__ in,
                                                       const cf32* __restrict__ tab, int L, int n, int ks, int tiles,
                                                       int units, int nct, int C, int64_t sib, int64_t sij,
-                                                      int64_t sob, int64_t soi, UpdateArgs upd) {
+                                                      int64_t sob, int64_t soi) {
     __shared__ __align__(16) cf32 wl[NI * kTwKS * 64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int unit = blockIdx.x * 4 + wave, b = unit / nct;
@@ -133,38 +131,6 @@ __global__ __launch_bounds__(256) void twiddle_kernel(cf32* __restrict__ out, co
             }
         }
     }
-    if constexpr (UPD) {
-        double sum[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int t = 0; t < NI; ++t)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int i = 16 * (t0 + t) + 4 * kq + r;
-                if (ok && i < n) {
-                    const int64_t v = (int64_t)b * sob + c + (int64_t)i * soi;
-                    cf32 an, gn;
-                    fista_step(upd.gamma[v], upd.a[v], cf32{acc[t][0][r], acc[t][1][r]}, upd.step, upd.thresh,
-                               upd.beta, upd.real, upd.aref ? upd.aref + v : nullptr, an, gn, sum);
-                    upd.a[v] = an;
-                    upd.gamma[v] = gn;
-                }
-            }
-        double* red = reinterpret_cast<double*>(wl);          // [5][4], tables read
-        __syncthreads();
-#pragma unroll
-        for (int w = 0; w < 5; ++w) {
-            double x = sum[w];
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-            if (lane == 0) red[w * 4 + wave] = x;
-        }
-        __syncthreads();
-        if (threadIdx.x < 5) {
-            const double* q = red + threadIdx.x * 4;
-            upd.part[((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 5 + threadIdx.x] = ((q[0] + q[1]) + q[2]) + q[3];
-        }
-        return;
-    }
     if (!ok) return;
     cf32* dst = out + (int64_t)b * sob + c;
 #pragma unroll
@@ -182,32 +148,26 @@ __global__ __launch_bounds__(256) void twiddle_kernel(cf32* __restrict__ out, co
         }
 }
 
-// Row tiles per wave: as many as the accumulators allow, fewer (more waves, each
-// input column read by more of them) while the launch has under 2048 waves.
-static int row_tiles(int tiles, int64_t units) {
-    int ni = std::min(tiles, kTwMaxNI);
-    while (ni > 1 && units * ((tiles + ni - 1) / ni) < 2048) --ni;
-    while (ni > 1 && (tiles + ni - 2) / (ni - 1) == (tiles + ni - 1) / ni) --ni;   // the same rounds with fewer
-    return ni;
-}
-
 // One lateral product over B batches of C channels: forward n -> L indices or
-// inverse L -> n (UPD: the update in place of the stores).  Returns its blocks.
-template <bool INV, bool UPD = false>
-static int twiddle(cf32* out, const cf32* in, const cf32* tab, int B, int L, int n, int C, int64_t sib,
-                    int64_t sij, int64_t sob, int64_t soi, hipStream_t s, const UpdateArgs& upd = UpdateArgs{}) {
+// inverse L -> n.
+template <bool INV>
+static void twiddle(cf32* out, const cf32* in, const cf32* tab, int B, int L, int n, int C, int64_t sib,
+                    int64_t sij, int64_t sob, int64_t soi, hipStream_t s) {
     const int rows = INV ? n : L / 2 + 1, J = INV ? L / 2 + 1 : n;
     const int tiles = (rows + 15) / 16, ks = (J + 3) / 4;
     const int nct = (C + 15) / 16;
     const int64_t units = (int64_t)B * nct;
-    const int ni = row_tiles(tiles, units);
+    // row tiles per wave: as many as the accumulators allow, fewer (more waves,
+    // each input column read by more of them) while the launch has under 2048 waves
+    int ni = std::min(tiles, kTwMaxNI);
+    while (ni > 1 && units * ((tiles + ni - 1) / ni) < 2048) --ni;
+    while (ni > 1 && (tiles + ni - 2) / (ni - 1) == (tiles + ni - 1) / ni) --ni;   // the same rounds with fewer
     const dim3 grid((unsigned)((units + 3) / 4), (tiles + ni - 1) / ni);
-#define UFSS_TW(T) hipLaunchKernelGGL((twiddle_kernel<T, INV, UPD>), grid, dim3(256), 0, s, out, in, tab, L, n, ks, tiles, \
-                                      (int)units, nct, C, sib, sij, sob, soi, upd)
+#define UFSS_TW(T) hipLaunchKernelGGL((twiddle_kernel<T, INV>), grid, dim3(256), 0, s, out, in, tab, L, n, ks, tiles, \
+                                      (int)units, nct, C, sib, sij, sob, soi)
     if (ni == 1) UFSS_TW(1); else if (ni == 2) UFSS_TW(2); else if (ni == 3) UFSS_TW(3); else UFSS_TW(4);
 #undef UFSS_TW
     UFSS_HIP(hipGetLastError());
-    return (int)(grid.x * grid.y);
 }
 
 // The transform indices (q_y, q_x) that share the stored entry (oy, ox): q_y = oy
@@ -672,6 +632,320 @@ static void contract(const Plan& P, hipStream_t s) {
     }
 }
 
+// ---------------------------------------------------------------------------
+// The passes between two contractions act on one position and channel at a time,
+// and the lateral products along y on one (x, channel) column: so the inverse
+// product along y, the pass and the next forward product along y are one kernel,
+// with the column in registers from one to the next.
+//   kPre    measurements, times H -> DFT_y
+//   kPost   IDFT_y -> times H (- ymeas) -> measurements
+//   kBins   IDFT_y -> H^2 and - H ymeas -> DFT_y       (A x - y on its way to R^)
+//   kDepth  IDFT_y -> FISTA update -> DFT_y            (X' on its way to the next X^)
+// What bounds it: launches and latencies.  On a small scan each product and each
+// pass takes 4-6 us as a kernel of its own, of which its arithmetic is under 1 us;
+// a FISTA iteration goes from 11 launches to 8.  (A whole plane in LDS, both axes
+// at once, 4 launches, gains nothing: 8-byte columns of every row of the array cost
+// 3 us to load and 5 us to store.)
+// A workgroup of 4 waves takes 16 channels of one x (2 or 4 where NT, the tiles of 16
+// rows y, is 2 or 1): wave w the inverse's tile w and every 4 / (units)-th tile of the
+// forward product, so that a chain is one tile long; the column goes from one to the
+// other through LDS.  A table operand is used once per wave: it is loaded from the
+// cache, with the column, kTwPK steps ahead.  Operands and order are twiddle_kernel's.
+// 32 x 32 x 256, 66 bins: the bins' side of an iteration (5 launches) 22.5 us -> 18
+// with 3, the depths' side (4) 25.5 -> 20.5 with 3, the fused kernels 7.4 and 9.6 us of
+// it (8.8 and 11.8 with all tiles in one wave); an apply pair of 45 x 51 x 301 (BF16
+// table) 139 -> 133 us with one launch less per operator.
+// ---------------------------------------------------------------------------
+enum { kPre, kPost, kBins, kDepth };
+
+struct ColumnArgs {
+    const cf32* in;                           // [ly][nx][C], or the measurements (kPre)
+    cf32* out;                                // [ly][nx][C], or the measurements (kPost)
+    const cf32 *tiy, *tfy;
+    int nx, ny, ly, C, nct, units;
+    // kPre, kPost, kBins
+    const int* inv;                           // [npos][C], or null: measurement c is channel c
+    const float* hu;
+    const cf32* ymeas;
+    int m;
+    double* part;                             // per block: 1 value (kPost, kBins) or 5 (kDepth)
+    // kDepth
+    UpdateArgs upd;
+    int more;
+    StatsJob job;                             // kBins: by the last block
+};
+
+// Block-wide FP64 sums of 4 waves in fixed order.
+template <int W>
+__device__ __forceinline__ void column_sums(double (&v)[W], double* red, double* out) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        double x = v[w];
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+        if (lane == 0) red[w * 4 + wave] = x;
+    }
+    __syncthreads();
+    if (threadIdx.x < W) {
+        const double* q = red + threadIdx.x * 4;
+        out[threadIdx.x] = ((q[0] + q[1]) + q[2]) + q[3];
+    }
+}
+
+// Units (one x, 16 channels) per workgroup.
+__host__ __device__ constexpr int column_units(int nt) { return nt == 1 ? 4 : nt == 2 ? 2 : 1; }
+
+template <int NT, int MODE>
+__global__ __launch_bounds__(256) void column_kernel(ColumnArgs g) {
+    constexpr int UN = column_units(NT), NW = 4 / UN;         // waves per unit
+    constexpr bool kIv = MODE != kPre, kFw = MODE != kPost;
+    __shared__ __align__(16) double smem[MODE == kBins ? kStatsRed + 6 : UN * NT * 256];
+    __shared__ double red[5 * 4];
+    if (MODE == kBins && (int)blockIdx.x * UN >= g.units) {
+        fista_stats(g.job, smem, smem + kStatsRed);
+        return;
+    }
+    const int nx = g.nx, ny = g.ny, L = g.ly;
+    const int64_t C = g.C;
+    const int J = L / 2 + 1, ksi = (J + 3) / 4, ksf = (ny + 3) / 4, tf = (J + 15) / 16;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int un = wave / NW, w = wave - un * NW;             // unit in the workgroup, wave in the unit
+    const int unit = blockIdx.x * UN + un, px = unit / g.nct;
+    const int ch = lane & 15, c = (unit - px * g.nct) * 16 + ch, kq = lane >> 4;
+    const bool ok = unit < g.units && c < C;
+    const bool mine = w < NT;                                 // the unit's waves that hold a tile
+    cf32* xs = reinterpret_cast<cf32*>(smem) + un * NT * 256; // [16 NT rows][16 channels]
+    const cf32* src = g.in + (int64_t)px * C + c;
+    const cf32* ti = g.tiy + (int64_t)min(w, NT - 1) * ksi * 64 + lane;
+    // table operand and column (folded about L / 2) of reduction step s
+    struct Col { cf32 a, e, o; };
+    auto fetch = [&](int s) {
+        Col v{{0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}};
+        if (s < ksi) v.a = ti[s * 64];
+        const int j = 4 * s + kq;
+        if (ok && j < J) {
+            v.e = src[(int64_t)j * nx * C];
+            if (j > 0 && 2 * j < L) v.o = src[(int64_t)(L - j) * nx * C];
+        }
+        return v;
+    };
+    Col cur[kTwPK];
+    if (kIv && mine) {
+#pragma unroll
+        for (int p = 0; p < kTwPK; ++p) cur[p] = fetch(p);
+    }
+    // the forward product's first operands
+    const bool fw = kFw && (MODE != kDepth || g.more);
+    cf32 af[kTwPK];
+    auto first = [&](int T) {
+#pragma unroll
+        for (int p = 0; p < kTwPK; ++p)
+            if (p < ksf) af[p] = g.tfy[((int64_t)T * ksf + p) * 64 + lane];
+    };
+    if (fw && w < tf) first(w);
+    // what the pass reads, requested before the product: rows i0 .. i0 + 3
+    const int i0 = 16 * w + 4 * kq;
+    auto pos = [&](int r) { return (int64_t)(i0 + r) * nx + px; };
+    int mi[4];
+    cf32 q[4], v[4];
+    float h = 0.f;
+    if constexpr (MODE != kDepth) {
+        if (ok) h = g.hu[c];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mi[r] = ok && mine && i0 + r < ny ? (g.inv ? g.inv[pos(r) * C + c] : c) : -1;
+        const cf32* rows = MODE == kPre ? g.in : g.ymeas;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            q[r] = cf32{0.f, 0.f};
+            if (rows && mi[r] >= 0) q[r] = rows[pos(r) * g.m + mi[r]];
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            q[r] = v[r] = cf32{0.f, 0.f};
+            if (!ok || !mine || i0 + r >= ny) continue;
+            q[r] = g.upd.gamma[pos(r) * C + c];
+            v[r] = g.upd.a[pos(r) * C + c];
+        }
+    }
+    f4v acc[2] = {f4v{0.f, 0.f, 0.f, 0.f}, f4v{0.f, 0.f, 0.f, 0.f}};
+    if (kIv && mine) {
+        for (int s0 = 0; s0 < ksi; s0 += kTwPK) {
+#pragma unroll
+            for (int p = 0; p < kTwPK; ++p) {
+                if (s0 + p >= ksi) break;                     // uniform
+                const Col u = cur[p];
+                cur[p] = fetch(s0 + p + kTwPK);
+                // an unmirrored index (0, L / 2) has sin = 0: its difference is not used
+                const float er = u.e.re + u.o.re, ei = u.e.im + u.o.im;
+                const float orr = u.e.re - u.o.re, oi = u.o.im - u.e.im;
+                acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(u.a.re, er, acc[0], 0, 0, 0);
+                acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(u.a.re, ei, acc[1], 0, 0, 0);
+                acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(u.a.im, oi, acc[0], 0, 0, 0);
+                acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(u.a.im, orr, acc[1], 0, 0, 0);
+            }
+        }
+    }
+    double sum[MODE == kDepth ? 5 : 1] = {};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        if constexpr (MODE == kDepth) {
+            if (ok && mine && i0 + r < ny) {
+                const int64_t at = pos(r) * C + c;
+                cf32 an, gn;
+                fista_step(q[r], v[r], cf32{acc[0][r], acc[1][r]}, g.upd.step, g.upd.thresh, g.upd.beta, g.upd.real,
+                           g.upd.aref ? g.upd.aref + at : nullptr, an, gn, sum);
+                g.upd.a[at] = an;
+                g.upd.gamma[at] = gn;
+                v[r] = gn;
+            }
+        } else if constexpr (MODE == kPre) {
+            v[r] = cf32{h * q[r].re, h * q[r].im};
+        } else {
+            float re = 0.f, im = 0.f;
+            if (mi[r] >= 0) {
+                re = acc[0][r] * h;
+                im = acc[1][r] * h;
+                if (g.ymeas) {
+                    re -= q[r].re;
+                    im -= q[r].im;
+                }
+                if (MODE == kPost) g.out[pos(r) * g.m + mi[r]] = cf32{re, im};
+            }
+            v[r] = cf32{h * re, h * im};
+            sum[0] += (double)re * re + (double)im * im;
+        }
+        if (kFw && mine) xs[(i0 + r) * 16 + ch] = v[r];
+    }
+    if constexpr (MODE == kDepth) column_sums(sum, red, g.part + 5 * (int64_t)blockIdx.x);
+    else if constexpr (MODE != kPre) column_sums(sum, red, g.part + blockIdx.x);
+    else __syncthreads();                                     // xs is written (column_sums has the barrier too)
+    if (!fw || unit >= g.units) return;
+    cf32* dst = g.out + (int64_t)px * C + c;
+    for (int T = w; T < tf; T += NW) {
+        f4v d[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) d[e] = f4v{0.f, 0.f, 0.f, 0.f};
+        for (int s0 = 0; s0 < ksf; s0 += kTwPK) {
+#pragma unroll
+            for (int p = 0; p < kTwPK; ++p) {
+                const int s = s0 + p;
+                if (s >= ksf) break;                          // uniform
+                const cf32 a = af[p], e = xs[(4 * s + kq) * 16 + ch];
+                if (s + kTwPK < ksf) af[p] = g.tfy[((int64_t)T * ksf + s + kTwPK) * 64 + lane];
+                d[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.re, e.re, d[0], 0, 0, 0);
+                d[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.re, e.im, d[1], 0, 0, 0);
+                d[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.im, e.re, d[2], 0, 0, 0);
+                d[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.im, e.im, d[3], 0, 0, 0);
+            }
+        }
+        if (T + NW < tf) first(T + NW);
+        if (!ok) continue;                                    // a lane's table operand is of another channel's row
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = 16 * T + 4 * kq + r;
+            const float cr = d[0][r], ci = d[1][r], sr = d[2][r], si = d[3][r];
+            if (2 * i <= L) dst[(int64_t)i * nx * C] = cf32{cr + si, ci - sr};
+            if (i > 0 && 2 * i < L) dst[(int64_t)(L - i) * nx * C] = cf32{cr - si, ci + sr};
+        }
+    }
+}
+
+// Rows y of a column: 4 tiles of 16, one per wave.  Longer grids, and grids whose update
+// would leave more partials than there is room for, take a kernel per product and pass.
+static constexpr int kColTiles = 4;
+
+static int column_blocks(const Plan& P, int C) {
+    const int un = column_units((P.g.ny + 15) / 16);
+    return (P.g.nx * ((C + 15) / 16) + un - 1) / un;
+}
+
+bool fft_fused(const Plan& P) {
+    return P.algo == UFSS_ALGO_FFT && !P.mix && P.g.ny <= 16 * kColTiles && column_blocks(P, P.g.nz) * 5 <= P.part_cap &&
+           column_blocks(P, (int)P.ubins_h.size()) <= P.part_cap / 2;
+}
+
+template <int MODE>
+static int column(const Plan& P, const cf32* in, cf32* out, int C, ColumnArgs g, hipStream_t s) {
+    g.in = in;
+    g.out = out;
+    g.tiy = P.d_tw_iy;
+    g.tfy = P.d_tw_fy;
+    g.nx = P.g.nx;
+    g.ny = P.g.ny;
+    g.ly = P.fft_ly;
+    g.C = C;
+    g.nct = (C + 15) / 16;
+    g.units = g.nx * g.nct;
+    const int nt = (g.ny + 15) / 16, blocks = column_blocks(P, C);
+    const dim3 grid(blocks + (MODE == kBins && g.job.stats ? 1 : 0));
+    auto go = [&](auto ntc) {
+        hipLaunchKernelGGL((column_kernel<decltype(ntc)::value, MODE>), grid, dim3(256), 0, s, g);
+    };
+    if (nt == 1) go(std::integral_constant<int, 1>{});
+    else if (nt == 2) go(std::integral_constant<int, 2>{});
+    else if (nt == 3) go(std::integral_constant<int, 3>{});
+    else go(std::integral_constant<int, 4>{});
+    UFSS_HIP(hipGetLastError());
+    return blocks;
+}
+
+static ColumnArgs meas_args(const Plan& P, const cf32* ymeas, double* part) {
+    ColumnArgs g{};
+    g.inv = P.d_inv;
+    g.hu = P.d_hu;
+    g.ymeas = ymeas;
+    g.m = P.m;
+    g.part = part;
+    return g;
+}
+
+// The products along x around the fused ones: [ly][lx][C] -> [ly][nx][C] and back.
+static void inverse_x(const Plan& P, int C, hipStream_t s) {
+    const int nx = P.g.nx, lx = P.fft_lx, ly = P.fft_ly;
+    twiddle<true>(P.d_ft, P.d_fb, P.d_tw_ix, ly, lx, nx, C, (int64_t)lx * C, C, (int64_t)nx * C, C, s);
+}
+static void forward_x(const Plan& P, int C, hipStream_t s) {
+    const int nx = P.g.nx, lx = P.fft_lx, ly = P.fft_ly;
+    twiddle<false>(P.d_fa, P.d_ft, P.d_tw_fx, ly, lx, nx, C, (int64_t)nx * C, C, (int64_t)lx * C, C, s);
+}
+
+int fft_post(const Plan& P, cf32* y, const cf32* ymeas, double* part, hipStream_t s) {
+    const int mu = (int)P.ubins_h.size();
+    inverse_x(P, mu, s);
+    return column<kPost>(P, P.d_ft, y, mu, meas_args(P, ymeas, part), s);
+}
+
+void fft_pre(const Plan& P, const cf32* r, hipStream_t s) {
+    const int mu = (int)P.ubins_h.size();
+    column<kPre>(P, r, P.d_ft, mu, meas_args(P, nullptr, nullptr), s);
+    forward_x(P, mu, s);
+}
+
+// The fused kernels work in place: a workgroup has read its columns before it writes them.
+int fft_residual(const Plan& P, const cf32* ymeas, double* part, const StatsJob& job, hipStream_t s) {
+    const int mu = (int)P.ubins_h.size();
+    ColumnArgs g = meas_args(P, ymeas, part);
+    g.job = job;
+    inverse_x(P, mu, s);
+    const int nb = column<kBins>(P, P.d_ft, P.d_ft, mu, g, s);
+    forward_x(P, mu, s);
+    return nb;
+}
+
+int fft_update(const Plan& P, const UpdateArgs& u, bool more, hipStream_t s) {
+    const int nz = P.g.nz;
+    ColumnArgs g{};
+    g.upd = u;
+    g.part = u.part;
+    g.more = more;
+    inverse_x(P, nz, s);
+    const int nb = column<kDepth>(P, P.d_ft, P.d_ft, nz, g, s);
+    if (more) forward_x(P, nz, s);
+    return nb;
+}
+
 // Forward, in three steps (the contraction is the core kernel):
 //   x[ny][nx][nz] -> T[ny][lx][nz] -> X^[ly][lx][nz]
 void fft_fwd_transform(const Plan& P, const cf32* x, hipStream_t s) {
@@ -699,15 +973,6 @@ void fft_adj_transform(const Plan& P, hipStream_t s) {
 }
 
 void fft_adj_contract(const Plan& P, hipStream_t s) { contract<false>(P, s); }
-
-int fft_adj_inverse_update(const Plan& P, const UpdateArgs& u, int cap, hipStream_t s) {
-    const int nx = P.g.nx, ny = P.g.ny, nz = P.g.nz, lx = P.fft_lx, ly = P.fft_ly;
-    const int64_t units = (int64_t)nx * ((nz + 15) / 16);
-    const int tiles = (ny + 15) / 16, ni = row_tiles(tiles, units);
-    if ((units + 3) / 4 * ((tiles + ni - 1) / ni) * 5 > cap) return 0;      // the last product's blocks
-    twiddle<true>(P.d_ft, P.d_fb, P.d_tw_ix, ly, lx, nx, nz, (int64_t)lx * nz, nz, (int64_t)nx * nz, nz, s);
-    return twiddle<true, true>(nullptr, P.d_ft, P.d_tw_iy, nx, ly, ny, nz, nz, (int64_t)nx * nz, nz, (int64_t)nx * nz, s, u);
-}
 
 void fft_adj_inverse(const Plan& P, cf32* out, hipStream_t s) {
     const int nx = P.g.nx, ny = P.g.ny, nz = P.g.nz, lx = P.fft_lx, ly = P.fft_ly;

@@ -190,6 +190,62 @@ struct StatsJob {
     int have_ref = 0;
     double ref2 = 0.0;
 };
+static constexpr int kRedThreads = 256;
+// out[w] = sum over b of part[b][w] for w < width <= kRedW, one workgroup of
+// at least kRedThreads, fixed order: thread t sums b = t, t + kRedThreads, ... per column,
+// then one tree over the threads carries all columns at once (the same pairs
+// as a tree per column, with one barrier per level for all of them).  Thread
+// w < width writes out[w] (and keep[w] when given); every thread returns after
+// the last barrier.
+static constexpr int kRedW = 8;
+static constexpr int kStatsRed = kRedW * kRedThreads;   // doubles of `red` below
+
+__device__ __forceinline__ void block_reduce_cols(const double* __restrict__ part, int nblk,
+                                                  int width, double* __restrict__ out,
+                                                  double* red, double* keep) {
+    double acc[kRedW];
+#pragma unroll
+    for (int w = 0; w < kRedW; ++w) acc[w] = 0.0;
+    for (int b = threadIdx.x; threadIdx.x < kRedThreads && b < nblk; b += kRedThreads) {
+#pragma unroll
+        for (int w = 0; w < kRedW; ++w)
+            if (w < width) acc[w] += part[(int64_t)b * width + w];
+    }
+#pragma unroll
+    for (int w = 0; w < kRedW; ++w)
+        if (w < width && threadIdx.x < kRedThreads) red[w * kRedThreads + threadIdx.x] = acc[w];
+    __syncthreads();
+    for (int off = kRedThreads / 2; off > 0; off >>= 1) {
+        if (threadIdx.x < off)
+            for (int w = 0; w < width; ++w) red[w * kRedThreads + threadIdx.x] += red[w * kRedThreads + threadIdx.x + off];
+        __syncthreads();
+    }
+    if (threadIdx.x < width) {
+        out[threadIdx.x] = red[threadIdx.x * kRedThreads];
+        if (keep) keep[threadIdx.x] = red[threadIdx.x * kRedThreads];
+    }
+    __syncthreads();
+}
+
+// The residual's partials and the update's five partial columns reduced (each
+// as reduce_kernel, same order) and the iteration's statistics, in one launch:
+// res2_out <- ||A gamma_k - y||^2, upd_out <- the five sums
+// {l1a, l1g, dA2, a2, ref2diff}, then with g1 = ||gamma_k||_1
+//   stats[k] = {1/2 res2 + lam g1, sqrt(res2), sqrt(dA2 / a2), sqrt(ref2diff / ref2)}
+// and g1 <- ||gamma_new||_1 for the next iteration.
+__device__ __forceinline__ void fista_stats(const StatsJob& job, double* red, double* upd) {
+    block_reduce_cols(job.res_part, job.res_nblk, 1, job.res2_out, red, upd + 5);
+    block_reduce_cols(job.part, job.nblk, 5, job.upd_out, red, upd);
+    if (threadIdx.x != 0) return;
+    const double r2 = upd[5];
+    double* st = job.stats + 4 * (int64_t)job.k;
+    st[0] = 0.5 * r2 + job.lam * job.g1[0];
+    st[1] = sqrt(r2);
+    st[2] = upd[3] > 0.0 ? sqrt(upd[2] / upd[3]) : 0.0;
+    st[3] = job.have_ref ? sqrt(upd[4] / job.ref2) : 0.0;
+    job.g1[0] = upd[1];
+}
+
 // The forward post pass and the adjoint pre pass of the same values in one launch:
 // rop <- the adjoint's operand of A x (- ymeas), FP64 partials of its norm in
 // part (count returned); `job`: an earlier iteration's statistics, by one more block.
@@ -285,7 +341,7 @@ __device__ __forceinline__ void fista_step(cf32 gm, cf32 aa, cf32 gg, float step
     }
 }
 // The FISTA update of launch_update applied to A^H's result as it is formed
-// (the last lateral product): x and gamma in place, 5 FP64 partials per block.
+// (transform plans): x and gamma in place, 5 FP64 partials per block.
 struct UpdateArgs {
     cf32* gamma = nullptr;
     cf32* a = nullptr;
@@ -294,9 +350,16 @@ struct UpdateArgs {
     float step = 0.f, thresh = 0.f, beta = 0.f;
     int real = 0;
 };
-// Returns the number of partial blocks, 0 if the grid has too many for `cap`
-// doubles (then nothing of the last product was launched).
-int fft_adj_inverse_update(const Plan& P, const UpdateArgs& u, int cap, hipStream_t s);
+// Plans without mixing on grids of at most 64 rows: the passes around a contraction
+// in one kernel with the lateral products along y.  fft_post: Y^ -> y = A x (- ymeas),
+// partials of ||y||^2 (count returned); fft_pre: r -> R^; fft_residual: Y^ -> R^ of
+// A x - ymeas (with partials, and an earlier iteration's statistics by one more block);
+// fft_update: X' -> the FISTA update and, if more, X^ of the new gamma.
+bool fft_fused(const Plan& P);
+int fft_post(const Plan& P, cf32* y, const cf32* ymeas, double* part, hipStream_t s);
+void fft_pre(const Plan& P, const cf32* r, hipStream_t s);
+int fft_residual(const Plan& P, const cf32* ymeas, double* part, const StatsJob& job, hipStream_t s);
+int fft_update(const Plan& P, const UpdateArgs& u, bool more, hipStream_t s);
 
 // Random mixing passes (vec.hip): they replace launch_forward_post and
 // launch_adjoint_pre on mixed plans.

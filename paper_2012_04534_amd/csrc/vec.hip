@@ -12,7 +12,7 @@
 
 namespace ufss {
 
-static constexpr int kThreads = 256;
+static constexpr int kThreads = kRedThreads;
 static constexpr int kMaxBlocks = 1024;
 
 int max_blocks_vec() { return kMaxBlocks; }
@@ -113,13 +113,9 @@ int launch_forward_post(const Plan& P, cf32* y, const cf32* ymeas, double* part,
 // and the zeroing of rop go.  The last block (job.stats) reduces an earlier
 // iteration's partials instead: a launch of its own on the critical path takes
 // 4-5 us, as much as either pass.
-// Measured with the update in the transform's last product (fft.hip): 20 FISTA
-// iterations of the 32 x 32 x 256 scan 2100 -> 1968 us on the transform plan, 20 of
-// the 32-position B-scan (GEMM) 792 -> 672 us.
+// 20 FISTA iterations of the 32-position B-scan (GEMM): 792 -> 672 us.  (Transform
+// plans go further: column_kernel.)
 // ---------------------------------------------------------------------------
-__device__ void fista_stats(const StatsJob& job, double* red, double* upd);
-static constexpr int kStatsRed = 8 * kThreads;
-
 template <int PG, bool BF16>
 __global__ __launch_bounds__(kThreads) void post_pre_kernel(
     const cf32* __restrict__ yraw, int split, int64_t npos, int mu, int m, const int* __restrict__ inv,
@@ -486,41 +482,6 @@ int launch_extrap(int64_t n, const cf32* a, const cf32* b, float beta, cf32* out
 // ---------------------------------------------------------------------------
 // Fixed-order reductions.
 // ---------------------------------------------------------------------------
-// out[w] = sum over b of part[b][w] for w < width <= kRedW, one workgroup of
-// kThreads, fixed order: thread t sums b = t, t + kThreads, ... per column,
-// then one tree over the threads carries all columns at once (the same pairs
-// as a tree per column, with one barrier per level for all of them).  Thread
-// w < width writes out[w] (and keep[w] when given); every thread returns after
-// the last barrier.
-static constexpr int kRedW = 8;
-
-__device__ __forceinline__ void block_reduce_cols(const double* __restrict__ part, int nblk,
-                                                  int width, double* __restrict__ out,
-                                                  double* red, double* keep) {
-    double acc[kRedW];
-#pragma unroll
-    for (int w = 0; w < kRedW; ++w) acc[w] = 0.0;
-    for (int b = threadIdx.x; b < nblk; b += kThreads) {
-#pragma unroll
-        for (int w = 0; w < kRedW; ++w)
-            if (w < width) acc[w] += part[(int64_t)b * width + w];
-    }
-#pragma unroll
-    for (int w = 0; w < kRedW; ++w)
-        if (w < width) red[w * kThreads + threadIdx.x] = acc[w];
-    __syncthreads();
-    for (int off = kThreads / 2; off > 0; off >>= 1) {
-        if (threadIdx.x < off)
-            for (int w = 0; w < width; ++w) red[w * kThreads + threadIdx.x] += red[w * kThreads + threadIdx.x + off];
-        __syncthreads();
-    }
-    if (threadIdx.x < width) {
-        out[threadIdx.x] = red[threadIdx.x * kThreads];
-        if (keep) keep[threadIdx.x] = red[threadIdx.x * kThreads];
-    }
-    __syncthreads();
-}
-
 __global__ __launch_bounds__(kThreads) void reduce_kernel(const double* __restrict__ part,
                                                           int nblk, int width,
                                                           double* __restrict__ out) {
@@ -639,25 +600,6 @@ __global__ __launch_bounds__(kThreads) void copy_kernel(int64_t n, const cf32* _
 void launch_copy(int64_t n, const cf32* src, cf32* dst, hipStream_t s) {
     hipLaunchKernelGGL(copy_kernel, dim3(blocks_for(n)), dim3(kThreads), 0, s, n, src, dst);
     UFSS_HIP(hipGetLastError());
-}
-
-// The residual's partials and the update's five partial columns reduced (each
-// as reduce_kernel, same order) and the iteration's statistics, in one launch:
-// res2_out <- ||A gamma_k - y||^2, upd_out <- the five sums
-// {l1a, l1g, dA2, a2, ref2diff}, then with g1 = ||gamma_k||_1
-//   stats[k] = {1/2 res2 + lam g1, sqrt(res2), sqrt(dA2 / a2), sqrt(ref2diff / ref2)}
-// and g1 <- ||gamma_new||_1 for the next iteration.
-__device__ void fista_stats(const StatsJob& job, double* red, double* upd) {
-    block_reduce_cols(job.res_part, job.res_nblk, 1, job.res2_out, red, upd + 5);
-    block_reduce_cols(job.part, job.nblk, 5, job.upd_out, red, upd);
-    if (threadIdx.x != 0) return;
-    const double r2 = upd[5];
-    double* st = job.stats + 4 * (int64_t)job.k;
-    st[0] = 0.5 * r2 + job.lam * job.g1[0];
-    st[1] = sqrt(r2);
-    st[2] = upd[3] > 0.0 ? sqrt(upd[2] / upd[3]) : 0.0;
-    st[3] = job.have_ref ? sqrt(upd[4] / job.ref2) : 0.0;
-    job.g1[0] = upd[1];
 }
 
 __global__ __launch_bounds__(kThreads) void reduce_fista_stats_kernel(StatsJob job) {

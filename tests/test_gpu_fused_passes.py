@@ -1,5 +1,5 @@
-"""FISTA's fused passes (forward post + adjoint pre, the update in the transform
-path's last product, statistics reduced one iteration late) against the same
+"""FISTA's fused passes (forward post + adjoint pre, the update between the transform
+path's products, statistics reduced one iteration late) against the same
 iterations from the operator calls and an FP64 update: one to eight lanes per
 sum, union rows with unselected bins, BF16 operands, odd sizes, one position,
 and a grid with more blocks of partials than the fused update has room for."""
@@ -38,6 +38,12 @@ def dev():
     ("fft", False, 1, 1, 12, 3, False, -1, False, True, 3),
     ("fft", False, 130, 2, 7, 2, True, 4, False, False, 2),        # more than one block of rows
     ("fft", False, 1024, 1, 832, 2, False, 0, False, True, 2),     # partials past the fused update's room
+    ("fft", False, 150, 100, 5, 2, True, 1, False, True, 3),       # more than 64 rows: a kernel per product
+    ("fft", False, 10, 64, 6, 20, True, 3, False, True, 3),        # the most rows of one column
+    ("fft", False, 9, 65, 6, 20, True, 3, False, False, 3),        # one more
+    ("fft", False, 5, 47, 20, 19, False, -1, True, True, 2),       # three tiles of rows
+    ("fft", False, 16, 16, 17, 40, True, -1, True, True, 3),       # exactly one tile per axis
+    ("fft", True, 40, 33, 9, 3, True, 5, False, False, 2),         # several tiles, transforms past one staged run
 ])
 def test_fista_matches_the_operator_calls(algo, bf16, nx, ny, nz, m, per, win, real, ref, iters, dev):
     from paper_2012_04534_amd import ufss as u

@@ -66,6 +66,28 @@ def test_transform_paths(nx, ny, nz, m, win, beam, bf16, dev):
     check(plan, O.dense_A(g, bins), g, m, TOL16 if bf16 else TOL32, dev)
 
 
+@pytest.mark.parametrize("nx,ny,nz,m,win,per", [(17, 90, 35, 13, 1, True), (97, 101, 3, 2, 2, False),
+                                                (40, 64, 20, 18, 5, True), (64, 64, 33, 5, -1, False)])
+def test_rows_past_one_column_match_the_windowed_products(nx, ny, nz, m, win, per, dev):
+    """Around and past the 64 rows that one wave holds: the same operator as the
+    windowed GEMM, each within its bound."""
+    from paper_2012_04534_amd import ufss as u
+    g = W.geometry(nx, ny, nz, 1024, win_x=win, win_y=win)
+    bins, _ = u.ufss_select_freqs(g, m, per, 3 + m)
+    x = torch.from_numpy(W.cn((ny, nx, nz), 21).astype(np.complex64)).to(dev)
+    r = torch.from_numpy(W.cn((ny, nx, m), 22).astype(np.complex64)).to(dev)
+    got = []
+    for algo in (u.ALGO_FFT, u.ALGO_GEMM):
+        plan = u.Plan(g, m, per, bins, algo=algo)
+        yo, xo = torch.empty_like(r), torch.empty_like(x)
+        u.ufss_forward(plan, x, yo)
+        u.ufss_adjoint(plan, r, xo)
+        got.append((yo.cpu().numpy().reshape(-1), xo.cpu().numpy().reshape(-1)))
+        plan.close()
+    assert errs(got[0][0], got[1][0]) < 2 * TOL32
+    assert errs(got[0][1], got[1][1]) < 2 * TOL32
+
+
 @pytest.mark.parametrize("nt,m", [(32, 1), (64, 3), (64, 32), (128, 128), (32, 16)])
 def test_mixing_lanes_per_measurement(nt, m, dev):
     from paper_2012_04534_amd import ufss as u
