@@ -218,10 +218,10 @@ struct Orbit {
 // or the last reduction entry load some other finite entry (the table is
 // followed by zeros), which meets a zero column or a row that is not stored.
 //
-// Per launch, forward / adjoint, before (quadrant, vector FMAs) and after: 64 x
-// 64 x 512 (128 bins, W = 16) 181 / 176 -> 96 / 100 us (4.7 TB/s of table), 32 x
-// 32 x 256 (66 bins, full) 27.5 / 27.3 -> 20.4 / 22.9, 50 x 50 x 50 (256 bins) 53 /
-// 52 -> 29 / 27; unequal axes (45 x 51 x 301, 76 bins) 45 / 51 -> 39 / 43.
+// Per launch, forward / adjoint, before (quadrant, vector FMAs) and now: 64 x
+// 64 x 512 (128 bins, W = 16) 181 / 176 -> 94 / 100 us (4.8 TB/s of table), 32 x
+// 32 x 256 (66 bins, full) 27.5 / 27.3 -> 17.6 / 19.7, 50 x 50 x 50 (256 bins) 53 /
+// 52 -> 28 / 26.5; unequal axes (45 x 51 x 301, 76 bins) 45 / 51 -> 35 / 38.
 static constexpr int kPD = 2;
 static constexpr int kNW = 4;
 static constexpr int kRC = 512;
@@ -590,21 +590,28 @@ void fft_setup(Plan& P) {
     release();
 }
 
-// One contraction launch: tiles per wave by the number of outputs (forward: up
-// to 3 blocks of 32, as few padded ones as possible; adjoint: up to 2 tiles of
-// 16), at most kNW groups per workgroup (one per wave), fewer while the grid has
-// under 512 workgroups (the waves then share the reduction).
+// One contraction launch.  Tiles per wave: forward one block of 32 outputs where a
+// workgroup has a wave for each, else two (BF16 tables, half the bytes per load: up to
+// 3, as few padded ones as possible); adjoint up to 2 tiles of 16.  Groups per
+// workgroup: at most kNW, one per wave (adjoint 2, so that two waves share a reduction),
+// fewer while the grid has too few workgroups to spread evenly over 256 CUs: with 528 of
+// 3 blocks each, the busiest CU had 3 of them for a mean of 2.
+// Forward / adjoint, with 3 blocks per wave, 4 groups and 512 workgroups -> so: 32 x 32 x
+// 256, 66 bins 20.3 / 22.5 -> 17.6 / 19.7 us; 45 x 51 x 301, 76 bins 38.7 / 41.7 -> 35.0 /
+// 37.8 (BF16 32.0 / 33.8 -> 32.0 / 29.2); 64 x 64 x 512, 132 bins 100 / 105 -> 93 / 104.
 template <bool FWD, bool SWAP, typename TT>
 static void contract(const Plan& P, hipStream_t s) {
     const int mu = (int)P.ubins_h.size(), nz = P.g.nz;
     const int C = FWD ? mu : nz, R = FWD ? nz : mu;
     const int blocks = (C + group_rows(FWD, 1) - 1) / group_rows(FWD, 1);
-    int tb = std::min(blocks, FWD ? 3 : 2);
+    constexpr bool f32 = std::is_same<TT, cf32>::value;
+    int tb = std::min(blocks, FWD && !f32 ? 3 : 2);
     for (int t = tb - 1; t >= 2; --t)
         if ((blocks + t - 1) / t * t < (blocks + tb - 1) / tb * tb) tb = t;
+    if (FWD && f32 && blocks <= kNW) tb = 1;
     const int all = (blocks + tb - 1) / tb, gr = group_rows(FWD, tb);
-    int g = std::min(all, kNW);
-    while (g > 1 && P.fft_entries * ((all + g - 1) / g) < 512) --g;
+    int g = std::min(all, FWD ? kNW : 2);
+    while (g > 1 && P.fft_entries * ((all + g - 1) / g) < (!FWD ? 512 : f32 ? 768 : 1024)) --g;
     const dim3 grid(P.fft_entries, (all + g - 1) / g);
     const int rs = (SWAP ? 16 : 8) + 2;
     const size_t cols = (size_t)(std::min(R, kRC) + step_len(FWD)) * rs;
@@ -619,7 +626,7 @@ static void contract(const Plan& P, hipStream_t s) {
     };
     if (tb == 1) go(std::integral_constant<int, 1>{});
     else if (tb == 2) go(std::integral_constant<int, 2>{});
-    else if constexpr (FWD) go(std::integral_constant<int, 3>{});
+    else if constexpr (FWD && !f32) go(std::integral_constant<int, 3>{});
     UFSS_HIP(hipGetLastError());
 }
 
