@@ -45,11 +45,12 @@ static int nblk(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(
 // of a neighbour row (e_y, e_z) serve the 3 XV products of each weight, and a
 // weight read from LDS serves the whole run.  The channel count is a template
 // constant (accumulators in registers).  What bounds them is the latency of the
-// neighbour loads, a row at a time.  32 x 32 x 256, 8 channels, before (one voxel
-// per thread, run-time channel count) and after: conv1 46 -> 10.6 us, conv2 17 + 5
-// (the extrapolation's own pass) -> 15.9, their transposes 52 -> 13.7 and 17 ->
-// 14.7; rows unrolled by 3 leave too few registers (conv2 23).
-static constexpr int kXC = 2;            // the convolutions: more, shorter runs (4: 14-20 us, latency shows)
+// neighbour loads: a row is loaded in straight line while the one before it is used.
+// 32 x 32 x 256, 8 channels, before (one voxel per thread, run-time channel count), with
+// a row at a time and so: conv1 46, 10.6, 9.9 us, conv2 17 + 5 (the extrapolation's own
+// pass), 15.9, 14.1, their transposes 52, 13.7, 12.8 and 17, 14.7, 13.1.  (The same ahead
+// with a branch per column waits at each join: conv2 19.)
+static constexpr int kXC = 2;            // the convolutions: more, shorter runs (4: 14-20 us; 1: 12-16)
 static constexpr int kXW = 4;            // the weight gradients: more products per load (2: 22 us)
 
 struct Run {
@@ -92,6 +93,30 @@ __device__ __forceinline__ void row_values(const Dims& d, const Run& r, bool in,
         v[k] = T{};
         if (in && x >= 0 && x < d.nx) v[k] = at(off + (int64_t)(k - 1) * d.nz);
     }
+}
+
+// The columns x - 1 .. x + XV of a run with their loads in straight line, a row ahead:
+// a voxel outside the grid is replaced by its nearest one inside, and by zero after the
+// load.
+template <int XV>
+struct RunColumns {
+    int64_t at[XV + 2];     // nearest voxel of column k at the run's (y, z)
+    bool ok[XV + 2];
+    __device__ RunColumns(const Dims& d, const Run& r) {
+#pragma unroll
+        for (int k = 0; k < XV + 2; ++k) {
+            const int x = r.x + k - 1;
+            ok[k] = x >= 0 && x < d.nx;
+            at[k] = ((int64_t)r.y * d.nx + min(max(x, 0), d.nx - 1)) * d.nz + r.z;
+        }
+    }
+};
+// Offset to the row's nearest row inside, and whether it is the row itself.
+__device__ __forceinline__ bool row_offset(const Dims& d, const Run& r, int row, int64_t& o) {
+    const int y = r.y + row / 3 - 1, z = r.z + row % 3 - 1;
+    const int yc = min(max(y, 0), d.ny - 1), zc = min(max(z, 0), d.nz - 1);
+    o = (int64_t)(yc - r.y) * d.nx * d.nz + (zc - r.z);
+    return yc == y && zc == z;
 }
 
 // --- forward kernels ---------------------------------------------------------
@@ -149,12 +174,22 @@ __global__ __launch_bounds__(kLT) void k_conv1(Dims d, const cf32* __restrict__ 
         for (int k = 0; k < kXC; ++k)
 #pragma unroll
             for (int o = 0; o < CH; ++o) acc[k][o] = b1[o];
+        const RunColumns<kXC> col(d, r);
+        cf32 v[kXC + 2], next[kXC + 2];
+        bool in = false, in_next;
+        auto load = [&](int row) {
+            int64_t off;
+            in_next = row_offset(d, r, row, off);
+#pragma unroll
+            for (int k = 0; k < kXC + 2; ++k) next[k] = u[col.at[k] + off];
+        };
+        load(0);
 #pragma unroll 1
         for (int row = 0; row < 9; ++row) {
-            int64_t off;
-            const bool in = row_inside(d, r, row, off);
-            cf32 v[kXC + 2];
-            row_values(d, r, in, off, [&](int64_t at) { return u[r.v + at]; }, v);
+            in = in_next;
+#pragma unroll
+            for (int k = 0; k < kXC + 2; ++k) v[k] = in && col.ok[k] ? next[k] : cf32{0.f, 0.f};
+            load(min(row + 1, 8));
 #pragma unroll
             for (int k = 0; k < kXC + 2; ++k) v[k] = cf32{v[k].re * ic, v[k].im * ic};
 #pragma unroll
@@ -196,14 +231,29 @@ __global__ __launch_bounds__(kLT) void k_conv2(Dims d, const float* __restrict__
             ar[k] = b2[0];
             ai[k] = b2[1];
         }
+        const RunColumns<kXC> col(d, r);
+        float cur[CH][kXC + 2], next[CH][kXC + 2];
+        bool in = false, in_next;
+        auto load = [&](int row) {
+            int64_t off;
+            in_next = row_offset(d, r, row, off);
+#pragma unroll
+            for (int k = 0; k < kXC + 2; ++k)
+#pragma unroll
+                for (int p = 0; p < CH; ++p) next[p][k] = (h + p * d.n)[col.at[k] + off];
+        };
+        load(0);
 #pragma unroll 1
         for (int row = 0; row < 9; ++row) {
-            int64_t off;
-            const bool in = row_inside(d, r, row, off);
+            in = in_next;
+#pragma unroll
+            for (int p = 0; p < CH; ++p)
+#pragma unroll
+                for (int k = 0; k < kXC + 2; ++k) cur[p][k] = in && col.ok[k] ? next[p][k] : 0.f;
+            load(min(row + 1, 8));
 #pragma unroll
             for (int c = 0; c < CH; ++c) {
-                float v[kXC + 2];
-                row_values(d, r, in, off, [&](int64_t at) { return h[(int64_t)c * d.n + r.v + at]; }, v);
+                const float (&v)[kXC + 2] = cur[c];
 #pragma unroll
                 for (int e = 0; e < 3; ++e) {
                     const float2 a = w[(row * 3 + e) * CH + c];
@@ -268,12 +318,27 @@ __global__ __launch_bounds__(kLT) void k_conv2_bwd(Dims d, const cf32* __restric
         for (int k = 0; k < kXC; ++k)
 #pragma unroll
             for (int c = 0; c < CH; ++c) acc[k][c] = 0.f;
+        float hv[CH][kXC];
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+#pragma unroll
+            for (int k = 0; k < kXC; ++k) hv[c][k] = (h + c * d.n)[r.v + min(k, d.nx - 1 - r.x) * nz];
+        const RunColumns<kXC> col(d, r);
+        cf32 v[kXC + 2], next[kXC + 2];
+        bool in = false, in_next;
+        auto load = [&](int row) {
+            int64_t off;
+            in_next = row_offset(d, r, row, off);
+#pragma unroll
+            for (int k = 0; k < kXC + 2; ++k) next[k] = dx[col.at[k] + off];
+        };
+        load(0);
 #pragma unroll 1
         for (int row = 0; row < 9; ++row) {
-            int64_t off;
-            const bool in = row_inside(d, r, row, off);
-            cf32 v[kXC + 2];
-            row_values(d, r, in, off, [&](int64_t at) { return dx[r.v + at]; }, v);
+            in = in_next;
+#pragma unroll
+            for (int k = 0; k < kXC + 2; ++k) v[k] = in && col.ok[k] ? next[k] : cf32{0.f, 0.f};
+            load(min(row + 1, 8));
 #pragma unroll
             for (int e = 0; e < 3; ++e)
 #pragma unroll
@@ -289,7 +354,7 @@ __global__ __launch_bounds__(kLT) void k_conv2_bwd(Dims d, const cf32* __restric
             for (int k = 0; k < kXC; ++k)
                 if (r.x + k < d.nx) {
                     const int64_t o = (int64_t)c * d.n + r.v + k * nz;
-                    dh[o] = h[o] > 0.f ? acc[k][c] : 0.f;
+                    dh[o] = hv[c][k] > 0.f ? acc[k][c] : 0.f;
                 }
     }
 }
@@ -308,14 +373,29 @@ __global__ __launch_bounds__(kLT) void k_conv1_bwd(Dims d, const float* __restri
         float ar[kXC], ai[kXC];
 #pragma unroll
         for (int k = 0; k < kXC; ++k) ar[k] = ai[k] = 0.f;
+        const RunColumns<kXC> col(d, r);
+        float cur[CH][kXC + 2], next[CH][kXC + 2];
+        bool in = false, in_next;
+        auto load = [&](int row) {
+            int64_t off;
+            in_next = row_offset(d, r, row, off);
+#pragma unroll
+            for (int k = 0; k < kXC + 2; ++k)
+#pragma unroll
+                for (int p = 0; p < CH; ++p) next[p][k] = (dh + p * d.n)[col.at[k] + off];
+        };
+        load(0);
 #pragma unroll 1
         for (int row = 0; row < 9; ++row) {
-            int64_t off;
-            const bool in = row_inside(d, r, row, off);
+            in = in_next;
+#pragma unroll
+            for (int p = 0; p < CH; ++p)
+#pragma unroll
+                for (int k = 0; k < kXC + 2; ++k) cur[p][k] = in && col.ok[k] ? next[p][k] : 0.f;
+            load(min(row + 1, 8));
 #pragma unroll
             for (int o = 0; o < CH; ++o) {
-                float v[kXC + 2];
-                row_values(d, r, in, off, [&](int64_t at) { return dh[(int64_t)o * d.n + r.v + at]; }, v);
+                const float (&v)[kXC + 2] = cur[o];
 #pragma unroll
                 for (int e = 0; e < 3; ++e) {
                     const float2 a = w[(row * 3 + e) * CH + o];
