@@ -170,6 +170,8 @@ int op_residual(Plan& P, const cf32* x, const cf32* ymeas, double* part, const S
     return launch_post_pre(P, ymeas, part, job, s);
 }
 
+void op_adjoint_spectrum(Plan& P, hipStream_t s) { fft_adjoint_core(P, s); }
+
 int op_adjoint_residual(Plan& P, cf32* x, hipStream_t s, bool defer_sum) {
     return post_pre_ok(P) ? adjoint_core(P, x, s, defer_sum) : op_adjoint(P, P.d_r, x, s, defer_sum);
 }

@@ -648,6 +648,7 @@ static void contract(const Plan& P, hipStream_t s) {
 //   kPost   IDFT_y -> times H (- ymeas) -> measurements
 //   kBins   IDFT_y -> H^2 and - H ymeas -> DFT_y       (A x - y on its way to R^)
 //   kDepth  IDFT_y -> FISTA update -> DFT_y            (X' on its way to the next X^)
+//   kProx   IDFT_y -> a learned stage's gradient and proximal step
 // What bounds it: launches and latencies.  On a small scan each product and each
 // pass takes 4-6 us as a kernel of its own, of which its arithmetic is under 1 us;
 // a FISTA iteration goes from 11 launches to 8.  (A whole plane in LDS, both axes
@@ -663,7 +664,7 @@ static void contract(const Plan& P, hipStream_t s) {
 // it (8.8 and 11.8 with all tiles in one wave); an apply pair of 45 x 51 x 301 (BF16
 // table) 139 -> 133 us with one launch less per operator.
 // ---------------------------------------------------------------------------
-enum { kPre, kPost, kBins, kDepth };
+enum { kPre, kPost, kBins, kDepth, kProx };
 
 struct ColumnArgs {
     const cf32* in;                           // [ly][nx][C], or the measurements (kPre)
@@ -679,6 +680,7 @@ struct ColumnArgs {
     // kDepth
     UpdateArgs upd;
     int more;
+    ProxArgs prox;
     StatsJob job;                             // kBins: by the last block
 };
 
@@ -706,7 +708,7 @@ __host__ __device__ constexpr int column_units(int nt) { return nt == 1 ? 4 : nt
 template <int NT, int MODE>
 __global__ __launch_bounds__(256) void column_kernel(ColumnArgs g) {
     constexpr int UN = column_units(NT), NW = 4 / UN;         // waves per unit
-    constexpr bool kIv = MODE != kPre, kFw = MODE != kPost;
+    constexpr bool kIv = MODE != kPre, kFw = MODE != kPost && MODE != kProx, kMeas = MODE != kDepth && MODE != kProx;
     __shared__ __align__(16) double smem[MODE == kBins ? kStatsRed + 6 : UN * NT * 256];
     __shared__ double red[5 * 4];
     if (MODE == kBins && (int)blockIdx.x * UN >= g.units) {
@@ -757,7 +759,7 @@ __global__ __launch_bounds__(256) void column_kernel(ColumnArgs g) {
     int mi[4];
     cf32 q[4], v[4];
     float h = 0.f;
-    if constexpr (MODE != kDepth) {
+    if constexpr (kMeas) {
         if (ok) h = g.hu[c];
 #pragma unroll
         for (int r = 0; r < 4; ++r) mi[r] = ok && mine && i0 + r < ny ? (g.inv ? g.inv[pos(r) * C + c] : c) : -1;
@@ -772,8 +774,8 @@ __global__ __launch_bounds__(256) void column_kernel(ColumnArgs g) {
         for (int r = 0; r < 4; ++r) {
             q[r] = v[r] = cf32{0.f, 0.f};
             if (!ok || !mine || i0 + r >= ny) continue;
-            q[r] = g.upd.gamma[pos(r) * C + c];
-            v[r] = g.upd.a[pos(r) * C + c];
+            q[r] = (MODE == kProx ? g.prox.gam : g.upd.gamma)[pos(r) * C + c];
+            if (MODE == kDepth) v[r] = g.upd.a[pos(r) * C + c];
         }
     }
     f4v acc[2] = {f4v{0.f, 0.f, 0.f, 0.f}, f4v{0.f, 0.f, 0.f, 0.f}};
@@ -793,6 +795,21 @@ __global__ __launch_bounds__(256) void column_kernel(ColumnArgs g) {
                 acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(u.a.im, orr, acc[1], 0, 0, 0);
             }
         }
+    }
+    if constexpr (MODE == kProx) {
+        const float st = g.prox.step(), th = g.prox.threshold();
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            if (!ok || !mine || i0 + r >= ny) continue;
+            const int64_t at = pos(r) * C + c;
+            const cf32 b{acc[0][r], acc[1][r]};
+            cf32 z, u;
+            prox_step(q[r], b, st, th, z, u);
+            if (g.prox.g) g.prox.g[at] = b;
+            g.prox.z[at] = z;
+            g.prox.u[at] = u;
+        }
+        return;
     }
     double sum[MODE == kDepth ? 5 : 1] = {};
 #pragma unroll
@@ -939,6 +956,13 @@ int fft_residual(const Plan& P, const cf32* ymeas, double* part, const StatsJob&
     const int nb = column<kBins>(P, P.d_ft, P.d_ft, mu, g, s);
     forward_x(P, mu, s);
     return nb;
+}
+
+void fft_prox(const Plan& P, const ProxArgs& a, hipStream_t s) {
+    ColumnArgs g{};
+    g.prox = a;
+    inverse_x(P, P.g.nz, s);
+    column<kProx>(P, P.d_ft, nullptr, P.g.nz, g, s);
 }
 
 int fft_update(const Plan& P, const UpdateArgs& u, bool more, hipStream_t s) {

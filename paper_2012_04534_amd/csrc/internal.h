@@ -340,6 +340,24 @@ __device__ __forceinline__ void fista_step(cf32 gm, cf32 aa, cf32 gg, float step
         acc[4] += er * er + ei * ei;
     }
 }
+// A learned stage's gradient step z = gam - s g and proximal step u = soft(z, th), with
+// s = exp(par[0]) / L and th = exp(par[1]) lam / L; g is kept if given.
+struct ProxArgs {
+    const cf32* gam = nullptr;
+    const float* par = nullptr;
+    float invL = 0.f;
+    const double* lam = nullptr;
+    cf32 *g = nullptr, *z = nullptr, *u = nullptr;
+    __device__ float step() const { return expf(par[0]) * invL; }
+    __device__ float threshold() const { return expf(par[1]) * (float)lam[0] * invL; }
+};
+__device__ __forceinline__ void prox_step(cf32 a, cf32 b, float s, float th, cf32& z, cf32& u) {
+    const float zr = a.re - s * b.re, zi = a.im - s * b.im;
+    const float mag = sqrtf(zr * zr + zi * zi);
+    const float sc = mag > th ? 1.0f - th / mag : 0.0f;
+    z = cf32{zr, zi};
+    u = cf32{zr * sc, zi * sc};
+}
 // The FISTA update of launch_update applied to A^H's result as it is formed
 // (transform plans): x and gamma in place, 5 FP64 partials per block.
 struct UpdateArgs {
@@ -354,12 +372,14 @@ struct UpdateArgs {
 // in one kernel with the lateral products along y.  fft_post: Y^ -> y = A x (- ymeas),
 // partials of ||y||^2 (count returned); fft_pre: r -> R^; fft_residual: Y^ -> R^ of
 // A x - ymeas (with partials, and an earlier iteration's statistics by one more block);
-// fft_update: X' -> the FISTA update and, if more, X^ of the new gamma.
+// fft_update: X' -> the FISTA update and, if more, X^ of the new gamma; fft_prox: X' ->
+// a learned stage's proximal step.
 bool fft_fused(const Plan& P);
 int fft_post(const Plan& P, cf32* y, const cf32* ymeas, double* part, hipStream_t s);
 void fft_pre(const Plan& P, const cf32* r, hipStream_t s);
 int fft_residual(const Plan& P, const cf32* ymeas, double* part, const StatsJob& job, hipStream_t s);
 int fft_update(const Plan& P, const UpdateArgs& u, bool more, hipStream_t s);
+void fft_prox(const Plan& P, const ProxArgs& a, hipStream_t s);
 
 // Random mixing passes (vec.hip): they replace launch_forward_post and
 // launch_adjoint_pre on mixed plans.
@@ -390,6 +410,8 @@ int op_adjoint(Plan& P, const cf32* y, cf32* x, hipStream_t s, bool defer_sum = 
 // whose passes cannot be fused, op_forward_partials and op_adjoint through P.d_r.
 // Returns the partial blocks of ||A x - ymeas||^2 in part.
 int op_residual(Plan& P, const cf32* x, const cf32* ymeas, double* part, const StatsJob& job, hipStream_t s);
+// fft_fused plans: the contraction of what op_residual left, up to X'.
+void op_adjoint_spectrum(Plan& P, hipStream_t s);
 // The adjoint of what op_residual left; as op_adjoint.
 int op_adjoint_residual(Plan& P, cf32* x, hipStream_t s, bool defer_sum = false);
 

@@ -130,19 +130,14 @@ __global__ __launch_bounds__(kLT) void k_momentum(int64_t n, const cf32* __restr
 }
 
 // stage parameters at par: [rho, kappa, ...]
-__global__ __launch_bounds__(kLT) void k_prox(int64_t n, const cf32* __restrict__ gam,
-                                              const cf32* __restrict__ g, const float* __restrict__ par,
-                                              float invL, const double* __restrict__ lam,
-                                              cf32* __restrict__ z, cf32* __restrict__ u) {
-    const float s = expf(par[0]) * invL;
-    const float th = expf(par[1]) * (float)lam[0] * invL;
+// (transform plans: in the adjoint's last lateral product, fft_prox)
+__global__ __launch_bounds__(kLT) void k_prox(int64_t n, ProxArgs p) {
+    const float s = p.step(), th = p.threshold();
     for (int64_t i = (int64_t)blockIdx.x * kLT + threadIdx.x; i < n; i += (int64_t)gridDim.x * kLT) {
-        const cf32 a = gam[i], b = g[i];
-        const float zr = a.re - s * b.re, zi = a.im - s * b.im;
-        const float mag = sqrtf(zr * zr + zi * zi);
-        const float sc = mag > th ? 1.0f - th / mag : 0.0f;
-        z[i] = cf32{zr, zi};
-        u[i] = cf32{zr * sc, zi * sc};
+        cf32 z, u;
+        prox_step(p.gam[i], p.g[i], s, th, z, u);
+        p.z[i] = z;
+        p.u[i] = u;
     }
 }
 
@@ -766,8 +761,8 @@ static void with_channels(int ch, F f) {
     }
 }
 
-// Forward pass; activations kept for the backward pass.  Result in N.x[S].
-static void net_forward(Net& N, const cf32* y, hipStream_t s) {
+// Forward pass; with `keep`, all that the backward pass reads is kept.  Result in N.x[S].
+static void net_forward(Net& N, const cf32* y, bool keep, hipStream_t s) {
     Plan& P = *N.P;
     const int64_t n = P.nvox;
     const float invL = (float)(1.0 / N.L);
@@ -785,9 +780,15 @@ static void net_forward(Net& N, const cf32* y, hipStream_t s) {
     for (int i = 0; i < N.S; ++i) {
         const float* par = N.d_par + (int64_t)i * N.sn;
         op_residual(P, N.gam[i], y, P.d_part, StatsJob{}, s);
-        op_adjoint_residual(P, N.g[i], s);
-        hipLaunchKernelGGL(k_prox, dim3(nblk(n)), dim3(kLT), 0, s, n, N.gam[i], N.g[i], par, invL,
-                           N.d_lam, N.z[i], N.u[i]);
+        ProxArgs prox{N.gam[i], par, invL, N.d_lam, N.g[i], N.z[i], N.u[i]};
+        if (fft_fused(P)) {
+            op_adjoint_spectrum(P, s);
+            if (!keep) prox.g = nullptr;
+            fft_prox(P, prox, s);
+        } else {
+            op_adjoint_residual(P, N.g[i], s);
+            hipLaunchKernelGGL(k_prox, dim3(nblk(n)), dim3(kLT), 0, s, n, prox);
+        }
         const bool more = i + 1 < N.S;
         with_channels(ch, [&](auto chc) {
             constexpr int CH = decltype(chc)::value;
@@ -855,14 +856,14 @@ static void net_backward(Net& N, const cf32* aref, hipStream_t s) {
 
 void net_forward_out(Net& N, const cf32* y, cf32* x, hipStream_t s) {
     if (!y || !x) fail(UFSS_ERR_INVALID_ARG, "NULL buffer");
-    net_forward(N, y, s);
+    net_forward(N, y, false, s);
     launch_copy(N.P->nvox, N.x[N.S], x, s);
 }
 
 double net_grad(Net& N, const cf32* y, const cf32* aref, int accumulate, hipStream_t s) {
     if (!y || !aref) fail(UFSS_ERR_INVALID_ARG, "NULL buffer");
     if (!accumulate) UFSS_HIP(hipMemsetAsync(N.d_grad, 0, N.np * sizeof(float), s));
-    net_forward(N, y, s);
+    net_forward(N, y, true, s);
     net_backward(N, aref, s);
     double h[3];
     UFSS_HIP(hipMemcpyAsync(h, N.d_sc, 3 * sizeof(double), hipMemcpyDeviceToHost, s));

@@ -52,3 +52,29 @@ def test_shapes(nx, ny, nz, ch):
     assert np.linalg.norm(grad[idx] - fd) / np.linalg.norm(fd) < 1e-3
     net.close()
     plan.close()
+
+
+@pytest.mark.parametrize("nx,ny,nz", [(2, 17, 18), (5, 64, 3), (3, 65, 2), (20, 1, 33)])
+def test_transform_plan_shapes(nx, ny, nz):
+    """The proximal step in the transform path's last product: tiles of rows, the most
+    rows of one column and one more (a pass of its own), against the oracle network."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2012_04534_amd import ufss as u
+    dev, S, ch, shape, m = torch.device("cuda:0"), 2, 3, (ny, nx, nz), 4
+    g = W.geometry(nx, ny, nz, 64, win_x=1, win_y=1)
+    bins, _ = u.ufss_select_freqs(g, m, False, 3)
+    Am = O.dense_A(g, bins)
+    y = W.cn((ny, nx, m), 5).astype(np.complex64)
+    plan = u.Plan(g, m, False, bins, algo=u.ALGO_FFT)
+    L = u.ufss_lipschitz(plan)
+    net = u.Net(plan, stages=S, channels=ch, L=L, mu=0.1)
+    p = (0.05 * np.random.default_rng(8).standard_normal(S * N.stage_size(ch))).astype(np.float32)
+    u.ufss_unrolled_params(net, set_to=p)
+    x = torch.zeros(shape, dtype=torch.complex64, device=dev)
+    u.ufss_unrolled_forward(net, torch.from_numpy(y).to(dev), x)
+    xo = N.forward(lambda v: Am @ v, lambda v: Am.conj().T @ v, y.reshape(-1).astype(np.complex128),
+                   p.astype(np.float64), S, ch, L, 0.1, shape)
+    assert np.linalg.norm(x.cpu().numpy() - xo) / np.linalg.norm(xo) < 1e-5
+    net.close()
+    plan.close()
