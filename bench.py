@@ -46,19 +46,19 @@ PEAK_PHASOR_TERMS = 256 * 4 * 16 * 2.4e9 / PHASOR_SLOTS_PER_TERM
 # source it was measured on; a changed source or another tiling reports null.
 TRAFFIC = {
     # 32 x 32 C-scan, FP32 union-GEMM, shipped tiling (profiles/cscan32_fp32_gemm.md)
-    "cscan32/gemm/forward/fs12-zs8-nw4-np2-zc16": {"bytes": 55.414e6, "sha": "50773752df10ba5f"},
-    "cscan32/gemm/adjoint/as12-np2-kc16-nw8": {"bytes": 81.190e6, "sha": "50773752df10ba5f"},
+    "cscan32/gemm/forward/fs12-zs8-nw4-np4-zc16": {"bytes": 82.138e6, "sha": "b05960bd38ee0604"},
+    "cscan32/gemm/adjoint/as32-np4-kc8-nw4": {"bytes": 79.488e6, "sha": "b05960bd38ee0604"},
     # transform-domain contraction (profiles/cscan32_fp32_transform.md, cscan64_fp32_transform.md):
     # the table once plus the transform rows in and out
-    "cscan32/transform/forward/fs1-zs1-nw1-np0-zc0": {"bytes": 149.644e6, "sha": "b7d94652b869eec0"},
-    "cscan32/transform/adjoint/as1-np0-kc0-nw0": {"bytes": 149.143e6, "sha": "b7d94652b869eec0"},
-    "cscan64/transform/forward/fs1-zs1-nw1-np0-zc0": {"bytes": 914.074e6, "sha": "b7d94652b869eec0"},
-    "cscan64/transform/adjoint/as1-np0-kc0-nw0": {"bytes": 914.088e6, "sha": "b7d94652b869eec0"},
+    "cscan32/transform/forward/fs1-zs1-nw1-np0-zc0": {"bytes": 82.227e6, "sha": "d98f32cacb7275e8"},
+    "cscan32/transform/adjoint/as1-np0-kc0-nw0": {"bytes": 90.753e6, "sha": "d98f32cacb7275e8"},
+    "cscan64/transform/forward/fs1-zs1-nw1-np0-zc0": {"bytes": 484.325e6, "sha": "d98f32cacb7275e8"},
+    "cscan64/transform/adjoint/as1-np0-kc0-nw0": {"bytes": 530.796e6, "sha": "d98f32cacb7275e8"},
     # the same with the BF16 table (profiles/cscan32_bf16_transform.md, cscan64_bf16_transform.md)
-    "cscan32/transform-bf16/adjoint/as1-np0-kc0-nw0": {"bytes": 79.976e6, "sha": "b7d94652b869eec0"},
-    "cscan32/transform-bf16/forward/fs1-zs1-nw1-np0-zc0": {"bytes": 80.399e6, "sha": "b7d94652b869eec0"},
-    "cscan64/transform-bf16/adjoint/as1-np0-kc0-nw0": {"bytes": 473.501e6, "sha": "b7d94652b869eec0"},
-    "cscan64/transform-bf16/forward/fs1-zs1-nw1-np0-zc0": {"bytes": 473.507e6, "sha": "b7d94652b869eec0"},
+    "cscan32/transform-bf16/adjoint/as1-np0-kc0-nw0": {"bytes": 46.654e6, "sha": "d98f32cacb7275e8"},
+    "cscan32/transform-bf16/forward/fs1-zs1-nw1-np0-zc0": {"bytes": 46.140e6, "sha": "d98f32cacb7275e8"},
+    "cscan64/transform-bf16/adjoint/as1-np0-kc0-nw0": {"bytes": 304.915e6, "sha": "d98f32cacb7275e8"},
+    "cscan64/transform-bf16/forward/fs1-zs1-nw1-np0-zc0": {"bytes": 284.940e6, "sha": "d98f32cacb7275e8"},
     # BF16 GEMMs with phasor tables (profiles/cscan32_bf16_gemm.md, cscan64_bf16_gemm.md):
     # mostly re-reads of the table tiles, one per workgroup and offset (the
     # tables, 170 MB at 32 x 32, sit in the last-level cache); the 32 x 32
@@ -106,6 +106,28 @@ def window_terms(g, bins, per_pos):
     cy = np.array([min(p + wy, ny - 1) - max(p - wy, 0) + 1 for p in range(ny)])
     cx = np.array([min(p + wx, nx - 1) - max(p - wx, 0) + 1 for p in range(nx)])
     return int(cy.sum()) * int(cx.sum()) * bins.shape[-1] * g["nz"]
+
+
+def mirror_share(g):
+    """Offset classes (|d_x|, |d_y|) over window voxels: the FP32 GEMMs add the
+    voxels at mirrored offsets first and form one product for them."""
+    def axis(n, win):
+        w = n - 1 if win < 0 else min(win, n - 1)
+        p = np.arange(n)
+        voxels = np.minimum(p + w, n - 1) - np.maximum(p - w, 0) + 1
+        return np.minimum(w, np.maximum(p, n - 1 - p)).sum() + n, voxels.sum()
+    (fx, vx), (fy, vy) = axis(g["nx"], g["win_x"]), axis(g["ny"], g["win_y"])
+    return float(fx * fy) / float(vx * vy)
+
+
+def table_bytes(g, info, entry):
+    """The transform contraction's stored table: (ly/2+1)(lx/2+1) entries, with both
+    axes alike (where it is symmetric in them) one of each pair, by nz depths and the
+    union's bins padded to even, `entry` bytes each."""
+    nox, noy = [(g["n" + a] + info["win_" + a]) // 2 + 1 for a in "xy"]
+    alike = g["nx"] == g["ny"] and info["win_x"] == info["win_y"] and g["dx"] == g["dy"]
+    entries = nox * (nox + 1) // 2 if alike else nox * noy
+    return entries * g["nz"] * (info["union_size"] + info["union_size"] % 2) * entry
 
 
 def operator_outputs(ufss, W, g, w, bins, dev, tcfg):
@@ -555,6 +577,8 @@ def cscan64_rates(ufss, W, dev, ev_time, tcfg):
         tfl = 16.0 * cm / ((tf + ta) * 1e-3)
         out[tag] = {"forward_ms": round(tf, 3), "adjoint_ms": round(ta, 3),
                     "a_plus_ah_tflops": round(tfl / 1e12, 2), "frac_of_mfma_peak": round(tfl / peak, 4)}
+        if dt == ufss.F32:          # as the roofline's needed_frac
+            out[tag]["needed_frac"] = round(tfl * 0.75 * mirror_share(g) / peak, 4)
         p.close()
     out["fp32_transform"] = transform_rates(ufss, g, w["m"], False, bins, x, y, xo, ev_time, cm)
     return out
@@ -564,7 +588,7 @@ def transform_rates(ufss, g, m, per_pos, bins, x, y, xo, ev_time, cm):
     """The transform-domain operator (UFSS_ALGO_FFT) on the same problem: apply
     times, the direct-sum-equivalent rate (the same algorithmic count as the
     GEMM rows, so the two compare as times) and its contraction kernels against
-    HBM: each streams its table of (ly/2+1)(lx/2+1) nz mu complex64 once."""
+    HBM: each streams its table once."""
     p = ufss.Plan(g, m, per_pos, bins, algo=ufss.ALGO_FFT)
     tf = ev_time(lambda: ufss.ufss_forward(p, x, y), 3)
     ta = ev_time(lambda: ufss.ufss_adjoint(p, y, xo), 3)
@@ -572,7 +596,7 @@ def transform_rates(ufss, g, m, per_pos, bins, x, y, xo, ev_time, cm):
     ca = ufss.ufss_time_kernel(p, 1, 20)
     info = p.info()
     lx, ly = g["nx"] + info["win_x"], g["ny"] + info["win_y"]
-    tab = (ly // 2 + 1) * (lx // 2 + 1) * g["nz"] * info["union_size"] * 8
+    tab = table_bytes(g, info, 8)
     p.close()
     return {"forward_ms": round(tf, 4), "adjoint_ms": round(ta, 4),
             "direct_sum_equivalent_tflops": round(16.0 * cm / ((tf + ta) * 1e-3) / 1e12, 1),
@@ -829,11 +853,9 @@ def main():
     extras["kernel_launches_timed"] = {"forward": n_f, "adjoint": n_a}
     dom, k_ms = ("adjoint", k_a) if k_a >= k_f else ("forward", k_f)
     if algo == ufss.ALGO_FFT:
-        # the contraction streams its table of (ly/2+1)(lx/2+1) nz mu complex
-        # entries (8 bytes, 4 in BF16) once per launch: bound by HBM
-        pi = plan.info()
-        tab = ((g["ny"] + pi["win_y"]) // 2 + 1) * ((g["nx"] + pi["win_x"]) // 2 + 1) * g["nz"] * \
-            pi["union_size"] * (4 if bf16 else 8)
+        # the contraction streams its table of complex entries (8 bytes, 4 in
+        # BF16) once per launch: bound by HBM
+        tab = table_bytes(g, plan.info(), 4 if bf16 else 8)
         roof = {"bound": "hbm", "achieved": round(tab / (k_ms * 1e-3) / 1e9, 1),
                 "peak": PEAK_HBM / 1e9, "unit": "GB/s"}
     elif algo == ufss.ALGO_PHASOR:
@@ -845,6 +867,12 @@ def main():
     else:
         roof = {"bound": "mfma", "achieved": round(8.0 * cmac / (k_ms * 1e-3) / 1e12, 3),
                 "peak": (PEAK_BF16_MFMA if bf16 else PEAK_FP32_MFMA) / 1e12, "unit": "TFLOP/s"}
+        if not bf16:
+            # `achieved` counts the windowed sum; of its products the kernels form
+            # one per class of mirrored offsets, each in Gauss's three real products,
+            # so `frac` can pass 1: the share of the peak spent on products that
+            # the kernels need (no padding, no union bins) is `needed_frac`
+            roof["needed_frac"] = round(roof["achieved"] * 0.75 * mirror_share(g) / roof["peak"], 4)
     roof["frac"] = round(roof["achieved"] / roof["peak"], 4)
     pinfo = plan.info()
     roof["traffic"] = traffic_bytes(args.workload, algo_name, dom, pinfo) \

@@ -60,8 +60,9 @@ extern "C" {
                                correlation as a cyclic lateral transform of size
                                L >= N + W per axis, contracted over depth / bins
                                with a precomputed transformed kernel table
-                               ((ly/2+1)(lx/2+1) nz (union bins) complex, built
-                               in FP64, stored FP32, or BF16 for BF16 plans with
+                               (at most (ly/2+1)(lx/2+1) nz (union bins) complex,
+                               half where both axes are alike; built in FP64,
+                               stored FP32, or BF16 for BF16 plans with
                                transforms and sums still in FP32); shared or
                                per-position (over the union) subsets; no grouped
                                (batched) launches */

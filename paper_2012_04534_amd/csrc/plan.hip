@@ -406,9 +406,14 @@ Plan* plan_create(const ufss_geom* g, int m, int per_position, const int32_t* bi
     if (g->algo == UFSS_ALGO_AUTO && per_position && !mix && g->dtype == UFSS_F32) {
         // per-position subsets: the phasor path costs about one phasor per
         // selected bin and term, the union-GEMM one MFMA slot per union bin
-        // (padded) at several times the rate; measured on the 50x50x50
-        // replica the phasor path wins while the union has at least ~5x the
-        // bins of one position (n_f = 1, 2, 5 of a 37-bin union), the GEMM above
+        // (padded) and class of mirrored offsets at several times the rate.  A + A^H
+        // in us, phasor / GEMM, by union bins over one position's: 50 x 50 x 50 with a
+        // beam 18: 904 / 2489, 7.4: 1967 / 2458, 5.3: 2226 / 2466; 30 x 40 x 70 with a
+        // beam 7.4: 900 / 1061, 5.3: 1030 / 1058; without one 32 x 32 x 256 16: 1121 / 1814,
+        // 8.2: 1918 / 1818, 5.1: 3218 / 1820; 48 x 40 x 200 (W = 16) 25: 746 / 957, 13: 1172 / 953.
+        // The line holds for the beam; without one the two cross at 8 to 16, and it stays
+        // at 5 there too because what a plan may be used for (batches, tilings, windows)
+        // follows from its path.
         std::vector<int> uu(bins, bins + nsel);
         std::sort(uu.begin(), uu.end());
         const int64_t nu = std::unique(uu.begin(), uu.end()) - uu.begin();
