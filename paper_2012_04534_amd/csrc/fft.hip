@@ -211,7 +211,7 @@ struct Orbit {
 //   adjoint: lane l loads entries (z = l % 16, k = 16 s + 4 (l / 16) .. + 3): one
 //   tile of 16 rows, four steps of the reduction, 128 contiguous bytes per row
 // A workgroup of kNW waves takes one entry and a block of its outputs; a wave
-// takes one group of TB tiles (16-byte loads kPD steps ahead; 8-byte in BF16)
+// takes one group of TB tiles (16-byte loads kPD steps ahead)
 // and, where there are fewer groups than waves, a share of the reduction,
 // summed over the waves in LDS in fixed order.  Members are staged in LDS, kRC
 // reduction entries at a time, zero past the last; lanes past the last output
@@ -226,37 +226,22 @@ static constexpr int kPD = 2;
 static constexpr int kNW = 4;
 static constexpr int kRC = 512;
 
-template <typename TT> struct TabPair;
-template <> struct TabPair<cf32> {      // two FP32 entries
-    f4v v;
-    __device__ void load(const cf32* p) { v = *reinterpret_cast<const f4v*>(p); }
-    __device__ f4v get() const { return v; }
-};
-template <> struct TabPair<cbf16> {     // two BF16 entries (rounded to nearest even once at plan time)
-    uint2 v;
-    __device__ void load(const cbf16* p) { v = *reinterpret_cast<const uint2*>(p); }
-    __device__ f4v get() const {
-        return f4v{__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u),
-                   __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u)};
-    }
-};
-
 // Outputs of one group (TB tiles), and reduction entries of a step.
 __host__ __device__ constexpr int group_rows(bool fwd, int tb) { return (fwd ? 32 : 16) * tb; }
-__host__ __device__ constexpr int step_len(bool fwd) { return fwd ? 4 : 16; }
+__host__ __device__ constexpr int step_len(bool fwd, bool bf16) { return fwd && !bf16 ? 4 : 16; }
 
-template <bool FWD, int TB, bool SWAP, typename TT>
-__global__ __launch_bounds__(64 * kNW) void contract_kernel(const TT* __restrict__ tab, const int2* __restrict__ orbits,
+template <bool FWD, int TB, bool SWAP>
+__global__ __launch_bounds__(64 * kNW) void contract_kernel(const cf32* __restrict__ tab, const int2* __restrict__ orbits,
                                                        const cf32* __restrict__ in, cf32* __restrict__ out,
                                                        int ly, int lx, int nz, int mus, int C, int R, int groups) {
     extern __shared__ __align__(16) unsigned char smem[];
     float* xs = reinterpret_cast<float*>(smem);               // [kRC][RS] members' columns
     float* red = xs;                                          // [shares][16][rows + 1] after the reduction
     constexpr int NQ = SWAP ? 8 : 4, RS = 2 * NQ + 2;
-    constexpr int GR = group_rows(FWD, TB), ND = FWD ? 2 * TB : TB, ST = step_len(FWD), NL = FWD ? 1 : 2;
+    constexpr int GR = group_rows(FWD, TB), ND = FWD ? 2 * TB : TB, ST = step_len(FWD, false), NL = FWD ? 1 : 2;
     const Orbit orb(orbits[blockIdx.x], ly, lx, SWAP);
     const int nq = orb.n;
-    const TT* tb = tab + (int64_t)blockIdx.x * nz * mus;
+    const cf32* tb = tab + (int64_t)blockIdx.x * nz * mus;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int c0 = blockIdx.y * groups * GR;                  // first output of the block
     const int ng = min(groups, (C - c0 + GR - 1) / GR);       // its groups (1..kNW)
@@ -281,13 +266,13 @@ __global__ __launch_bounds__(64 * kNW) void contract_kernel(const TT* __restrict
 #pragma unroll
     for (int t = 0; t < TB; ++t)
         off[t] = FWD ? kq * mus + min(gc0 + 32 * t + 2 * i, mus - 2) : min(gc0 + 16 * t + i, nz - 1) * mus + 4 * kq;
-    TabPair<TT> buf[kPD][TB][NL];
-    auto load = [&](TabPair<TT> (&b)[TB][NL], int r0, int st) {
-        const TT* p = tb + (FWD ? (int64_t)(r0 + 4 * st) * mus : (int64_t)(r0 + 16 * st));
+    f4v buf[kPD][TB][NL];                                     // two entries each
+    auto load = [&](f4v (&b)[TB][NL], int r0, int st) {
+        const cf32* p = tb + (FWD ? (int64_t)(r0 + 4 * st) * mus : (int64_t)(r0 + 16 * st));
 #pragma unroll
         for (int t = 0; t < TB; ++t)
 #pragma unroll
-            for (int h = 0; h < NL; ++h) b[t][h].load(p + off[t] + 2 * h);
+            for (int h = 0; h < NL; ++h) b[t][h] = *reinterpret_cast<const f4v*>(p + off[t] + 2 * h);
     };
     for (int r0 = 0; r0 < R; r0 += kRC) {
         const int rc = min(kRC, R - r0), nst = (rc + ST - 1) / ST;
@@ -317,7 +302,7 @@ __global__ __launch_bounds__(64 * kNW) void contract_kernel(const TT* __restrict
                     const float b0 = xr[0], o0 = other(b0);
 #pragma unroll
                     for (int t = 0; t < TB; ++t) {
-                        const f4v a = buf[p][t][0].get();
+                        const f4v a = buf[p][t][0];
                         D[2 * t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b0, D[2 * t], 0, 0, 0);
                         D[2 * t + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, b0, D[2 * t + 1], 0, 0, 0);
                         D[2 * t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, o0, D[2 * t], 0, 0, 0);
@@ -329,7 +314,7 @@ __global__ __launch_bounds__(64 * kNW) void contract_kernel(const TT* __restrict
                         const float b0 = xr[2 * h * RS], b1 = xr[(2 * h + 1) * RS], o0 = other(b0), o1 = other(b1);
                         f4v a[TB];
 #pragma unroll
-                        for (int t = 0; t < TB; ++t) a[t] = buf[p][t][h].get();
+                        for (int t = 0; t < TB; ++t) a[t] = buf[p][t][h];
 #pragma unroll
                         for (int t = 0; t < TB; ++t) D[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t].x, b0, D[t], 0, 0, 0);
 #pragma unroll
@@ -363,6 +348,155 @@ __global__ __launch_bounds__(64 * kNW) void contract_kernel(const TT* __restrict
             re += red[(h * 16 + 2 * q) * pitch + c];
             im += red[(h * 16 + 2 * q + 1) * pitch + c];
         }
+        out[orb.row(q) * C + c0 + c] = cf32{re, im};
+    }
+}
+
+// The same on a BF16 table, with the BF16 matrix cores: v_mfma_f32_16x16x32_bf16
+// takes 16 reduction entries a step, (re, im) after one another as they lie in the
+// table, against columns that hold (Xre, -+Xim) for a real and (Xim, +-Xre) for an
+// imaginary part.  The FP32 members are cut into three BF16 parts (8 leading bits, the
+// next 8, the last 8: their sum is the member), so every product is exact and the sums
+// stay FP32; where an entry has at most 4 members, the first two parts share a product
+// (columns 0-7 and 8-15).  2 or 3 products of 16 cycles take the place of 8 FP32 ones
+// of 32, which bounded this kernel (its table is half the FP32 one's): forward / adjoint
+// 32 x 32 x 256, 66 bins 20.0 / 17.1 -> 12.8 / 13.9 us, 45 x 51 x 301, 76 bins 32.8 / 30.8 ->
+// 21.1 / 23.1 (4.7 / 4.3 TB/s of table), 64 x 64 x 512, 128 bins 57 / 60 -> 44 / 54.
+//   forward: lane l loads entries (z = 16 s + 4 (l / 16) .. + 3, k = 2 (l % 16), + 1) of
+//   32 outputs: two tiles, rows 2 i and 2 i + 1
+//   adjoint: lane l loads entries (z = l % 16, k = 16 s + 4 (l / 16) .. + 3)
+// Columns in LDS: plane, group of 4 entries, column, 4 entries of (re, im): one 16-byte
+// read per operand; groups padded by 16 bytes against bank conflicts of the staging.
+typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
+typedef unsigned int u4v __attribute__((ext_vector_type(4)));
+static constexpr int kRB = 256;                               // reduction entries staged at a time
+static constexpr int kGP = 16 * 16 + 16;                      // bytes of a group of 4 entries
+
+template <bool FWD, int TB, bool SWAP>
+__global__ __launch_bounds__(64 * kNW) void contract_bf16_kernel(const cbf16* __restrict__ tab, const int2* __restrict__ orbits,
+                                                       const cf32* __restrict__ in, cf32* __restrict__ out,
+                                                       int ly, int lx, int nz, int mus, int C, int R, int groups) {
+    static_assert(kRB == 64 * kNW, "a thread stages one reduction entry");
+    extern __shared__ __align__(16) unsigned char smem[];
+    float* red = reinterpret_cast<float*>(smem);              // [shares][16][rows + 1] after the reduction
+    constexpr int NQ = SWAP ? 8 : 4, NPL = SWAP ? 3 : 2;
+    constexpr int GR = group_rows(FWD, TB), ND = FWD ? 2 * TB : TB, ST = step_len(FWD, true), NL = FWD ? 4 : 2;
+    const Orbit orb(orbits[blockIdx.x], ly, lx, SWAP);
+    const int nq = orb.n;
+    const cbf16* tb = tab + (int64_t)blockIdx.x * nz * mus;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int c0 = blockIdx.y * groups * GR;                  // first output of the block
+    const int ng = min(groups, (C - c0 + GR - 1) / GR);       // its groups (1..kNW)
+    const int shares = kNW / ng;                              // waves per group
+    const int grp = wave % ng, share = wave / ng;
+    const bool active = share < shares;
+    const int i = lane & 15, kq = lane >> 4;
+    const int gc0 = c0 + grp * GR;
+
+    f4v D[ND];
+#pragma unroll
+    for (int t = 0; t < ND; ++t) D[t] = f4v{0.f, 0.f, 0.f, 0.f};
+    int off[TB];
+#pragma unroll
+    for (int t = 0; t < TB; ++t)
+        off[t] = FWD ? 4 * kq * mus + min(gc0 + 32 * t + 2 * i, mus - 2) : min(gc0 + 16 * t + i, nz - 1) * mus + 4 * kq;
+    uint2 buf[kPD][TB][NL];                                   // two entries each
+    auto load = [&](uint2 (&b)[TB][NL], int r0, int st) {
+        const cbf16* p = tb + (FWD ? (int64_t)(r0 + 16 * st) * mus : (int64_t)(r0 + 16 * st));
+#pragma unroll
+        for (int t = 0; t < TB; ++t)
+#pragma unroll
+            for (int h = 0; h < NL; ++h) b[t][h] = *reinterpret_cast<const uint2*>(p + off[t] + h * (FWD ? mus : 2));
+    };
+    for (int r0 = 0; r0 < R; r0 += kRB) {
+        const int rc = min(kRB, R - r0), nst = (rc + ST - 1) / ST;
+#pragma unroll
+        for (int p = 0; p < kPD; ++p)
+            if (active && share + p * shares < nst) load(buf[p], r0, share + p * shares);
+        if (r0 > 0) __syncthreads();                          // the previous chunk's columns are read
+        const int r = threadIdx.x;
+        if (r < nst * ST) {
+            unsigned char* dst = smem + (r >> 2) * kGP + (r & 3) * 4;
+            auto put = [&](int plane, int col, float a, float b) {       // the top halves of a and b
+                *reinterpret_cast<unsigned*>(dst + plane * (kRB / 4) * kGP + col * 16) =
+                    (__float_as_uint(a) >> 16) | (__float_as_uint(b) & 0xffff0000u);
+            };
+            auto top = [](float a) { return __uint_as_float(__float_as_uint(a) & 0xffff0000u); };
+            cf32 v[NQ];
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                v[q] = cf32{0.f, 0.f};
+                if (q < nq && r < rc) v[q] = in[orb.row(q) * R + r0 + r];
+            }
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                float re = v[q].re, im = v[q].im;
+#pragma unroll
+                for (int part = 0; part < 3; ++part) {
+                    const float tr = top(re), ti = top(im);
+                    const int plane = SWAP ? part : part >> 1, col = 2 * q + (SWAP ? 0 : 8 * (part & 1));
+                    put(plane, col, tr, FWD ? -ti : ti);
+                    put(plane, col + 1, ti, FWD ? tr : -tr);
+                    re -= tr;
+                    im -= ti;
+                }
+                if (!SWAP) {
+                    put(1, 8 + 2 * q, 0.f, 0.f);
+                    put(1, 9 + 2 * q, 0.f, 0.f);
+                }
+            }
+        }
+        __syncthreads();
+        if (!active) continue;
+        for (int st0 = share; st0 < nst; st0 += kPD * shares) {
+#pragma unroll
+            for (int p = 0; p < kPD; ++p) {
+                const int st = st0 + p * shares;
+                if (st >= nst) break;                         // wave-uniform
+                const unsigned char* src = smem + (4 * st + kq) * kGP + i * 16;
+                bf8v b[NPL], a[ND];
+#pragma unroll
+                for (int w = 0; w < NPL; ++w) b[w] = *reinterpret_cast<const bf8v*>(src + w * (kRB / 4) * kGP);
+#pragma unroll
+                for (int t = 0; t < TB; ++t) {
+                    const uint2* e = buf[p][t];
+                    if constexpr (FWD) {
+                        a[2 * t] = __builtin_bit_cast(bf8v, u4v{e[0].x, e[1].x, e[2].x, e[3].x});
+                        a[2 * t + 1] = __builtin_bit_cast(bf8v, u4v{e[0].y, e[1].y, e[2].y, e[3].y});
+                    } else {
+                        a[t] = __builtin_bit_cast(bf8v, u4v{e[0].x, e[0].y, e[1].x, e[1].y});
+                    }
+                }
+                // smallest parts first
+#pragma unroll
+                for (int w = NPL - 1; w >= 0; --w)
+#pragma unroll
+                    for (int t = 0; t < ND; ++t) D[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t], b[w], D[t], 0, 0, 0);
+                if (st + kPD * shares < nst) load(buf[p], r0, st + kPD * shares);
+            }
+        }
+    }
+    __syncthreads();                                          // the columns are read; red takes their place
+    const int rows = min(groups * GR, C - c0), pitch = ng * GR + 1;
+    if (active) {
+#pragma unroll
+        for (int t = 0; t < ND; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int lr = FWD ? 32 * (t >> 1) + 2 * (4 * kq + r) + (t & 1) : 16 * t + 4 * kq + r;
+                red[(share * 16 + i) * pitch + grp * GR + lr] = D[t][r];
+            }
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < nq * rows; t += 64 * kNW) {
+        const int q = t / rows, c = t - q * rows;
+        float re = 0.f, im = 0.f;
+        for (int h = 0; h < shares; ++h)
+#pragma unroll
+            for (int w = 0; w < (SWAP ? 1 : 2); ++w) {
+                re += red[(h * 16 + 8 * w + 2 * q) * pitch + c];
+                im += red[(h * 16 + 8 * w + 2 * q + 1) * pitch + c];
+            }
         out[orb.row(q) * C + c0 + c] = cf32{re, im};
     }
 }
@@ -558,7 +692,7 @@ void fft_setup(Plan& P) {
         UFSS_HIP(hipMalloc(&cx, hx.size() * sizeof(double)));
         UFSS_HIP(hipMalloc(&cy, hy.size() * sizeof(double)));
         // the contraction may load up to a step past the last entry's rows
-        const int64_t slack = 4 * P.fft_mus + 16;
+        const int64_t slack = 16 * P.fft_mus + 16;
         UFSS_HIP(hipMalloc(&P.d_khat, (P.fft_entries * row + slack) * tbytes1));
         UFSS_HIP(hipMemset(static_cast<char*>(P.d_khat) + P.fft_entries * row * tbytes1, 0, slack * tbytes1));
         P.ws_bytes += (P.fft_entries * row + slack) * (int64_t)tbytes1 + P.fft_entries * (int64_t)sizeof(int2);
@@ -593,36 +727,43 @@ void fft_setup(Plan& P) {
 // One contraction launch.  Tiles per wave: forward one block of 32 outputs where a
 // workgroup has a wave for each, else two (BF16 tables, half the bytes per load: up to
 // 3, as few padded ones as possible); adjoint up to 2 tiles of 16.  Groups per
-// workgroup: at most kNW, one per wave (adjoint 2, so that two waves share a reduction),
+// workgroup: at most kNW, one per wave (FP32 adjoint 2, so that two waves share a reduction),
 // fewer while the grid has too few workgroups to spread evenly over 256 CUs: with 528 of
 // 3 blocks each, the busiest CU had 3 of them for a mean of 2.
-// Forward / adjoint, with 3 blocks per wave, 4 groups and 512 workgroups -> so: 32 x 32 x
-// 256, 66 bins 20.3 / 22.5 -> 17.6 / 19.7 us; 45 x 51 x 301, 76 bins 38.7 / 41.7 -> 35.0 /
-// 37.8 (BF16 32.0 / 33.8 -> 32.0 / 29.2); 64 x 64 x 512, 132 bins 100 / 105 -> 93 / 104.
-template <bool FWD, bool SWAP, typename TT>
+// FP32, forward / adjoint, with 3 blocks per wave, 4 groups and 512 workgroups -> so: 32 x
+// 32 x 256, 66 bins 20.3 / 22.5 -> 17.6 / 19.7 us; 45 x 51 x 301, 76 bins 38.7 / 41.7 ->
+// 35.0 / 37.8; 64 x 64 x 512, 132 bins 100 / 105 -> 93 / 104.  BF16 by the FP32 rule -> so:
+// 12.8 / 15.3 -> 12.8 / 13.9; 21.1 / 23.5 -> 21.1 / 23.1; 57 / 57 -> 46 / 56.
+template <bool FWD, bool SWAP, bool BF16>
 static void contract(const Plan& P, hipStream_t s) {
     const int mu = (int)P.ubins_h.size(), nz = P.g.nz;
     const int C = FWD ? mu : nz, R = FWD ? nz : mu;
     const int blocks = (C + group_rows(FWD, 1) - 1) / group_rows(FWD, 1);
-    constexpr bool f32 = std::is_same<TT, cf32>::value;
+    constexpr bool f32 = !BF16;
     int tb = std::min(blocks, FWD && !f32 ? 3 : 2);
     for (int t = tb - 1; t >= 2; --t)
         if ((blocks + t - 1) / t * t < (blocks + tb - 1) / tb * tb) tb = t;
     if (FWD && f32 && blocks <= kNW) tb = 1;
     const int all = (blocks + tb - 1) / tb, gr = group_rows(FWD, tb);
-    int g = std::min(all, FWD ? kNW : 2);
-    while (g > 1 && P.fft_entries * ((all + g - 1) / g) < (!FWD ? 512 : f32 ? 768 : 1024)) --g;
+    int g = std::min(all, FWD || BF16 ? kNW : 2);
+    while (g > 1 && P.fft_entries * ((all + g - 1) / g) < (FWD && f32 ? 768 : 512)) --g;
     const dim3 grid(P.fft_entries, (all + g - 1) / g);
     const int rs = (SWAP ? 16 : 8) + 2;
-    const size_t cols = (size_t)(std::min(R, kRC) + step_len(FWD)) * rs;
+    const size_t cols = BF16 ? (size_t)(SWAP ? 3 : 2) * (kRB / 4) * kGP / sizeof(float)
+                             : (size_t)(std::min(R, kRC) + step_len(FWD, false)) * rs;
     size_t red = 0;                       // over the group counts a block may have
     for (int n : {g, all - (all - 1) / g * g}) red = std::max(red, (size_t)(kNW / n) * 16 * (n * gr + 1));
     const size_t lds = std::max(cols, red) * sizeof(float);
     auto go = [&](auto tbc) {
         constexpr int TB = decltype(tbc)::value;
-        hipLaunchKernelGGL((contract_kernel<FWD, TB, SWAP, TT>), grid, dim3(64 * kNW), lds, s,
-                           static_cast<const TT*>(P.d_khat), P.d_orb, P.d_fa, P.d_fb, P.fft_ly, P.fft_lx, nz,
-                           P.fft_mus, C, R, g);
+        if constexpr (BF16)
+            hipLaunchKernelGGL((contract_bf16_kernel<FWD, TB, SWAP>), grid, dim3(64 * kNW), lds, s,
+                               static_cast<const cbf16*>(P.d_khat), P.d_orb, P.d_fa, P.d_fb, P.fft_ly, P.fft_lx, nz,
+                               P.fft_mus, C, R, g);
+        else
+            hipLaunchKernelGGL((contract_kernel<FWD, TB, SWAP>), grid, dim3(64 * kNW), lds, s,
+                               static_cast<const cf32*>(P.d_khat), P.d_orb, P.d_fa, P.d_fb, P.fft_ly, P.fft_lx, nz,
+                               P.fft_mus, C, R, g);
     };
     if (tb == 1) go(std::integral_constant<int, 1>{});
     else if (tb == 2) go(std::integral_constant<int, 2>{});
@@ -633,9 +774,9 @@ static void contract(const Plan& P, hipStream_t s) {
 template <bool FWD>
 static void contract(const Plan& P, hipStream_t s) {
     if (P.dtype == UFSS_BF16) {
-        if (P.fft_swap) contract<FWD, true, cbf16>(P, s); else contract<FWD, false, cbf16>(P, s);
+        if (P.fft_swap) contract<FWD, true, true>(P, s); else contract<FWD, false, true>(P, s);
     } else {
-        if (P.fft_swap) contract<FWD, true, cf32>(P, s); else contract<FWD, false, cf32>(P, s);
+        if (P.fft_swap) contract<FWD, true, false>(P, s); else contract<FWD, false, false>(P, s);
     }
 }
 

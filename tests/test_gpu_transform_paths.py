@@ -55,6 +55,8 @@ def check(plan, A, g, m, tol, dev):
     (150, 1, 9, 4, -1, False),      # transform length 299: several staged runs of the lateral tables
     (520, 1, 5, 2, 3, False),       # more than 512 positions on an axis
     (1, 1, 12, 3, -1, False),       # one position
+    (6, 6, 257, 34, -1, False),     # one depth past a staged run of the BF16 contraction
+    (5, 3, 15, 17, 2, True),        # fewer depths than one of its steps, one bin past a step
 ])
 def test_transform_paths(nx, ny, nz, m, win, beam, bf16, dev):
     from paper_2012_04534_amd import ufss as u
@@ -64,6 +66,14 @@ def test_transform_paths(nx, ny, nz, m, win, beam, bf16, dev):
     bins, _ = u.ufss_select_freqs(g, m, False, 3 + m)
     plan = u.Plan(g, m, False, bins, dtype=u.BF16 if bf16 else u.F32, algo=u.ALGO_FFT)
     check(plan, O.dense_A(g, bins), g, m, TOL16 if bf16 else TOL32, dev)
+
+
+def test_bins_past_a_staged_run(dev):
+    """The BF16 contraction's adjoint stages 256 bins at a time."""
+    from paper_2012_04534_amd import ufss as u
+    g = W.geometry(4, 3, 20, 4096)
+    bins, _ = u.ufss_select_freqs(g, 260, False, 5)
+    check(u.Plan(g, 260, False, bins, dtype=u.BF16, algo=u.ALGO_FFT), O.dense_A(g, bins), g, 260, TOL16, dev)
 
 
 @pytest.mark.parametrize("nx,ny,nz,m,win,per", [(17, 90, 35, 13, 1, True), (97, 101, 3, 2, 2, False),
