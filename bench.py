@@ -50,15 +50,15 @@ TRAFFIC = {
     "cscan32/gemm/adjoint/as32-np4-kc8-nw4": {"bytes": 79.488e6, "sha": "b05960bd38ee0604"},
     # transform-domain contraction (profiles/cscan32_fp32_transform.md, cscan64_fp32_transform.md):
     # the table once plus the transform rows in and out
-    "cscan32/transform/forward/fs1-zs1-nw1-np0-zc0": {"bytes": 82.268e6, "sha": "eb86c9651dc7f492"},
-    "cscan32/transform/adjoint/as1-np0-kc0-nw0": {"bytes": 90.434e6, "sha": "eb86c9651dc7f492"},
-    "cscan64/transform/forward/fs1-zs1-nw1-np0-zc0": {"bytes": 484.321e6, "sha": "eb86c9651dc7f492"},
-    "cscan64/transform/adjoint/as1-np0-kc0-nw0": {"bytes": 530.789e6, "sha": "eb86c9651dc7f492"},
+    "cscan32/transform/forward/fs1-zs1-nw1-np0-zc0": {"bytes": 82.099e6, "sha": "0d6bade0c9430185"},
+    "cscan32/transform/adjoint/as1-np0-kc0-nw0": {"bytes": 90.289e6, "sha": "0d6bade0c9430185"},
+    "cscan64/transform/forward/fs1-zs1-nw1-np0-zc0": {"bytes": 484.320e6, "sha": "0d6bade0c9430185"},
+    "cscan64/transform/adjoint/as1-np0-kc0-nw0": {"bytes": 530.790e6, "sha": "0d6bade0c9430185"},
     # the same with the BF16 table (profiles/cscan32_bf16_transform.md, cscan64_bf16_transform.md)
-    "cscan32/transform-bf16/adjoint/as1-np0-kc0-nw0": {"bytes": 50.800e6, "sha": "eb86c9651dc7f492"},
-    "cscan32/transform-bf16/forward/fs1-zs1-nw1-np0-zc0": {"bytes": 46.165e6, "sha": "eb86c9651dc7f492"},
-    "cscan64/transform-bf16/adjoint/as1-np0-kc0-nw0": {"bytes": 278.596e6, "sha": "eb86c9651dc7f492"},
-    "cscan64/transform-bf16/forward/fs1-zs1-nw1-np0-zc0": {"bytes": 258.671e6, "sha": "eb86c9651dc7f492"},
+    "cscan32/transform-bf16/adjoint/as1-np0-kc0-nw0": {"bytes": 51.100e6, "sha": "0d6bade0c9430185"},
+    "cscan32/transform-bf16/forward/fs1-zs1-nw1-np0-zc0": {"bytes": 46.165e6, "sha": "0d6bade0c9430185"},
+    "cscan64/transform-bf16/adjoint/as1-np0-kc0-nw0": {"bytes": 278.593e6, "sha": "0d6bade0c9430185"},
+    "cscan64/transform-bf16/forward/fs1-zs1-nw1-np0-zc0": {"bytes": 258.671e6, "sha": "0d6bade0c9430185"},
     # BF16 GEMMs with phasor tables (profiles/cscan32_bf16_gemm.md, cscan64_bf16_gemm.md):
     # mostly re-reads of the table tiles, one per workgroup and offset (the
     # tables, 170 MB at 32 x 32, sit in the last-level cache); the 32 x 32

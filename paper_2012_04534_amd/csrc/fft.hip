@@ -225,6 +225,7 @@ struct Orbit {
 static constexpr int kPD = 2;
 static constexpr int kNW = 4;
 static constexpr int kRC = 512;
+static constexpr int kSeg = 32;          // steps per first-level sum (a multiple of kPD): shorter chains round less
 
 // Outputs of one group (TB tiles), and reduction entries of a step.
 __host__ __device__ constexpr int group_rows(bool fwd, int tb) { return (fwd ? 32 : 16) * tb; }
@@ -258,9 +259,9 @@ __global__ __launch_bounds__(64 * kNW) void contract_kernel(const cf32* __restri
         return sgn * __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(b), 0xB1, 0xf, 0xf, true));
     };
 
-    f4v D[ND];
+    f4v D[ND], sum[ND];                                       // of kSeg steps, of those before
 #pragma unroll
-    for (int t = 0; t < ND; ++t) D[t] = f4v{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < ND; ++t) D[t] = sum[t] = f4v{0.f, 0.f, 0.f, 0.f};
     // this lane's entries of step 0, and what a step and a tile add
     int off[TB];
 #pragma unroll
@@ -292,40 +293,47 @@ __global__ __launch_bounds__(64 * kNW) void contract_kernel(const cf32* __restri
         }
         __syncthreads();
         if (!active) continue;
-        for (int st0 = share; st0 < nst; st0 += kPD * shares) {
+        for (int sg = share; sg < nst; sg += kSeg * shares) {
+            for (int st0 = sg; st0 < min(nst, sg + kSeg * shares); st0 += kPD * shares) {
 #pragma unroll
-            for (int p = 0; p < kPD; ++p) {
-                const int st = st0 + p * shares;
-                if (st >= nst) break;                         // wave-uniform
-                const float* xr = xs + (FWD ? 4 * st + kq : 16 * st + 4 * kq) * RS + col;
-                if constexpr (FWD) {
-                    const float b0 = xr[0], o0 = other(b0);
+                for (int p = 0; p < kPD; ++p) {
+                    const int st = st0 + p * shares;
+                    if (st >= nst) break;                         // wave-uniform
+                    const float* xr = xs + (FWD ? 4 * st + kq : 16 * st + 4 * kq) * RS + col;
+                    if constexpr (FWD) {
+                        const float b0 = xr[0], o0 = other(b0);
 #pragma unroll
-                    for (int t = 0; t < TB; ++t) {
-                        const f4v a = buf[p][t][0];
-                        D[2 * t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b0, D[2 * t], 0, 0, 0);
-                        D[2 * t + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, b0, D[2 * t + 1], 0, 0, 0);
-                        D[2 * t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, o0, D[2 * t], 0, 0, 0);
-                        D[2 * t + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, o0, D[2 * t + 1], 0, 0, 0);
+                        for (int t = 0; t < TB; ++t) {
+                            const f4v a = buf[p][t][0];
+                            D[2 * t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b0, D[2 * t], 0, 0, 0);
+                            D[2 * t + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, b0, D[2 * t + 1], 0, 0, 0);
+                            D[2 * t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, o0, D[2 * t], 0, 0, 0);
+                            D[2 * t + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, o0, D[2 * t + 1], 0, 0, 0);
+                        }
+                    } else {
+#pragma unroll
+                        for (int h = 0; h < NL; ++h) {
+                            const float b0 = xr[2 * h * RS], b1 = xr[(2 * h + 1) * RS], o0 = other(b0), o1 = other(b1);
+                            f4v a[TB];
+#pragma unroll
+                            for (int t = 0; t < TB; ++t) a[t] = buf[p][t][h];
+#pragma unroll
+                            for (int t = 0; t < TB; ++t) D[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t].x, b0, D[t], 0, 0, 0);
+#pragma unroll
+                            for (int t = 0; t < TB; ++t) D[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t].y, o0, D[t], 0, 0, 0);
+#pragma unroll
+                            for (int t = 0; t < TB; ++t) D[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t].z, b1, D[t], 0, 0, 0);
+#pragma unroll
+                            for (int t = 0; t < TB; ++t) D[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t].w, o1, D[t], 0, 0, 0);
+                        }
                     }
-                } else {
-#pragma unroll
-                    for (int h = 0; h < NL; ++h) {
-                        const float b0 = xr[2 * h * RS], b1 = xr[(2 * h + 1) * RS], o0 = other(b0), o1 = other(b1);
-                        f4v a[TB];
-#pragma unroll
-                        for (int t = 0; t < TB; ++t) a[t] = buf[p][t][h];
-#pragma unroll
-                        for (int t = 0; t < TB; ++t) D[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t].x, b0, D[t], 0, 0, 0);
-#pragma unroll
-                        for (int t = 0; t < TB; ++t) D[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t].y, o0, D[t], 0, 0, 0);
-#pragma unroll
-                        for (int t = 0; t < TB; ++t) D[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t].z, b1, D[t], 0, 0, 0);
-#pragma unroll
-                        for (int t = 0; t < TB; ++t) D[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t].w, o1, D[t], 0, 0, 0);
-                    }
+                    if (st + kPD * shares < nst) load(buf[p], r0, st + kPD * shares);
                 }
-                if (st + kPD * shares < nst) load(buf[p], r0, st + kPD * shares);
+            }
+#pragma unroll
+            for (int t = 0; t < ND; ++t) {
+                sum[t] += D[t];
+                D[t] = f4v{0.f, 0.f, 0.f, 0.f};
             }
         }
     }
@@ -337,7 +345,7 @@ __global__ __launch_bounds__(64 * kNW) void contract_kernel(const cf32* __restri
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int lr = FWD ? 32 * (t >> 1) + 2 * (4 * kq + r) + (t & 1) : 16 * t + 4 * kq + r;
-                red[(share * 16 + i) * pitch + grp * GR + lr] = D[t][r];
+                red[(share * 16 + i) * pitch + grp * GR + lr] = sum[t][r];
             }
     }
     __syncthreads();
