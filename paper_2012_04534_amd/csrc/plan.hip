@@ -248,7 +248,7 @@ static void free_plan(Plan* P) {
     void* ptrs[] = {P->d_bins, P->d_ubins, P->d_map, P->d_hsel, P->d_u, P->d_yraw,
                     P->d_rop, P->d_xop, P->d_part, P->d_part_res, P->d_scalars, P->d_r, P->d_g,
                     P->d_gamma, P->d_v, P->d_stats, P->d_gpart, P->d_ptab_f, P->d_ptab_a,
-                    P->d_bt, P->d_bt_scal, P->d_amp, P->d_xih, P->d_khat, P->d_orb, P->d_inv, P->d_hu, P->d_tw_fx, P->d_tw_fy,
+                    P->d_bt, P->d_bt_scal, P->d_amp, P->d_xih, P->d_khat, P->d_orb, P->d_inv, P->d_tw_fx, P->d_tw_fy,
                     P->d_tw_ix, P->d_tw_iy, P->d_fa, P->d_fb, P->d_ft};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
@@ -482,15 +482,19 @@ Plan* plan_create(const ufss_geom* g, int m, int per_position, const int32_t* bi
         P->d_hsel = dalloc<float>(*P, hsel.size());
         upload(P->d_hsel, hsel.data(), hsel.size());
         if (!mix && algo != UFSS_ALGO_PHASOR) {
-            std::vector<float> hu(mu);
-            for (int j = 0; j < mu; ++j) hu[j] = (float)pulse_spectrum(*g, d, u[j]);
-            P->d_hu = dalloc<float>(*P, mu);
-            upload(P->d_hu, hu.data(), mu);
-            if (per_position) {      // shared subsets: the union is the subset, in order
-                std::vector<int> inv((size_t)npos * mu, -1);
+            if (!per_position) {     // shared subsets: the union is the subset, in order
+                P->d_hu = P->d_hsel;
+            } else {                 // [npos][mu] inverse map, then H over the union
+                const size_t nmap = (size_t)npos * mu;
+                std::vector<int> inv(nmap + mu, -1);
                 for (int64_t i = 0; i < nsel; ++i) inv[i / m * mu + map[i]] = (int)(i % m);
+                for (int j = 0; j < mu; ++j) {
+                    const float h = (float)pulse_spectrum(*g, d, u[j]);
+                    std::memcpy(&inv[nmap + j], &h, sizeof h);
+                }
                 P->d_inv = dalloc<int>(*P, inv.size());
                 upload(P->d_inv, inv.data(), inv.size());
+                P->d_hu = reinterpret_cast<float*>(P->d_inv + nmap);
             }
         }
         if (mix) {
