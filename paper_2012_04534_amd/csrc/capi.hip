@@ -304,9 +304,11 @@ int fista(Plan& P, const cf32* y, double lambda, double L, int iters, double tol
         if (job.stats) launch_reduce_fista_stats(job, s);
         job.stats = nullptr;
     };
-    // fused transform plans: each update leaves the new gamma's spectrum
+    // fused transform plans: each update leaves the new gamma's spectrum; a call's
+    // first is formed in the same order, so that where a run is stopped and resumed
+    // does not show in its iterates
     const bool chain = fft_fused(P);
-    if (chain && iters > 0) fft_fwd_transform(P, gamma, s);
+    if (chain && iters > 0) fft_spectrum(P, gamma, s);
     for (int k = 0; k < iters; ++k) {
         // the residual's partials wait in a buffer of their own for the statistics,
         // which the next iteration's post pass reduces beside its own work (two

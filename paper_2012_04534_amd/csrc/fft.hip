@@ -798,6 +798,7 @@ static void contract(const Plan& P, hipStream_t s) {
 //   kBins   IDFT_y -> H^2 and - H ymeas -> DFT_y       (A x - y on its way to R^)
 //   kDepth  IDFT_y -> FISTA update -> DFT_y            (X' on its way to the next X^)
 //   kProx   IDFT_y -> a learned stage's gradient and proximal step
+//   kSpec   voxels -> DFT_y                            (a first iteration's X^, by kDepth's arithmetic)
 // What bounds it: launches and latencies.  On a small scan each product and each
 // pass takes 4-6 us as a kernel of its own, of which its arithmetic is under 1 us;
 // a FISTA iteration goes from 11 launches to 8.  (A whole plane in LDS, both axes
@@ -813,10 +814,10 @@ static void contract(const Plan& P, hipStream_t s) {
 // it (8.8 and 11.8 with all tiles in one wave); an apply pair of 45 x 51 x 301 (BF16
 // table) 139 -> 133 us with one launch less per operator.
 // ---------------------------------------------------------------------------
-enum { kPre, kPost, kBins, kDepth, kProx };
+enum { kPre, kPost, kBins, kDepth, kProx, kSpec };
 
 struct ColumnArgs {
-    const cf32* in;                           // [ly][nx][C], or the measurements (kPre)
+    const cf32* in;                           // [ly][nx][C], or the measurements (kPre) or voxels (kSpec)
     cf32* out;                                // [ly][nx][C], or the measurements (kPost)
     const cf32 *tiy, *tfy;
     int nx, ny, ly, C, nct, units;
@@ -857,7 +858,8 @@ __host__ __device__ constexpr int column_units(int nt) { return nt == 1 ? 4 : nt
 template <int NT, int MODE>
 __global__ __launch_bounds__(256) void column_kernel(ColumnArgs g) {
     constexpr int UN = column_units(NT), NW = 4 / UN;         // waves per unit
-    constexpr bool kIv = MODE != kPre, kFw = MODE != kPost && MODE != kProx, kMeas = MODE != kDepth && MODE != kProx;
+    constexpr bool kIv = MODE != kPre && MODE != kSpec, kFw = MODE != kPost && MODE != kProx;
+    constexpr bool kMeas = MODE == kPre || MODE == kPost || MODE == kBins;
     __shared__ __align__(16) double smem[MODE == kBins ? kStatsRed + 6 : UN * NT * 256];
     __shared__ double red[5 * 4];
     if (MODE == kBins && (int)blockIdx.x * UN >= g.units) {
@@ -923,7 +925,7 @@ __global__ __launch_bounds__(256) void column_kernel(ColumnArgs g) {
         for (int r = 0; r < 4; ++r) {
             q[r] = v[r] = cf32{0.f, 0.f};
             if (!ok || !mine || i0 + r >= ny) continue;
-            q[r] = (MODE == kProx ? g.prox.gam : g.upd.gamma)[pos(r) * C + c];
+            q[r] = (MODE == kSpec ? g.in : MODE == kProx ? g.prox.gam : g.upd.gamma)[pos(r) * C + c];
             if (MODE == kDepth) v[r] = g.upd.a[pos(r) * C + c];
         }
     }
@@ -973,6 +975,8 @@ __global__ __launch_bounds__(256) void column_kernel(ColumnArgs g) {
                 g.upd.gamma[at] = gn;
                 v[r] = gn;
             }
+        } else if constexpr (MODE == kSpec) {
+            v[r] = q[r];
         } else if constexpr (MODE == kPre) {
             v[r] = cf32{h * q[r].re, h * q[r].im};
         } else {
@@ -992,7 +996,7 @@ __global__ __launch_bounds__(256) void column_kernel(ColumnArgs g) {
         if (kFw && mine) xs[(i0 + r) * 16 + ch] = v[r];
     }
     if constexpr (MODE == kDepth) column_sums(sum, red, g.part + 5 * (int64_t)blockIdx.x);
-    else if constexpr (MODE != kPre) column_sums(sum, red, g.part + blockIdx.x);
+    else if constexpr (MODE == kPost || MODE == kBins) column_sums(sum, red, g.part + blockIdx.x);
     else __syncthreads();                                     // xs is written (column_sums has the barrier too)
     if (!fw || unit >= g.units) return;
     cf32* dst = g.out + (int64_t)px * C + c;
@@ -1124,6 +1128,12 @@ int fft_update(const Plan& P, const UpdateArgs& u, bool more, hipStream_t s) {
     const int nb = column<kDepth>(P, P.d_ft, P.d_ft, nz, g, s);
     if (more) forward_x(P, nz, s);
     return nb;
+}
+
+// X^ as fft_update leaves it, in the same order and arithmetic (y, then x).
+void fft_spectrum(const Plan& P, const cf32* x, hipStream_t s) {
+    column<kSpec>(P, x, P.d_ft, P.g.nz, ColumnArgs{}, s);
+    forward_x(P, P.g.nz, s);
 }
 
 // Forward, in three steps (the contraction is the core kernel):

@@ -372,13 +372,15 @@ struct UpdateArgs {
 // in one kernel with the lateral products along y.  fft_post: Y^ -> y = A x (- ymeas),
 // partials of ||y||^2 (count returned); fft_pre: r -> R^; fft_residual: Y^ -> R^ of
 // A x - ymeas (with partials, and an earlier iteration's statistics by one more block);
-// fft_update: X' -> the FISTA update and, if more, X^ of the new gamma; fft_prox: X' ->
-// a learned stage's proximal step.
+// fft_update: X' -> the FISTA update and, if more, X^ of the new gamma; fft_spectrum: X^
+// of an iterate, bit for bit as fft_update leaves it; fft_prox: X' -> a learned stage's
+// proximal step.
 bool fft_fused(const Plan& P);
 int fft_post(const Plan& P, cf32* y, const cf32* ymeas, double* part, hipStream_t s);
 void fft_pre(const Plan& P, const cf32* r, hipStream_t s);
 int fft_residual(const Plan& P, const cf32* ymeas, double* part, const StatsJob& job, hipStream_t s);
 int fft_update(const Plan& P, const UpdateArgs& u, bool more, hipStream_t s);
+void fft_spectrum(const Plan& P, const cf32* x, hipStream_t s);
 void fft_prox(const Plan& P, const ProxArgs& a, hipStream_t s);
 
 // Random mixing passes (vec.hip): they replace launch_forward_post and
