@@ -528,6 +528,7 @@ struct AdjArgs {
     int kc;                // bin chunk (multiple of 4)
     int split;             // parts, see tile_range; split > 1 writes partials
     int top;               // the heaviest tile's work
+    int kcons;             // the union is consecutive bins
     cf32* part;            // [split][ny][nx][nz] when split > 1
     int64_t nvox;
     int nblk;              // blocks of this plan's grid
@@ -607,10 +608,12 @@ __device__ __forceinline__ void adj_f32_body(const AdjArgs& a, const int b, unsi
         };
         if (left >= KC) {
             // a whole chunk: lane group kq takes bins NJ kq .. NJ kq + NJ - 1 of it.
-            // CONS: where those are consecutive integers (for every lane), its
+            // CONS (8-wave workgroups, a union of consecutive bins): the lane's
             // phasor steps by exp(-j 2 pi u) from one to the next: one rotation
             // (4 FMAs) instead of a cos/sin pair, whose issue does not hide under
-            // the products; the chain restarts from cos/sin at every offset
+            // the products; the chain restarts from cos/sin at every offset.
+            // Three rotations in a row have about twice a cos/sin pair's error, so
+            // the other kernels, whose callers cannot choose, do without
             auto offsets = [&](auto consc) {
                 constexpr bool CONS = decltype(consc)::value;
                 uint32_t kl[NJ];
@@ -660,9 +663,12 @@ __device__ __forceinline__ void adj_f32_body(const AdjArgs& a, const int b, unsi
                     }
                 }
             };
-            const bool cons = NJ > 1 && __all(klds[NJ * kq + NJ - 1] - klds[NJ * kq] == NJ - 1);
-            if (cons) offsets(std::true_type{});
-            else offsets(std::false_type{});
+            if constexpr (NW == 8 && NJ > 1) {
+                if (a.kcons) offsets(std::true_type{});
+                else offsets(std::false_type{});
+            } else {
+                offsets(std::false_type{});
+            }
         } else if (left <= 2) {
             // a last chunk of at most 2 bins: the K = 4 of one product takes
             // those bins at two offsets, lane groups kq = 0, 1 at a_x and
@@ -914,6 +920,7 @@ static int adj_args(const Plan& P, cf32* out, AdjArgs& a, size_t& lds, int np, i
     lds = gemm_lds(tpy, hc, np, a.sw, a.kc, a.wx, zspan, P.d_amp != nullptr, (size_t)a.kc * 4);
     a.split = P.adj_split;
     a.top = top_work(P, np);
+    a.kcons = P.ubins_h.back() - P.ubins_h.front() == a.mu - 1;
     a.part = P.d_gpart;
     a.nvox = P.nvox;
     a.nblk = a.ntx * a.nty * a.nzt * a.split;
