@@ -617,6 +617,7 @@ int autotune(Plan& P, const char* cache_path, int flags, hipStream_t s, int32_t*
         std::vector<int> cand;
         for (int c : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64})
             if (c <= ndy) cand.push_back(c);
+        const int64_t fwd_bytes = (int64_t)P.npos * (int64_t)P.ubins_h.size() * 8, adj_bytes = P.nvox * 8;
         // inputs: the plan's own workspace vectors hold finite values
         UFSS_HIP(hipMemsetAsync(P.d_gamma, 0, P.nvox * sizeof(cf32), s));
         UFSS_HIP(hipMemsetAsync(P.d_r, 0, (size_t)P.npos * P.m * sizeof(cf32), s));
@@ -641,7 +642,7 @@ int autotune(Plan& P, const char* cache_path, int flags, hipStream_t s, int32_t*
                 for (int nw : nwc)
                     for (int zs : zcand)
                         for (int c : cand) {
-                            if (c * zs > 96) continue;          // bounds the partial-sum workspace
+                            if (c * zs > 96 || !parts_fit(c * zs, fwd_bytes)) continue;   // bounds the partial-sum workspace
                             P.fwd_nw = nw;
                             P.fwd_np = np;
                             P.bf_fwd_rows = wr;
@@ -656,7 +657,7 @@ int autotune(Plan& P, const char* cache_path, int flags, hipStream_t s, int32_t*
         int bzc = 16;
         if (P.dtype == UFSS_F32 && !quick) {
             for (int c : cand) {
-                if (c * bz > 96) continue;
+                if (c * bz > 96 || !parts_fit(c * bz, fwd_bytes)) continue;
                 P.fwd_zc = 8;
                 plan_set_splits(P, c, P.adj_split, bz);
                 double t = time_ms([&]() { op_forward(P, P.d_gamma, P.d_r, nullptr, nullptr, s); }, 3, s);
@@ -676,6 +677,7 @@ int autotune(Plan& P, const char* cache_path, int flags, hipStream_t s, int32_t*
                     for (int aw : awc) {
                         if (aw == 8 && np != 2) continue;
                         for (int c : cand) {
+                            if (!parts_fit(c, adj_bytes)) continue;
                             P.adj_np = np;
                             P.bf_adj_rows = wr;
                             P.bf_adj_nz = nzs;
@@ -693,6 +695,7 @@ int autotune(Plan& P, const char* cache_path, int flags, hipStream_t s, int32_t*
         int bkc = 16;
         if (P.dtype == UFSS_F32 && !quick) {
             for (int c : cand) {
+                if (!parts_fit(c, adj_bytes)) continue;
                 P.adj_kc = 8;
                 plan_set_splits(P, bf, c, bz);
                 double t = time_ms([&]() { op_adjoint(P, P.d_r, P.d_g, s); }, 3, s);

@@ -808,14 +808,14 @@ static int top_work(const Plan& P, int np) {
 // Default number of parts for `groups` workgroups per part and lateral tile: as
 // many as make about 3072 workgroups with work (12 per CU: the dispatcher evens
 // out their differences; fewer, larger ones measured up to 25% slower on the
-// 32 x 32 C-scan), within 64 parts, the steps of a tile and 512 MiB of partials.
+// 32 x 32 C-scan), within 64 parts, the steps of a tile and kPartsMax.
 static int default_split(const Plan& P, int np, int groups, int steps, int64_t part_bytes) {
     const int sw = sub_width(P), tpx = sw * np, tpy = 16 / sw;
     int64_t sx = 0, sy = 0;
     for (int x0 = 0; x0 < P.g.nx; x0 += tpx) sx += tile_nax(x0, np, sw, P.g.nx, P.d.wx);
     for (int y0 = 0; y0 < P.g.ny; y0 += tpy) sy += tile_nay(y0, tpy, P.g.ny, P.d.wy);
     const double full = std::max(1.0, (double)sx * sy / top_work(P, np) * groups);   // workgroups with work per part
-    const int64_t most = std::max<int64_t>(1, (int64_t(512) << 20) / std::max<int64_t>(1, part_bytes));
+    const int64_t most = std::max<int64_t>(1, kPartsMax / part_bytes);
     const int64_t split = std::max<int64_t>(1, std::min<int64_t>({(int64_t)(3072.0 / full + 0.5), 64, steps, most}));
     return (int)(split >= 8 ? split & ~(int64_t)7 : split);      // whole eighths for the XCDs
 }
@@ -824,12 +824,16 @@ int gemm_split(const Plan& P) {
     const int mu = (int)P.ubins_h.size();
     const int nw = std::max(1, std::min(P.fwd_nw, (mu + 15) / 16));
     const int steps = P.g.ny == 1 ? std::min(P.d.wx + 1, 4) : (P.d.wy + 1) * ((P.g.nz + 15) / 16);
-    return default_split(P, fwd_tile_np(P), (mu + 16 * nw - 1) / (16 * nw), steps, (int64_t)P.npos * mu * 8);
+    return default_split(P, fwd_tile_np(P), (mu + 16 * nw - 1) / (16 * nw), steps, (int64_t)P.npos * mu * 8 * gemm_zsplit(P));
 }
 
 // A B-scan's forward: its parts are depth chunks first (a workgroup walks its
 // chunks one after the other, each with a staging round of its own), then a_x.
-int gemm_zsplit(const Plan& P) { return P.g.ny == 1 ? std::min((P.g.nz + 15) / 16, 8) : 1; }
+int gemm_zsplit(const Plan& P) {
+    if (P.g.ny > 1) return 1;
+    const int64_t most = std::max<int64_t>(1, kPartsMax / ((int64_t)P.npos * (int64_t)P.ubins_h.size() * 8));
+    return (int)std::min<int64_t>({(P.g.nz + 15) / 16, 8, most});
+}
 
 int adj_split(const Plan& P) {
     const int mu = (int)P.ubins_h.size();

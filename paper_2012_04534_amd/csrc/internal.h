@@ -252,6 +252,10 @@ __device__ __forceinline__ void fista_stats(const StatsJob& job, double* red, do
 bool post_pre_ok(const Plan& P);
 int launch_post_pre(const Plan& P, const cf32* ymeas, double* part, const StatsJob& job, hipStream_t s);
 void launch_to_bf16(const cf32* x, void* out, int64_t n, hipStream_t s);
+// Most bytes of split partials that a direction's defaults and the autotuner choose:
+// a batch holds two such sets per scan.
+static constexpr int64_t kPartsMax = int64_t(512) << 20;
+inline bool parts_fit(int parts, int64_t part_bytes) { return parts == 1 || parts * part_bytes <= kPartsMax; }
 int gemm_split(const Plan& P);
 int gemm_zsplit(const Plan& P);
 int adj_split(const Plan& P);

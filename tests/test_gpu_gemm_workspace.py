@@ -1,0 +1,58 @@
+"""Split partials of the FP32 GEMMs stay within 512 MiB per direction: the default
+parts of a long B-scan, whose forward divides both its depths and its offsets, and
+the parts that the autotuner tries."""
+import threading
+
+import pytest
+
+from paper_2012_04534_amd import workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+CAP = 512 << 20
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch.device("cuda:0")
+
+
+@pytest.mark.parametrize("nx,nz,m", [(60000, 128, 150), (30000, 128, 150)])
+def test_default_partials_within_the_cap(nx, nz, m, dev):
+    from paper_2012_04534_amd import ufss as u
+    g = W.geometry(nx, 1, nz, 1280, win_x=4, win_y=0)
+    bins, _ = u.ufss_select_freqs(g, m, False, 3)
+    plan = u.Plan(g, m, False, bins, algo=u.ALGO_GEMM)
+    i = plan.info()
+    assert i["fwd_split"] * i["fwd_zsplit"] * nx * m * 8 <= CAP
+    assert i["adj_split"] == 1 or i["adj_split"] * nx * nz * 8 <= CAP
+    plan.close()
+
+
+def test_autotuner_tries_no_more_than_the_cap(dev):
+    from paper_2012_04534_amd import ufss as u
+    g = W.geometry(4096, 1, 1024, 2048, win_x=63, win_y=0)
+    bins, _ = u.ufss_select_freqs(g, 32, False, 3)
+    plan = u.Plan(g, 32, False, bins, algo=u.ALGO_GEMM)      # 32 MiB a copy of the volume
+    torch.cuda.synchronize()
+    held = plan.info()["adj_split"] * 4096 * 1024 * 8 + plan.info()["fwd_split"] * plan.info()["fwd_zsplit"] * 4096 * 32 * 8
+    start = torch.cuda.mem_get_info()[0] + held
+    low, stop = [start], threading.Event()
+
+    def watch():
+        while not stop.is_set():
+            low[0] = min(low[0], torch.cuda.mem_get_info()[0])
+
+    t = threading.Thread(target=watch)
+    t.start()
+    try:
+        u.ufss_autotune(plan, use_cache=False, write_cache=False, quick=True)
+    finally:
+        stop.set()
+        t.join()
+    # one direction's partials at a time reach the cap; the other's are far below it here
+    assert start - low[0] <= CAP + (128 << 20)
+    plan.close()
