@@ -27,16 +27,12 @@
 #include <vector>
 
 #include "internal.h"
+#include "run.h"
 
 namespace ufss {
 
 static constexpr int kLT = 256;
 static constexpr int kMaxCh = 8;
-
-struct Dims {
-    int nx, ny, nz;
-    int64_t n;
-};
 
 static int nblk(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(1024, (n + kLT - 1) / kLT)); }
 
@@ -52,26 +48,6 @@ static int nblk(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(
 // with a branch per column waits at each join: conv2 19.)
 static constexpr int kXC = 2;            // the convolutions: more, shorter runs (4: 14-20 us; 1: 12-16)
 static constexpr int kXW = 4;            // the weight gradients: more products per load (2: 22 us)
-
-struct Run {
-    int z, x, y;            // depth, first column of the run
-    int64_t v;              // its voxel (column x + k: v + k nz)
-};
-template <int XV>
-__host__ __device__ static inline int64_t run_count(const Dims& d) {
-    return (int64_t)d.ny * ((d.nx + XV - 1) / XV) * d.nz;
-}
-// (a network's grid holds fewer than 2^31 voxels: 32-bit arithmetic)
-template <int XV>
-__device__ __forceinline__ Run run_at(const Dims& d, int64_t t) {
-    const int nxr = (d.nx + XV - 1) / XV, c = (int)t / d.nz;
-    Run r;
-    r.z = (int)t - c * d.nz;
-    r.y = c / nxr;
-    r.x = (c - r.y * nxr) * XV;
-    r.v = ((int64_t)r.y * d.nx + r.x) * d.nz + r.z;
-    return r;
-}
 
 // Row (e_y, e_z) = (row / 3 - 1, row % 3 - 1) of the neighbours: whether it is
 // inside the grid, and the offset to it.  Tap e of a row is e_x = e - 1, offset
@@ -663,7 +639,7 @@ static int stage_size(int ch) { return 2 + ch * 54 + ch + 2 * ch * 27 + 2; }
 Net* net_create(Plan* P, int S, int ch, double L, double mu, uint64_t seed) {
     if (!P) fail(UFSS_ERR_INVALID_ARG, "plan is NULL");
     if (S < 1 || S > 256 || ch < 1 || ch > kMaxCh) fail(UFSS_ERR_INVALID_ARG, "stages in [1,256], channels in [1,8]");
-    if (P->nvox >= (int64_t(1) << 31)) fail(UFSS_ERR_UNSUPPORTED, "the network needs fewer than 2^31 voxels");
+    if (P->nvox >= (int64_t(1) << 32)) fail(UFSS_ERR_OOM, "no device holds a network of 2^32 voxels");   // see run_at
     if (!(L > 0) || !(mu > 0)) fail(UFSS_ERR_INVALID_ARG, "L and mu must be positive");
     Net* N = new Net();
     try {
