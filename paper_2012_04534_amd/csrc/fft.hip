@@ -373,18 +373,26 @@ __global__ __launch_bounds__(64 * kNW) void contract_kernel(const cf32* __restri
 //   forward: lane l loads entries (z = 16 s + 4 (l / 16) .. + 3, k = 2 (l % 16), + 1) of
 //   32 outputs: two tiles, rows 2 i and 2 i + 1
 //   adjoint: lane l loads entries (z = l % 16, k = 16 s + 4 (l / 16) .. + 3)
+// The matrix cores take BF16 values below 2^-126 as zero, which the second and third
+// parts of members below 2^-103 can be: where all members of an entry are below 2^-63
+// (kSizable, the upper exponent bits, none set) they are cut once more at 2^64 times
+// their size and the sums scaled back.  (Next to a larger member each loses under 2^-63
+// of that one.)
 // Columns in LDS: plane, group of 4 entries, column, 4 entries of (re, im): one 16-byte
 // read per operand; groups padded by 16 bytes against bank conflicts of the staging.
 typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
 typedef unsigned int u4v __attribute__((ext_vector_type(4)));
 static constexpr int kRB = 256;                               // reduction entries staged at a time
 static constexpr int kGP = 16 * 16 + 16;                      // bytes of a group of 4 entries
+static constexpr float kLarger = 0x1p64f;
+static constexpr unsigned kSizable = 0x60000000u;
 
 template <bool FWD, int TB, bool SWAP>
 __global__ __launch_bounds__(64 * kNW) void contract_bf16_kernel(const cbf16* __restrict__ tab, const int2* __restrict__ orbits,
                                                        const cf32* __restrict__ in, cf32* __restrict__ out,
                                                        int ly, int lx, int nz, int mus, int C, int R, int groups) {
-    static_assert(kRB == 64 * kNW, "a thread stages one reduction entry");
+    static_assert(kRB == 64 * kNW && kNW == 4, "a thread stages one reduction entry, an int4 holds the waves' sizes");
+    __shared__ __align__(16) int sizes[kNW];
     extern __shared__ __align__(16) unsigned char smem[];
     float* red = reinterpret_cast<float*>(smem);              // [shares][16][rows + 1] after the reduction
     constexpr int NQ = SWAP ? 8 : 4, NPL = SWAP ? 3 : 2;
@@ -402,8 +410,6 @@ __global__ __launch_bounds__(64 * kNW) void contract_bf16_kernel(const cbf16* __
     const int gc0 = c0 + grp * GR;
 
     f4v D[ND];
-#pragma unroll
-    for (int t = 0; t < ND; ++t) D[t] = f4v{0.f, 0.f, 0.f, 0.f};
     int off[TB];
 #pragma unroll
     for (int t = 0; t < TB; ++t)
@@ -416,75 +422,91 @@ __global__ __launch_bounds__(64 * kNW) void contract_bf16_kernel(const cbf16* __
 #pragma unroll
             for (int h = 0; h < NL; ++h) b[t][h] = *reinterpret_cast<const uint2*>(p + off[t] + h * (FWD ? mus : 2));
     };
-    for (int r0 = 0; r0 < R; r0 += kRB) {
-        const int rc = min(kRB, R - r0), nst = (rc + ST - 1) / ST;
+    float scale = 1.f;
+    unsigned bits = 0;                                        // all bits of this thread's members
+    for (;;) {
 #pragma unroll
-        for (int p = 0; p < kPD; ++p)
-            if (active && share + p * shares < nst) load(buf[p], r0, share + p * shares);
-        if (r0 > 0) __syncthreads();                          // the previous chunk's columns are read
-        const int r = threadIdx.x;
-        if (r < nst * ST) {
-            unsigned char* dst = smem + (r >> 2) * kGP + (r & 3) * 4;
-            auto put = [&](int plane, int col, float a, float b) {       // the top halves of a and b
-                *reinterpret_cast<unsigned*>(dst + plane * (kRB / 4) * kGP + col * 16) =
-                    (__float_as_uint(a) >> 16) | (__float_as_uint(b) & 0xffff0000u);
-            };
-            auto top = [](float a) { return __uint_as_float(__float_as_uint(a) & 0xffff0000u); };
-            cf32 v[NQ];
+        for (int t = 0; t < ND; ++t) D[t] = f4v{0.f, 0.f, 0.f, 0.f};
+        for (int r0 = 0; r0 < R; r0 += kRB) {
+            const int rc = min(kRB, R - r0), nst = (rc + ST - 1) / ST;
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                v[q] = cf32{0.f, 0.f};
-                if (q < nq && r < rc) v[q] = in[orb.row(q) * R + r0 + r];
-            }
+            for (int p = 0; p < kPD; ++p)
+                if (active && share + p * shares < nst) load(buf[p], r0, share + p * shares);
+            if (r0 > 0) __syncthreads();                          // the previous chunk's columns are read
+            const int r = threadIdx.x;
+            if (r < nst * ST) {
+                unsigned char* dst = smem + (r >> 2) * kGP + (r & 3) * 4;
+                auto put = [&](int plane, int col, float a, float b) {       // the top halves of a and b
+                    *reinterpret_cast<unsigned*>(dst + plane * (kRB / 4) * kGP + col * 16) =
+                        (__float_as_uint(a) >> 16) | (__float_as_uint(b) & 0xffff0000u);
+                };
+                auto top = [](float a) { return __uint_as_float(__float_as_uint(a) & 0xffff0000u); };
+                cf32 v[NQ];
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                float re = v[q].re, im = v[q].im;
-#pragma unroll
-                for (int part = 0; part < 3; ++part) {
-                    const float tr = top(re), ti = top(im);
-                    const int plane = SWAP ? part : part >> 1, col = 2 * q + (SWAP ? 0 : 8 * (part & 1));
-                    put(plane, col, tr, FWD ? -ti : ti);
-                    put(plane, col + 1, ti, FWD ? tr : -tr);
-                    re -= tr;
-                    im -= ti;
+                for (int q = 0; q < NQ; ++q) {
+                    v[q] = cf32{0.f, 0.f};
+                    if (q < nq && r < rc) v[q] = in[orb.row(q) * R + r0 + r];
                 }
-                if (!SWAP) {
-                    put(1, 8 + 2 * q, 0.f, 0.f);
-                    put(1, 9 + 2 * q, 0.f, 0.f);
-                }
-            }
-        }
-        __syncthreads();
-        if (!active) continue;
-        for (int st0 = share; st0 < nst; st0 += kPD * shares) {
 #pragma unroll
-            for (int p = 0; p < kPD; ++p) {
-                const int st = st0 + p * shares;
-                if (st >= nst) break;                         // wave-uniform
-                const unsigned char* src = smem + (4 * st + kq) * kGP + i * 16;
-                bf8v b[NPL], a[ND];
+                for (int q = 0; q < NQ; ++q) {
+                    bits |= __float_as_uint(v[q].re) | __float_as_uint(v[q].im);
+                    float re = v[q].re * scale, im = v[q].im * scale;
 #pragma unroll
-                for (int w = 0; w < NPL; ++w) b[w] = *reinterpret_cast<const bf8v*>(src + w * (kRB / 4) * kGP);
-#pragma unroll
-                for (int t = 0; t < TB; ++t) {
-                    const uint2* e = buf[p][t];
-                    if constexpr (FWD) {
-                        a[2 * t] = __builtin_bit_cast(bf8v, u4v{e[0].x, e[1].x, e[2].x, e[3].x});
-                        a[2 * t + 1] = __builtin_bit_cast(bf8v, u4v{e[0].y, e[1].y, e[2].y, e[3].y});
-                    } else {
-                        a[t] = __builtin_bit_cast(bf8v, u4v{e[0].x, e[0].y, e[1].x, e[1].y});
+                    for (int part = 0; part < 3; ++part) {
+                        const float tr = top(re), ti = top(im);
+                        const int plane = SWAP ? part : part >> 1, col = 2 * q + (SWAP ? 0 : 8 * (part & 1));
+                        put(plane, col, tr, FWD ? -ti : ti);
+                        put(plane, col + 1, ti, FWD ? tr : -tr);
+                        re -= tr;
+                        im -= ti;
+                    }
+                    if (!SWAP) {
+                        put(1, 8 + 2 * q, 0.f, 0.f);
+                        put(1, 9 + 2 * q, 0.f, 0.f);
                     }
                 }
-                // smallest parts first
+            }
+            __syncthreads();
+            if (!active) continue;
+            for (int st0 = share; st0 < nst; st0 += kPD * shares) {
 #pragma unroll
-                for (int w = NPL - 1; w >= 0; --w)
+                for (int p = 0; p < kPD; ++p) {
+                    const int st = st0 + p * shares;
+                    if (st >= nst) break;                         // wave-uniform
+                    const unsigned char* src = smem + (4 * st + kq) * kGP + i * 16;
+                    bf8v b[NPL], a[ND];
 #pragma unroll
-                    for (int t = 0; t < ND; ++t) D[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t], b[w], D[t], 0, 0, 0);
-                if (st + kPD * shares < nst) load(buf[p], r0, st + kPD * shares);
+                    for (int w = 0; w < NPL; ++w) b[w] = *reinterpret_cast<const bf8v*>(src + w * (kRB / 4) * kGP);
+#pragma unroll
+                    for (int t = 0; t < TB; ++t) {
+                        const uint2* e = buf[p][t];
+                        if constexpr (FWD) {
+                            a[2 * t] = __builtin_bit_cast(bf8v, u4v{e[0].x, e[1].x, e[2].x, e[3].x});
+                            a[2 * t + 1] = __builtin_bit_cast(bf8v, u4v{e[0].y, e[1].y, e[2].y, e[3].y});
+                        } else {
+                            a[t] = __builtin_bit_cast(bf8v, u4v{e[0].x, e[0].y, e[1].x, e[1].y});
+                        }
+                    }
+                    // smallest parts first
+#pragma unroll
+                    for (int w = NPL - 1; w >= 0; --w)
+#pragma unroll
+                        for (int t = 0; t < ND; ++t) D[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t], b[w], D[t], 0, 0, 0);
+                    if (st + kPD * shares < nst) load(buf[p], r0, st + kPD * shares);
+                }
             }
         }
+        if (scale == 1.f) {
+            const int size = (__any(bits & kSizable) ? 1 : 0) | (__any(bits & 0x7fffffffu) ? 2 : 0);
+            if (lane == 0) sizes[wave] = size;
+        }
+        __syncthreads();                                      // the columns are read; red takes their place
+        if (scale != 1.f) break;
+        const int4 w = *reinterpret_cast<const int4*>(sizes);
+        if (__builtin_amdgcn_readfirstlane(w.x | w.y | w.z | w.w) != 2) break;
+        scale = kLarger;                                      // small members only
     }
-    __syncthreads();                                          // the columns are read; red takes their place
+    const float back = 1.f / scale;
     const int rows = min(groups * GR, C - c0), pitch = ng * GR + 1;
     if (active) {
 #pragma unroll
@@ -492,7 +514,7 @@ __global__ __launch_bounds__(64 * kNW) void contract_bf16_kernel(const cbf16* __
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int lr = FWD ? 32 * (t >> 1) + 2 * (4 * kq + r) + (t & 1) : 16 * t + 4 * kq + r;
-                red[(share * 16 + i) * pitch + grp * GR + lr] = D[t][r];
+                red[(share * 16 + i) * pitch + grp * GR + lr] = D[t][r] * back;
             }
     }
     __syncthreads();
