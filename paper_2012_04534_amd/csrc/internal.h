@@ -109,8 +109,8 @@ struct Plan {
     int* d_ubins = nullptr;        // union bins [mu]
     int* d_map = nullptr;          // per (p, m): index into the union list
     float* d_hsel = nullptr;       // H_k per selection entry [m] or [npos*m]
-    int* d_inv = nullptr;          // per-position plans: (p, j) -> the m with map(p, m) = j, or -1
-    float* d_hu = nullptr;         // H_k per union bin [mu], inside d_hsel or after d_inv
+    int* d_inv = nullptr;          // per-position plans: (p, j) -> the m with map(p, m) = j, or -1; behind d_map
+    float* d_hu = nullptr;         // H_k per union bin [mu], inside d_hsel or behind d_inv
     uint32_t* d_u = nullptr;       // integer-turn delay table [wy+1][wx+1][nz]
     float* d_amp = nullptr;        // Gaussian beam amplitude, same layout (theta > 0)
     // random mixing (Rademacher signs): the union is every DFT index (signed

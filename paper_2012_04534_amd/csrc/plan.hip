@@ -248,7 +248,7 @@ static void free_plan(Plan* P) {
     void* ptrs[] = {P->d_bins, P->d_ubins, P->d_map, P->d_hsel, P->d_u, P->d_yraw,
                     P->d_rop, P->d_xop, P->d_part, P->d_part_res, P->d_scalars, P->d_r, P->d_g,
                     P->d_gamma, P->d_v, P->d_stats, P->d_gpart, P->d_ptab_f, P->d_ptab_a,
-                    P->d_bt, P->d_bt_scal, P->d_amp, P->d_xih, P->d_khat, P->d_orb, P->d_inv, P->d_tw_fx, P->d_tw_fy,
+                    P->d_bt, P->d_bt_scal, P->d_amp, P->d_xih, P->d_khat, P->d_orb, P->d_tw_fx, P->d_tw_fy,
                     P->d_tw_ix, P->d_tw_iy, P->d_fa, P->d_fb, P->d_ft};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
@@ -447,7 +447,13 @@ Plan* plan_create(const ufss_geom* g, int m, int per_position, const int32_t* bi
         P->ubins_h = u;
         const int mu = (int)u.size();
         const int opw = (algo == UFSS_ALGO_PHASOR) ? m : mu;   // operand row width
-        std::vector<int> map(mix ? 1 : nsel, 0);
+        // GEMM and transform plans with bins per position: the inverse map and H over the
+        // union behind the map, in one buffer (an allocation and an upload are 5-10 us each)
+        const bool inverse = !mix && algo != UFSS_ALGO_PHASOR && per_position;
+        const size_t nmap = (size_t)npos * mu;
+        std::vector<int> map;
+        map.reserve(mix ? 1 : nsel + (inverse ? nmap + mu : 0));
+        map.resize(mix ? 1 : nsel, 0);
         std::vector<float> hsel(mix ? mu : nsel);
         if (mix) {
             for (int j = 0; j < mu; ++j) hsel[j] = (float)pulse_spectrum(*g, d, u[j]);
@@ -473,6 +479,17 @@ Plan* plan_create(const ufss_geom* g, int m, int per_position, const int32_t* bi
                     uint64_t qi = (uint64_t)q & 0xFFFFFFFFull;
                     ut[((size_t)j * (wx + 1) + i) * g->nz + z] = (uint32_t)qi;
                 }
+        if (inverse) {
+            map.resize(nsel + nmap + mu, -1);
+            const int* at = map.data();
+            int* inv = map.data() + nsel;
+            for (int p = 0; p < npos; ++p)
+                for (int k = 0; k < m; ++k) inv[(size_t)p * mu + *at++] = k;
+            for (int j = 0; j < mu; ++j) {
+                const float h = (float)pulse_spectrum(*g, d, u[j]);
+                std::memcpy(&inv[nmap + j], &h, sizeof h);
+            }
+        }
         P->d_bins = dalloc<int>(*P, nsel);
         upload(P->d_bins, P->bins_h.data(), nsel);
         P->d_ubins = dalloc<int>(*P, mu);
@@ -481,21 +498,11 @@ Plan* plan_create(const ufss_geom* g, int m, int per_position, const int32_t* bi
         upload(P->d_map, map.data(), map.size());
         P->d_hsel = dalloc<float>(*P, hsel.size());
         upload(P->d_hsel, hsel.data(), hsel.size());
-        if (!mix && algo != UFSS_ALGO_PHASOR) {
-            if (!per_position) {     // shared subsets: the union is the subset, in order
-                P->d_hu = P->d_hsel;
-            } else {                 // [npos][mu] inverse map, then H over the union
-                const size_t nmap = (size_t)npos * mu;
-                std::vector<int> inv(nmap + mu, -1);
-                for (int64_t i = 0; i < nsel; ++i) inv[i / m * mu + map[i]] = (int)(i % m);
-                for (int j = 0; j < mu; ++j) {
-                    const float h = (float)pulse_spectrum(*g, d, u[j]);
-                    std::memcpy(&inv[nmap + j], &h, sizeof h);
-                }
-                P->d_inv = dalloc<int>(*P, inv.size());
-                upload(P->d_inv, inv.data(), inv.size());
-                P->d_hu = reinterpret_cast<float*>(P->d_inv + nmap);
-            }
+        if (inverse) {
+            P->d_inv = P->d_map + nsel;
+            P->d_hu = reinterpret_cast<float*>(P->d_inv + nmap);
+        } else {
+            P->d_hu = P->d_hsel;     // shared subsets: the union is the subset, in order
         }
         if (mix) {
             const int nrow = mix->per_sign ? npos : 1;
