@@ -563,10 +563,20 @@ Plan* plan_create(const ufss_geom* g, int m, int per_position, const int32_t* bi
     return P;
 }
 
-// Change the split-K factors of the GEMM path (reallocating their partials).
+// Change the split-K factors of the GEMM path (reallocating their partials).  What
+// the device has no room for is refused before anything is freed: the plan stays as
+// it was, where a failed allocation would leave its kernels without a buffer.
 void plan_set_splits(Plan& P, int fs, int as, int zs) {
     if (fs < 1 || as < 1 || zs < 1) fail(UFSS_ERR_INVALID_ARG, "split factors must be >= 1");
     const size_t mu = P.ubins_h.size();
+    const int64_t yraw = (int64_t)P.npos * mu * sizeof(cf32), gpart = P.nvox * sizeof(cf32);
+    const int64_t more = (fs * zs - P.fwd_split * P.fwd_zsplit) * yraw +
+                         ((as > 1 ? as : 0) - (P.d_gpart ? P.adj_split : 0)) * gpart;
+    if (more > 0) {
+        size_t room = 0, total = 0;
+        UFSS_HIP(hipMemGetInfo(&room, &total));
+        if (more > (int64_t)room) fail(UFSS_ERR_OOM, "no room for the split partials");
+    }
     if (fs * zs != P.fwd_split * P.fwd_zsplit) {
         UFSS_HIP(hipDeviceSynchronize());
         if (P.d_yraw) UFSS_HIP(hipFree(P.d_yraw));

@@ -1,8 +1,10 @@
 """Split partials of the FP32 GEMMs stay within 512 MiB per direction: the default
 parts of a long B-scan, whose forward divides both its depths and its offsets, and
-the parts that the autotuner tries."""
+the parts that the autotuner tries.  A tiling whose partials the device cannot hold
+is refused and leaves the plan as it was."""
 import threading
 
+import numpy as np
 import pytest
 
 from paper_2012_04534_amd import workloads as W
@@ -55,4 +57,23 @@ def test_autotuner_tries_no_more_than_the_cap(dev):
         t.join()
     # one direction's partials at a time reach the cap; the other's are far below it here
     assert start - low[0] <= CAP + (128 << 20)
+    plan.close()
+
+
+def test_refused_tiling_leaves_the_plan_usable(dev):
+    from paper_2012_04534_amd import ufss as u
+    g = W.geometry(1024, 400, 2, 1024, win_x=1, win_y=1)
+    bins, _ = u.ufss_select_freqs(g, 100, False, 3)
+    plan = u.Plan(g, 100, False, bins, algo=u.ALGO_GEMM)     # 312 MiB a part of the forward
+    x = torch.from_numpy(W.cn((400, 1024, 2), 1).astype(np.complex64)).to(dev)
+    y = [torch.empty((400, 1024, 100), dtype=torch.complex64, device=dev) for _ in range(2)]
+    before = plan.info()
+    u.ufss_forward(plan, x, y[0])
+    torch.cuda.synchronize()
+    with pytest.raises(u.UfssError) as e:
+        u.ufss_plan_set_tiling(plan, fwd_split=64, fwd_zsplit=64)      # 1.3 TB
+    assert e.value.name == "OOM"
+    assert plan.info() == before
+    u.ufss_forward(plan, x, y[1])
+    assert torch.equal(y[0], y[1])
     plan.close()
