@@ -26,6 +26,12 @@
 // 4.0 ms, adjoint 13.3 -> 4.0 ms; 32 x 32 x 256 (66 bins, full) 1.20 -> 0.73 and
 // 1.23 -> 0.75 ms; 32-position B-scan (128 depths, 32 bins) 0.26 -> 0.013 and
 // 0.067 -> 0.014 ms (there from the parts, below).
+// Offsets are summed from the far ones in: the near ones, where the phase is
+// stationary, make most of a scene's sum, and a chain that starts with them carries
+// it through all its roundings.  Relative error against 64 bits of the adjoint of a
+// scene's measurements, 22 x 41 x 99 with 16 bins: from the near ones out 3.0e-7, from
+// the far ones in 1.7e-7, one product per offset from -W to W 2.1e-7 (random operands:
+// 4.4e-7, 4.0e-7, 4.8e-7); the same time.
 //
 // MFMA: v_mfma_f32_16x16x4_f32.  Lane l holds A[i = l%16][k = l/16],
 // B[k = l/16][j = l%16] and D[i = 4(l/16) + r][j = l%16] for r = 0..3.
@@ -157,7 +163,7 @@ __host__ __device__ static inline int tile_nax(int x0, int np, int sw, int nx, i
 
 // What a tile and its part of the reduction run over.
 struct TileRange {
-    int t0, t1;          // steps (chunk of the reduction axis, a_y), a_y fastest
+    int t0, t1;          // steps (chunk of the reduction axis, a_y), a_y fastest, from the far one in
     int nay;             // a_y values of the tile
     int ax_lo, ax_hi;    // a_x range
 };
@@ -304,7 +310,7 @@ __device__ __forceinline__ void fwd_f32_body(const FwdArgs& a, const int b, unsi
         for (int s = 0; s < (FOLD ? NP : 1); ++s) t_re[s] = t_im[s] = f4{0.f, 0.f, 0.f, 0.f};
 
         for (int t = R.t0; t < R.t1; ++t) {
-            const int zi = t / R.nay, ay = t - zi * R.nay, z0 = zi * ZC;
+            const int zi = t / R.nay, ay = R.nay - 1 - (t - zi * R.nay), z0 = zi * ZC;
             __syncthreads();
             stage_mirrored<ZC, tpy>(halo, pitch, a.x, a.ny, a.nx, a.nz, py0, ay, px0 - a.wx, x_lo, x_hi, z0, a.nz);
             for (int q = threadIdx.x; q < (a.wx + 1) * ZC; q += blockDim.x) {
@@ -321,7 +327,7 @@ __device__ __forceinline__ void fwd_f32_body(const FwdArgs& a, const int b, unsi
             f4 m1[NP], m2[NP], m3[NP];
 #pragma unroll
             for (int s = 0; s < NP; ++s) m1[s] = m2[s] = m3[s] = f4{0.f, 0.f, 0.f, 0.f};
-            for (int ax = R.ax_lo; ax <= R.ax_hi; ++ax) {
+            for (int ax = R.ax_hi; ax >= R.ax_lo; --ax) {
                 const uint32_t* urow = ulds + ax * ZC;
                 const cf32* lrow = cell0 - ax * cs;
                 const cf32* rrow = ax > 0 ? cell0 + ax * cs : zcell;
@@ -339,7 +345,7 @@ __device__ __forceinline__ void fwd_f32_body(const FwdArgs& a, const int b, unsi
                     bmz[j] = -sn - c;
                     bpz[j] = c - sn;
                 }
-// this wave's offsets for the folded bins, and their phasors: the
+                // this wave's offsets for the folded bins, and their phasors: the
                 // wave's 4 bins x ZC depths are one phasor per lane (bin l % 4,
                 // depth l / 4), handed to the lanes that take them
                 const bool folds = FOLD && !TAIL && fold && (ax & 3) == wave;
@@ -582,7 +588,7 @@ __device__ __forceinline__ void adj_f32_body(const AdjArgs& a, const int b, unsi
     for (int s = 0; s < NP; ++s) out_re[s] = out_im[s] = f4{0.f, 0.f, 0.f, 0.f};
 
     for (int t = R.t0; t < R.t1; ++t) {
-        const int ki = t / R.nay, ay = t - ki * R.nay, k0 = ki * KC;
+        const int ki = t / R.nay, ay = R.nay - 1 - (t - ki * R.nay), k0 = ki * KC;
         const int left = a.mu - k0;                       // bins of this chunk, if fewer than KC
         __syncthreads();
         stage_mirrored<KC, tpy>(halo, pitch, a.r, a.ny, a.nx, a.mu, vy0, ay, vx0 - a.wx, x_lo, x_hi, k0, a.mu);
@@ -619,7 +625,7 @@ __device__ __forceinline__ void adj_f32_body(const AdjArgs& a, const int b, unsi
                 uint32_t kl[NJ];
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) kl[j] = (uint32_t)klds[NJ * kq + j];
-                for (int ax = R.ax_lo; ax <= R.ax_hi; ++ax) {
+                for (int ax = R.ax_hi; ax >= R.ax_lo; --ax) {
                     const uint32_t uz = ucol[ax * zspan];
                     const float gz = DIR ? gcol[ax * zspan] : 1.f;
                     const cf32* lrow = cell0 - ax * cs + NJ * kq;
@@ -672,12 +678,12 @@ __device__ __forceinline__ void adj_f32_body(const AdjArgs& a, const int b, unsi
         } else if (left <= 2) {
             // a last chunk of at most 2 bins: the K = 4 of one product takes
             // those bins at two offsets, lane groups kq = 0, 1 at a_x and
-            // kq = 2, 3 at a_x + 1 (zero past the last), so the chunk runs half
+            // kq = 2, 3 at a_x - 1 (zero past the first), so the chunk runs half
             // the offset steps and no product lane carries a padding bin
             const uint32_t k = (uint32_t)klds[kq & 1];
-            for (int ax = R.ax_lo; ax <= R.ax_hi; ax += 2) {
-                const int al = ax + (kq >> 1);
-                const bool ok = al <= R.ax_hi;
+            for (int ax = R.ax_hi; ax >= R.ax_lo; ax -= 2) {
+                const int al = ax - (kq >> 1);
+                const bool ok = al >= R.ax_lo;
                 const int ad = ok ? al : ax;
                 const cf32* lrow = cell0 - ad * cs + (kq & 1);
                 const cf32* rrow = cell0 + ad * cs + (kq & 1);
@@ -700,7 +706,7 @@ __device__ __forceinline__ void adj_f32_body(const AdjArgs& a, const int b, unsi
         } else {
             // a short last chunk: bins 4 j + kq, as many steps as it has fours
             const int nj = (left + 3) >> 2;
-            for (int ax = R.ax_lo; ax <= R.ax_hi; ++ax) {
+            for (int ax = R.ax_hi; ax >= R.ax_lo; --ax) {
                 const uint32_t uz = ucol[ax * zspan];
                 const float gz = DIR ? gcol[ax * zspan] : 1.f;
                 const cf32* lrow = cell0 - ax * cs + kq;
