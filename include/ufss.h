@@ -51,7 +51,9 @@ extern "C" {
 /* ---- operator algorithm -------------------------------------------------- */
 #define UFSS_ALGO_AUTO   0  /* GEMM, except FP32 per-position subsets whose
                                union holds at least 5 times the bins of one
-                               position: phasor path (measured faster there)  */
+                               position: phasor path (faster there with a
+                               Gaussian beam; without one only from 8 to 16
+                               times on)                                      */
 #define UFSS_ALGO_GEMM   1  /* windowed complex GEMM over (offset, depth) on MFMA;
                                per-position subsets run over their union of bins
                                and are gathered / scattered                    */

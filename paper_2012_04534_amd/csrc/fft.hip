@@ -644,7 +644,8 @@ void fft_setup(Plan& P) {
     const int nox = lx / 2 + 1, noy = ly / 2 + 1;
     if (fft_table_bytes(P) > kFftTableMax)
         fail(UFSS_ERR_UNSUPPORTED, "transform table larger than 32 GiB");
-    // LDS staging: twiddle rows (8 x L) and four transform rows (4 x nz or mu)
+    // the sizes that the path takes and is tested up to; its kernels stage chunks of a
+    // fixed size and set no limit of their own near these
     if (std::max(lx, ly) > 1024 || std::max(nz, mu) > 1536)
         fail(UFSS_ERR_UNSUPPORTED, "grid too large for the transform path (L <= 1024, nz and bins <= 1536)");
     P.fft_lx = lx;

@@ -411,9 +411,9 @@ Plan* plan_create(const ufss_geom* g, int m, int per_position, const int32_t* bi
         // beam 18: 904 / 2489, 7.4: 1967 / 2458, 5.3: 2226 / 2466; 30 x 40 x 70 with a
         // beam 7.4: 900 / 1061, 5.3: 1030 / 1058; without one 32 x 32 x 256 16: 1121 / 1814,
         // 8.2: 1918 / 1818, 5.1: 3218 / 1820; 48 x 40 x 200 (W = 16) 25: 746 / 957, 13: 1172 / 953.
-        // The line holds for the beam; without one the two cross at 8 to 16, and it stays
-        // at 5 there too because what a plan may be used for (batches, tilings, windows)
-        // follows from its path.
+        // The line holds for the beam.  Without one it is too low (the two cross at 8 to
+        // 16), but a plan's path decides which calls it takes: windows too wide for the
+        // GEMM run on the phasor path only, and batches and tilings refuse a phasor plan.
         std::vector<int> uu(bins, bins + nsel);
         std::sort(uu.begin(), uu.end());
         const int64_t nu = std::unique(uu.begin(), uu.end()) - uu.begin();
