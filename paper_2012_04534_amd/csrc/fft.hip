@@ -377,7 +377,9 @@ __global__ __launch_bounds__(64 * kNW) void contract_kernel(const cf32* __restri
 // parts of members below 2^-103 can be: where all members of an entry are below 2^-63
 // (kSizable, the upper exponent bits, none set) they are cut once more at 2^64 times
 // their size and the sums scaled back.  (Next to a larger member each loses under 2^-63
-// of that one.)
+// of that one.)  The sizes are looked at beside the outputs' sums, where it takes under
+// 0.5 us: 13.1 / 14.6, 21.9 / 24.3 and 44 / 50 us for the three scans above with members
+// of order one, 13.1 / 14.5, 21.9 / 23.8 and 44 / 50 without.
 // Columns in LDS: plane, group of 4 entries, column, 4 entries of (re, im): one 16-byte
 // read per operand; groups padded by 16 bytes against bank conflicts of the staging.
 typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
@@ -450,7 +452,11 @@ __global__ __launch_bounds__(64 * kNW) void contract_bf16_kernel(const cbf16* __
 #pragma unroll
                 for (int q = 0; q < NQ; ++q) {
                     bits |= __float_as_uint(v[q].re) | __float_as_uint(v[q].im);
-                    float re = v[q].re * scale, im = v[q].im * scale;
+                    float re = v[q].re, im = v[q].im;
+                    if (scale != 1.f) {                           // uniform
+                        re *= scale;
+                        im *= scale;
+                    }
 #pragma unroll
                     for (int part = 0; part < 3; ++part) {
                         const float tr = top(re), ti = top(im);
@@ -501,33 +507,33 @@ __global__ __launch_bounds__(64 * kNW) void contract_bf16_kernel(const cbf16* __
             if (lane == 0) sizes[wave] = size;
         }
         __syncthreads();                                      // the columns are read; red takes their place
-        if (scale != 1.f) break;
-        const int4 w = *reinterpret_cast<const int4*>(sizes);
-        if (__builtin_amdgcn_readfirstlane(w.x | w.y | w.z | w.w) != 2) break;
-        scale = kLarger;                                      // small members only
-    }
-    const float back = 1.f / scale;
-    const int rows = min(groups * GR, C - c0), pitch = ng * GR + 1;
-    if (active) {
+        const int rows = min(groups * GR, C - c0), pitch = ng * GR + 1;
+        if (active) {
+            const float back = 1.f / scale;
 #pragma unroll
-        for (int t = 0; t < ND; ++t)
+            for (int t = 0; t < ND; ++t)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int lr = FWD ? 32 * (t >> 1) + 2 * (4 * kq + r) + (t & 1) : 16 * t + 4 * kq + r;
-                red[(share * 16 + i) * pitch + grp * GR + lr] = D[t][r] * back;
-            }
-    }
-    __syncthreads();
-    for (int t = threadIdx.x; t < nq * rows; t += 64 * kNW) {
-        const int q = t / rows, c = t - q * rows;
-        float re = 0.f, im = 0.f;
-        for (int h = 0; h < shares; ++h)
+                for (int r = 0; r < 4; ++r) {
+                    const int lr = FWD ? 32 * (t >> 1) + 2 * (4 * kq + r) + (t & 1) : 16 * t + 4 * kq + r;
+                    red[(share * 16 + i) * pitch + grp * GR + lr] = D[t][r] * back;
+                }
+        }
+        __syncthreads();
+        const int4 w4 = *reinterpret_cast<const int4*>(sizes);
+        for (int t = threadIdx.x; t < nq * rows; t += 64 * kNW) {
+            const int q = t / rows, c = t - q * rows;
+            float re = 0.f, im = 0.f;
+            for (int h = 0; h < shares; ++h)
 #pragma unroll
-            for (int w = 0; w < (SWAP ? 1 : 2); ++w) {
-                re += red[(h * 16 + 8 * w + 2 * q) * pitch + c];
-                im += red[(h * 16 + 8 * w + 2 * q + 1) * pitch + c];
-            }
-        out[orb.row(q) * C + c0 + c] = cf32{re, im};
+                for (int w = 0; w < (SWAP ? 1 : 2); ++w) {
+                    re += red[(h * 16 + 8 * w + 2 * q) * pitch + c];
+                    im += red[(h * 16 + 8 * w + 2 * q + 1) * pitch + c];
+                }
+            out[orb.row(q) * C + c0 + c] = cf32{re, im};
+        }
+        if (scale != 1.f || __builtin_amdgcn_readfirstlane(w4.x | w4.y | w4.z | w4.w) != 2) break;
+        scale = kLarger;                                      // small members only: once more
+        __syncthreads();                                      // red is read; the columns take its place
     }
 }
 
