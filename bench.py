@@ -46,27 +46,30 @@ PEAK_PHASOR_TERMS = 256 * 4 * 16 * 2.4e9 / PHASOR_SLOTS_PER_TERM
 # source it was measured on; a changed source or another tiling reports null.
 TRAFFIC = {
     # 32 x 32 C-scan, FP32 union-GEMM, shipped tiling (profiles/cscan32_fp32_gemm.md)
-    "cscan32/gemm/forward/fs12-zs8-nw4-np4-zc16": {"bytes": 82.138e6, "sha": "b05960bd38ee0604"},
-    "cscan32/gemm/adjoint/as32-np4-kc8-nw4": {"bytes": 79.488e6, "sha": "b05960bd38ee0604"},
+    "cscan32/gemm/forward/fs12-zs8-nw4-np4-zc16": {"bytes": 82.529e6, "sha": "99b98f25ae46cafa"},
+    "cscan32/gemm/adjoint/as32-np4-kc8-nw4": {"bytes": 79.707e6, "sha": "99b98f25ae46cafa"},
+    # 64 x 64 C-scan (profiles/cscan64_fp32_gemm.md)
+    "cscan64/gemm/forward/fs6-zs8-nw4-np4-zc16": {"bytes": 219.210e6, "sha": "99b98f25ae46cafa"},
+    "cscan64/gemm/adjoint/as16-np4-kc16-nw4": {"bytes": 277.596e6, "sha": "99b98f25ae46cafa"},
     # transform-domain contraction (profiles/cscan32_fp32_transform.md, cscan64_fp32_transform.md):
     # the table once plus the transform rows in and out
-    "cscan32/transform/forward/fs1-zs1-nw1-np0-zc0": {"bytes": 82.099e6, "sha": "0d6bade0c9430185"},
-    "cscan32/transform/adjoint/as1-np0-kc0-nw0": {"bytes": 90.289e6, "sha": "0d6bade0c9430185"},
-    "cscan64/transform/forward/fs1-zs1-nw1-np0-zc0": {"bytes": 484.320e6, "sha": "0d6bade0c9430185"},
-    "cscan64/transform/adjoint/as1-np0-kc0-nw0": {"bytes": 530.790e6, "sha": "0d6bade0c9430185"},
+    "cscan32/transform/forward/fs1-zs1-nw1-np0-zc0": {"bytes": 82.259e6, "sha": "59811daac8b9428b"},
+    "cscan32/transform/adjoint/as1-np0-kc0-nw0": {"bytes": 91.067e6, "sha": "59811daac8b9428b"},
+    "cscan64/transform/forward/fs1-zs1-nw1-np0-zc0": {"bytes": 484.323e6, "sha": "59811daac8b9428b"},
+    "cscan64/transform/adjoint/as1-np0-kc0-nw0": {"bytes": 530.794e6, "sha": "59811daac8b9428b"},
     # the same with the BF16 table (profiles/cscan32_bf16_transform.md, cscan64_bf16_transform.md)
-    "cscan32/transform-bf16/adjoint/as1-np0-kc0-nw0": {"bytes": 51.100e6, "sha": "0d6bade0c9430185"},
-    "cscan32/transform-bf16/forward/fs1-zs1-nw1-np0-zc0": {"bytes": 46.165e6, "sha": "0d6bade0c9430185"},
-    "cscan64/transform-bf16/adjoint/as1-np0-kc0-nw0": {"bytes": 278.593e6, "sha": "0d6bade0c9430185"},
-    "cscan64/transform-bf16/forward/fs1-zs1-nw1-np0-zc0": {"bytes": 258.671e6, "sha": "0d6bade0c9430185"},
+    "cscan32/transform-bf16/adjoint/as1-np0-kc0-nw0": {"bytes": 50.911e6, "sha": "59811daac8b9428b"},
+    "cscan32/transform-bf16/forward/fs1-zs1-nw1-np0-zc0": {"bytes": 46.163e6, "sha": "59811daac8b9428b"},
+    "cscan64/transform-bf16/adjoint/as1-np0-kc0-nw0": {"bytes": 278.595e6, "sha": "59811daac8b9428b"},
+    "cscan64/transform-bf16/forward/fs1-zs1-nw1-np0-zc0": {"bytes": 258.679e6, "sha": "59811daac8b9428b"},
     # BF16 GEMMs with phasor tables (profiles/cscan32_bf16_gemm.md, cscan64_bf16_gemm.md):
     # mostly re-reads of the table tiles, one per workgroup and offset (the
     # tables, 170 MB at 32 x 32, sit in the last-level cache); the 32 x 32
     # forward is two launches (full bin tiles, then the short last one)
-    "cscan32/gemm-bf16/forward/fs12-zs8-wr1": {"bytes": 285.597e6, "sha": "6a80aa6837cf854b"},
-    "cscan32/gemm-bf16/adjoint/as12-wr1-nz2": {"bytes": 803.770e6, "sha": "6a80aa6837cf854b"},
-    "cscan64/gemm-bf16/forward/fs2-zs8-wr1": {"bytes": 508.500e6, "sha": "6a80aa6837cf854b"},
-    "cscan64/gemm-bf16/adjoint/as3-wr1-nz2": {"bytes": 680.896e6, "sha": "6a80aa6837cf854b"},
+    "cscan32/gemm-bf16/forward/fs12-zs8-wr1": {"bytes": 285.967e6, "sha": "6a80aa6837cf854b"},
+    "cscan32/gemm-bf16/adjoint/as12-wr1-nz2": {"bytes": 803.656e6, "sha": "6a80aa6837cf854b"},
+    "cscan64/gemm-bf16/forward/fs2-zs8-wr1": {"bytes": 509.592e6, "sha": "6a80aa6837cf854b"},
+    "cscan64/gemm-bf16/adjoint/as3-wr1-nz2": {"bytes": 681.340e6, "sha": "6a80aa6837cf854b"},
 }
 TRAFFIC_SRC = {"gemm": "paper_2012_04534_amd/csrc/gemm_f32.hip",
                "transform": "paper_2012_04534_amd/csrc/fft.hip",
